@@ -493,8 +493,8 @@ struct SpanKLegs {
 // Layout [span][lane] with LANES lanes per workgroup, so a wave's accesses are contiguous.
 template <int L, int LANES>
 struct SpanKLds {
-  float4* kt;  // &table[0][lane]
-  float* pt;   // &props[0][lane]
+  float4* kt;  // &table[0][lane], every span but the full one
+  float* pt;   // &props[0][lane], spans of 2..L-1 legs
   __device__ __forceinline__ void fill(const double (&k)[L][4]) {
     using SP = Spans<L>;
     static_for<0, L>([&](auto ac) {
@@ -503,11 +503,13 @@ struct SpanKLds {
       kt[SP::at(a, a) * LANES] = make_float4(float(acc[0]), float(-acc[1]), float(-acc[2]), float(-acc[3]));
       static_for<a + 1, L>([&](auto bc) {
         constexpr int b = decltype(bc)::value;
+        if constexpr (b - a + 1 < L) {
 #pragma unroll
-        for (int mu = 0; mu < 4; ++mu) acc[mu] += k[b][mu];
-        kt[SP::at(a, b) * LANES] = make_float4(float(acc[0]), float(-acc[1]), float(-acc[2]), float(-acc[3]));
-        // K^2 in FP64, its reciprocal in FP32 (within 1 ulp of the rounded K^2's)
-        if (b - a + 1 < L) pt[SP::at(a, b) * LANES] = __builtin_amdgcn_rcpf(float(minkowski_sq(acc)));
+          for (int mu = 0; mu < 4; ++mu) acc[mu] += k[b][mu];
+          kt[SP::at(a, b) * LANES] = make_float4(float(acc[0]), float(-acc[1]), float(-acc[2]), float(-acc[3]));
+          // K^2 in FP64, its reciprocal in FP32 (within 1 ulp of the rounded K^2's)
+          pt[(SP::at(a, b) - L) * LANES] = __builtin_amdgcn_rcpf(float(minkowski_sq(acc)));
+        }
       });
     });
   }
@@ -521,7 +523,7 @@ struct SpanKLds {
   }
   template <int A, int B>
   __device__ __forceinline__ float prop() const {
-    return pt[Spans<L>::at(A, B) * LANES];
+    return pt[(Spans<L>::at(A, B) - L) * LANES];
   }
 };
 
@@ -531,30 +533,92 @@ struct SpanKLds {
 __device__ __forceinline__ float fmac(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmac(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// A leaf current, the helicity source of one leg (polarisation()), has three zero words of its
+// eight: re[0], im[0] and im[3].  The products below take LX / LY = true for a leaf operand and
+// leave out the terms that hold one of those zeros; a term +-0 leaves an fma chain as it was, so
+// every value is the one the full chain gives.  That is 1335 of the recursion's 8072 FP32
+// instructions at n = 8 (17%) and 21 of its registers: FP32 n = 8 recursion kernel, one wave per
+// SIMD and bound by VALU issue, 1.232 -> 1.069 ms per 2^22 events.
+
 // r + i i = x . y, bilinear with the metric (+,-,-,-)
-template <typename T>
+template <bool LX = false, bool LY = false, typename T>
 __device__ __forceinline__ void cdot(const cv4<T>& x, const cv4<T>& y, T& r, T& i) {
-  r = fmac(-x.im[0], y.im[0], x.re[0] * y.re[0]);
-  i = fmac(x.im[0], y.re[0], x.re[0] * y.im[0]);
-#pragma unroll
-  for (int mu = 1; mu < 4; ++mu) {
-    r = fmac(-x.re[mu], y.re[mu], r);
-    r = fmac(x.im[mu], y.im[mu], r);
-    i = fmac(-x.re[mu], y.im[mu], i);
-    i = fmac(-x.im[mu], y.re[mu], i);
+  if constexpr (LX || LY) {
+    r = -x.re[1] * y.re[1];
+    i = -x.re[1] * y.im[1];
+  } else {
+    r = fmac(-x.im[0], y.im[0], x.re[0] * y.re[0]);
+    i = fmac(x.im[0], y.re[0], x.re[0] * y.im[0]);
+    r = fmac(-x.re[1], y.re[1], r);
+    i = fmac(-x.re[1], y.im[1], i);
   }
+  r = fmac(x.im[1], y.im[1], r);
+  i = fmac(-x.im[1], y.re[1], i);
+  r = fmac(-x.re[2], y.re[2], r);
+  r = fmac(x.im[2], y.im[2], r);
+  i = fmac(-x.re[2], y.im[2], i);
+  i = fmac(-x.im[2], y.re[2], i);
+  r = fmac(-x.re[3], y.re[3], r);
+  if constexpr (!LX && !LY) r = fmac(x.im[3], y.im[3], r);
+  if constexpr (!LY) i = fmac(-x.re[3], y.im[3], i);
+  if constexpr (!LX) i = fmac(-x.im[3], y.re[3], i);
+}
+
+// The same dot with its imaginary part returned negated (ni = -i, exactly: every step is the
+// negation of cdot's), for products whose consumer then needs no negated operand.
+template <bool LX = false, bool LY = false, typename T>
+__device__ __forceinline__ void cdot_ni(const cv4<T>& x, const cv4<T>& y, T& r, T& ni) {
+  if constexpr (LX || LY) {
+    r = -x.re[1] * y.re[1];
+    ni = x.re[1] * y.im[1];
+  } else {
+    r = fmac(-x.im[0], y.im[0], x.re[0] * y.re[0]);
+    ni = fmac(-x.im[0], y.re[0], -x.re[0] * y.im[0]);
+    r = fmac(-x.re[1], y.re[1], r);
+    ni = fmac(x.re[1], y.im[1], ni);
+  }
+  r = fmac(x.im[1], y.im[1], r);
+  ni = fmac(x.im[1], y.re[1], ni);
+  r = fmac(-x.re[2], y.re[2], r);
+  r = fmac(x.im[2], y.im[2], r);
+  ni = fmac(x.re[2], y.im[2], ni);
+  ni = fmac(x.im[2], y.re[2], ni);
+  r = fmac(-x.re[3], y.re[3], r);
+  if constexpr (!LX && !LY) r = fmac(x.im[3], y.im[3], r);
+  if constexpr (!LY) ni = fmac(x.re[3], y.im[3], ni);
+  if constexpr (!LX) ni = fmac(x.im[3], y.re[3], ni);
 }
 
 // r + i i = x . k for a real four-vector k given covariant (k_mu = g_mu k^mu)
-template <typename T>
+template <bool LX = false, typename T>
 __device__ __forceinline__ void rdot(const cv4<T>& x, const T k[4], T& r, T& i) {
-  r = x.re[0] * k[0];
-  i = x.im[0] * k[0];
-#pragma unroll
-  for (int mu = 1; mu < 4; ++mu) {
-    r = fmac(x.re[mu], k[mu], r);
-    i = fmac(x.im[mu], k[mu], i);
+  if constexpr (LX) {
+    r = x.re[1] * k[1];
+    i = x.im[1] * k[1];
+  } else {
+    r = fmac(x.re[1], k[1], x.re[0] * k[0]);
+    i = fmac(x.im[1], k[1], x.im[0] * k[0]);
   }
+  r = fmac(x.re[2], k[2], r);
+  i = fmac(x.im[2], k[2], i);
+  r = fmac(x.re[3], k[3], r);
+  if constexpr (!LX) i = fmac(x.im[3], k[3], i);
+}
+
+// x . k with k covariant, its real part returned negated (nr = -r, exactly)
+template <bool LX = false, typename T>
+__device__ __forceinline__ void rdot_nr(const cv4<T>& x, const T k[4], T& nr, T& i) {
+  if constexpr (LX) {
+    nr = -x.re[1] * k[1];
+    i = x.im[1] * k[1];
+  } else {
+    nr = fmac(-x.re[1], k[1], -x.re[0] * k[0]);
+    i = fmac(x.im[1], k[1], x.im[0] * k[0]);
+  }
+  nr = fmac(-x.re[2], k[2], nr);
+  i = fmac(x.im[2], k[2], i);
+  nr = fmac(-x.re[3], k[3], nr);
+  if constexpr (!LX) i = fmac(x.im[3], k[3], i);
 }
 
 // K_A - K_B contravariant, from covariant K_A, K_B (exact: only signs differ)
@@ -563,51 +627,32 @@ __device__ __forceinline__ T kdiff(const T (&ka)[4], const T (&kb)[4], int mu) {
   return mu == 0 ? ka[0] - kb[0] : kb[mu] - ka[mu];
 }
 
-// The same dot with its imaginary part returned negated (ni = -i, exactly: every step is the
-// negation of cdot's), for products whose consumer then needs no negated operand.
-template <typename T>
-__device__ __forceinline__ void cdot_ni(const cv4<T>& x, const cv4<T>& y, T& r, T& ni) {
-  r = fmac(-x.im[0], y.im[0], x.re[0] * y.re[0]);
-  ni = fmac(-x.im[0], y.re[0], -x.re[0] * y.im[0]);
+// acc += (cr + i ci) * y
+template <bool LY = false, typename T>
+__device__ __forceinline__ void caxpy(T cr, T ci, const cv4<T>& y, cv4<T>& acc) {
 #pragma unroll
-  for (int mu = 1; mu < 4; ++mu) {
-    r = fmac(-x.re[mu], y.re[mu], r);
-    r = fmac(x.im[mu], y.im[mu], r);
-    ni = fmac(x.re[mu], y.im[mu], ni);
-    ni = fmac(x.im[mu], y.re[mu], ni);
-  }
-}
-
-// x . k with k covariant, its real part returned negated (nr = -r, exactly)
-template <typename T>
-__device__ __forceinline__ void rdot_nr(const cv4<T>& x, const T k[4], T& nr, T& i) {
-  nr = -x.re[0] * k[0];
-  i = x.im[0] * k[0];
-#pragma unroll
-  for (int mu = 1; mu < 4; ++mu) {
-    nr = fmac(-x.re[mu], k[mu], nr);
-    i = fmac(x.im[mu], k[mu], i);
+  for (int mu = LY ? 1 : 0; mu < 4; ++mu) {
+    acc.re[mu] = fmac(cr, y.re[mu], acc.re[mu]);
+    if (!(LY && mu == 3)) {
+      acc.re[mu] = fmac(-ci, y.im[mu], acc.re[mu]);
+      acc.im[mu] = fmac(cr, y.im[mu], acc.im[mu]);
+    }
+    acc.im[mu] = fmac(ci, y.re[mu], acc.im[mu]);
   }
 }
 
 // acc += (cr - i nci) * y, the conjugate-sign form of caxpy (same roundings as
 // caxpy(cr, -nci, y, acc))
-template <typename T>
+template <bool LY = false, typename T>
 __device__ __forceinline__ void caxpy_nci(T cr, T nci, const cv4<T>& y, cv4<T>& acc) {
 #pragma unroll
-  for (int mu = 0; mu < 4; ++mu) {
-    acc.re[mu] = fmac(nci, y.im[mu], fmac(cr, y.re[mu], acc.re[mu]));
-    acc.im[mu] = fmac(-nci, y.re[mu], fmac(cr, y.im[mu], acc.im[mu]));
-  }
-}
-
-// acc += (cr + i ci) * y
-template <typename T>
-__device__ __forceinline__ void caxpy(T cr, T ci, const cv4<T>& y, cv4<T>& acc) {
-#pragma unroll
-  for (int mu = 0; mu < 4; ++mu) {
-    acc.re[mu] = fmac(-ci, y.im[mu], fmac(cr, y.re[mu], acc.re[mu]));
-    acc.im[mu] = fmac(ci, y.re[mu], fmac(cr, y.im[mu], acc.im[mu]));
+  for (int mu = LY ? 1 : 0; mu < 4; ++mu) {
+    acc.re[mu] = fmac(cr, y.re[mu], acc.re[mu]);
+    if (!(LY && mu == 3)) {
+      acc.re[mu] = fmac(nci, y.im[mu], acc.re[mu]);
+      acc.im[mu] = fmac(cr, y.im[mu], acc.im[mu]);
+    }
+    acc.im[mu] = fmac(-nci, y.re[mu], acc.im[mu]);
   }
 }
 
@@ -631,15 +676,16 @@ __device__ __forceinline__ void span_vertex(const KS& ks, const cv4<T> (&J)[Span
   static_for<A, B>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
+    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
     T ka[4], kb[4];
     ks.template K<A, i>(ka);
     ks.template K<i + 1, B>(kb);
     T dr, di, ar, ai, nbr, bi;
-    cdot(J[PA], J[PB], dr, di);
-    rdot(J[PA], kb, ar, ai);
-    rdot_nr(J[PB], ka, nbr, bi);
-    caxpy(ar, ai, J[PB], X);
-    caxpy_nci(nbr, bi, J[PA], X);  // X -= (J[PB].K_A) J[PA]
+    cdot<LA, LB>(J[PA], J[PB], dr, di);
+    rdot<LA>(J[PA], kb, ar, ai);
+    rdot_nr<LB>(J[PB], ka, nbr, bi);
+    caxpy<LB>(ar, ai, J[PB], X);
+    caxpy_nci<LA>(nbr, bi, J[PA], X);  // X -= (J[PB].K_A) J[PA]
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
       const T dk = kdiff(ka, kb, mu);
@@ -655,20 +701,20 @@ __device__ __forceinline__ void span_vertex(const KS& ks, const cv4<T> (&J)[Span
     static_for<i + 1, B>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
       T dr, ndi;
-      cdot_ni(J[SP::at(A, i)], J[SP::at(j + 1, B)], dr, ndi);
-      caxpy_nci(dr, ndi, J[SP::at(i + 1, j)], X);
+      cdot_ni<i == A, j + 1 == B>(J[SP::at(A, i)], J[SP::at(j + 1, B)], dr, ndi);
+      caxpy_nci<i + 1 == j>(dr, ndi, J[SP::at(i + 1, j)], X);
     });
   });
   // -(JA.JB) JC and -(JC.JB) JA through the span scalars S
   static_for<A + 1, B>([&](auto jc) {
     constexpr int j = decltype(jc)::value;
     constexpr int Sx = SP::at(A, j);
-    caxpy(Sr[Sx], Si[Sx], J[SP::at(j + 1, B)], Y);
+    caxpy<j + 1 == B>(Sr[Sx], Si[Sx], J[SP::at(j + 1, B)], Y);
   });
   static_for<A, B - 1>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     constexpr int Sx = SP::at(i + 1, B);
-    caxpy(Sr[Sx], Si[Sx], J[SP::at(A, i)], Y);
+    caxpy<i == A>(Sr[Sx], Si[Sx], J[SP::at(A, i)], Y);
   });
 #pragma unroll
   for (int mu = 0; mu < 4; ++mu) {
@@ -718,7 +764,7 @@ __device__ __forceinline__ void bg_amplitude(const KS& ks, const cv4<T> (&src)[L
   cv4<T> V;
   bg_forward<L, T>(ks, src, J, Sr, Si, V);
   T mr, mi;
-  cdot(eps0, V, mr, mi);
+  cdot<true, false>(eps0, V, mr, mi);
   m_re = double(mr);
   m_im = double(mi);
 }
@@ -773,29 +819,36 @@ __device__ __forceinline__ rv4<T> real_polarisation(const double p[4], T c, T s)
   return e;
 }
 
-// x . y (metric (+,-,-,-)) of real four-vectors
-template <typename T>
+// x . y (metric (+,-,-,-)) of real four-vectors.  LEAF: one of them is the source of one leg
+// (v[0] = 0), whose zero term is left out, here and in the two products below.
+template <bool LEAF = false, typename T>
 __device__ __forceinline__ T vdot(const rv4<T>& x, const rv4<T>& y) {
-  T r = x.v[0] * y.v[0];
-  r = fmac(-x.v[1], y.v[1], r);
+  T r;
+  if constexpr (LEAF)
+    r = -x.v[1] * y.v[1];
+  else
+    r = fmac(-x.v[1], y.v[1], x.v[0] * y.v[0]);
   r = fmac(-x.v[2], y.v[2], r);
   return fmac(-x.v[3], y.v[3], r);
 }
 
 // x . k for k given covariant
-template <typename T>
+template <bool LEAF = false, typename T>
 __device__ __forceinline__ T vdot_cov(const rv4<T>& x, const T (&k)[4]) {
-  T r = x.v[0] * k[0];
-  r = fmac(x.v[1], k[1], r);
+  T r;
+  if constexpr (LEAF)
+    r = x.v[1] * k[1];
+  else
+    r = fmac(x.v[1], k[1], x.v[0] * k[0]);
   r = fmac(x.v[2], k[2], r);
   return fmac(x.v[3], k[3], r);
 }
 
 // acc += c y
-template <typename T>
+template <bool LEAF = false, typename T>
 __device__ __forceinline__ void vaxpy(T c, const rv4<T>& y, rv4<T>& acc) {
 #pragma unroll
-  for (int mu = 0; mu < 4; ++mu) acc.v[mu] = fmac(c, y.v[mu], acc.v[mu]);
+  for (int mu = LEAF ? 1 : 0; mu < 4; ++mu) acc.v[mu] = fmac(c, y.v[mu], acc.v[mu]);
 }
 
 // One span [A..B] with real currents: its bracket sum V (regrouped as span_vertex; span
@@ -815,9 +868,10 @@ __device__ __forceinline__ void span_vertex_r(const KS& ks, const rv4<T> (&J)[Sp
     T ka[4], kb[4];
     ks.template K<A, i>(ka);
     ks.template K<i + 1, B>(kb);
-    const T d = vdot(J[PA], J[PB]);
-    vaxpy(vdot_cov(J[PA], kb), J[PB], X);
-    vaxpy(-vdot_cov(J[PB], ka), J[PA], X);
+    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
+    const T d = vdot<LA || LB>(J[PA], J[PB]);
+    vaxpy<LB>(vdot_cov<LA>(J[PA], kb), J[PB], X);
+    vaxpy<LA>(-vdot_cov<LB>(J[PB], ka), J[PA], X);
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) Y.v[mu] = fmac(d, kdiff(ka, kb, mu), Y.v[mu]);
     sv -= d;
@@ -826,16 +880,16 @@ __device__ __forceinline__ void span_vertex_r(const KS& ks, const rv4<T> (&J)[Sp
     constexpr int i = decltype(ic)::value;
     static_for<i + 1, B>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      vaxpy(vdot(J[SP::at(A, i)], J[SP::at(j + 1, B)]), J[SP::at(i + 1, j)], X);
+      vaxpy<i + 1 == j>(vdot<i == A || j + 1 == B>(J[SP::at(A, i)], J[SP::at(j + 1, B)]), J[SP::at(i + 1, j)], X);
     });
   });
   static_for<A + 1, B>([&](auto jc) {
     constexpr int j = decltype(jc)::value;
-    vaxpy(S[SP::at(A, j)], J[SP::at(j + 1, B)], Y);
+    vaxpy<j + 1 == B>(S[SP::at(A, j)], J[SP::at(j + 1, B)], Y);
   });
   static_for<A, B - 1>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
-    vaxpy(S[SP::at(i + 1, B)], J[SP::at(A, i)], Y);
+    vaxpy<i == A>(S[SP::at(i + 1, B)], J[SP::at(A, i)], Y);
   });
 #pragma unroll
   for (int mu = 0; mu < 4; ++mu) V.v[mu] = fmac(T(2), X.v[mu], Y.v[mu]);
@@ -864,7 +918,7 @@ __device__ __forceinline__ double bg_amplitude_r(const KS& ks, const rv4<T> (&sr
   rv4<T> V;
   T sv;
   span_vertex_r<L, 0, L - 1, T>(ks, J, S, V, sv);
-  return double(vdot(eps0, V));
+  return double(vdot<true>(eps0, V));
 }
 
 // ----------------------------------------------------------------------------------------

@@ -395,11 +395,12 @@ struct UseLdsK {
   static constexpr bool value = lds_span_table(N, std::is_same<T, float>::value ? 32 : 64);
 };
 
-// The LDS span table of one workgroup (only instantiated where UseLdsK holds).
+// The LDS span table of one workgroup (only instantiated where UseLdsK holds): momenta of every
+// span but the full one, propagators of the spans of 2..N-2 legs.
 template <int N>
 struct LdsTable {
-  float4 k[Spans<N - 1>::count * kLdsLanes];
-  float p[Spans<N - 1>::count * kLdsLanes];
+  float4 k[(Spans<N - 1>::count - 1) * kLdsLanes];
+  float p[(Spans<N - 1>::count - N) * kLdsLanes];
 };
 
 template <int N, typename T, bool LDS>
@@ -556,29 +557,39 @@ __device__ __forceinline__ double ordered_amp2_g(const double (&p)[N][4], const 
 }
 
 // Compensated (sum w, sum w^2) of a workgroup of up to 256 lanes, in a fixed tree order;
-// thread 0 stores (s, c, s2, c2) to dst.
+// thread 0 stores (s, c, s2, c2) to dst.  A wave whose lanes all hold zeros (every event failed
+// the cuts: 80% of the waves of 64 events at n = 8 and sqrt(S) = 14 TeV) has zero sums and
+// skips its six exchange steps, a chain of some 1500 cycles that one wave per SIMD cannot hide;
+// a workgroup of one wave needs no exchange through LDS.
 __device__ __forceinline__ void block_reduce_store(CSum w, CSum w2, double* dst) {
-  __shared__ double red[4][4];
+  if (__any(w.s != 0.0 || w.c != 0.0 || w2.s != 0.0 || w2.c != 0.0)) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    CSum ow{__shfl_down(w.s, off), __shfl_down(w.c, off)};
-    CSum ow2{__shfl_down(w2.s, off), __shfl_down(w2.c, off)};
-    w = cs_add(w, ow);
-    w2 = cs_add(w2, ow2);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[wave][0] = w.s; red[wave][1] = w.c; red[wave][2] = w2.s; red[wave][3] = w2.c;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    CSum a{red[0][0], red[0][1]}, b{red[0][2], red[0][3]};
-    const int nw = (int)(blockDim.x >> 6);
-    for (int v = 1; v < nw; ++v) {
-      a = cs_add(a, CSum{red[v][0], red[v][1]});
-      b = cs_add(b, CSum{red[v][2], red[v][3]});
+    for (int off = 32; off >= 1; off >>= 1) {
+      CSum ow{__shfl_down(w.s, off), __shfl_down(w.c, off)};
+      CSum ow2{__shfl_down(w2.s, off), __shfl_down(w2.c, off)};
+      w = cs_add(w, ow);
+      w2 = cs_add(w2, ow2);
     }
-    dst[0] = a.s; dst[1] = a.c; dst[2] = b.s; dst[3] = b.c;
+  }
+  if (blockDim.x > 64) {
+    __shared__ double red[4][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) {
+      red[wave][0] = w.s; red[wave][1] = w.c; red[wave][2] = w2.s; red[wave][3] = w2.c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      w = CSum{red[0][0], red[0][1]};
+      w2 = CSum{red[0][2], red[0][3]};
+      const int nw = (int)(blockDim.x >> 6);
+      for (int v = 1; v < nw; ++v) {
+        w = cs_add(w, CSum{red[v][0], red[v][1]});
+        w2 = cs_add(w2, CSum{red[v][2], red[v][3]});
+      }
+    }
+  }
+  if (threadIdx.x == 0) {
+    dst[0] = w.s; dst[1] = w.c; dst[2] = w2.s; dst[3] = w2.c;
   }
 }
 
@@ -663,13 +674,24 @@ __device__ __forceinline__ double generate_one(const GenClass& C, int64_t i, Per
   return finish_event<N>(C, i, pass, a2, ev.shat, ev.x1, ev.x2, scale_ratio<N>(C, ht, ev.x1, ev.x2));
 }
 
+// Waves per SIMD the compiler may leave room for in the one-lane recursion kernels.  A limit of
+// one pads the register allocation beyond 256, so that a second wave never fits, and is kept
+// only where the recursion needs that many: below, several waves hide the latency of the loads
+// and of the FP64 chains (n = 4 FP32 recursion kernel, 2^22 events: 242 us at one wave, 170 us
+// at seven, HBM bound).
+template <int N, typename T, int POL>
+constexpr int rec_waves() {
+  constexpr int words = (Spans<N - 1>::count * (POL == 0 ? 8 : 4) + 2 * N) * (int)(sizeof(T) / 4);
+  return words > 210 ? 1 : 8;
+}
+
 // Single-class generation of a class without the span table (FP32 n = 9, FP64 n <= 6): one
 // event per lane, one compensated partial per workgroup.  Launch: blockDim.x in
 // {64, 128, 192, 256} with perm_lds_bytes(N, blockDim.x) bytes of dynamic LDS; partials may
 // be NULL.
 template <int N, typename T, int POL = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_generate(GenClass C,
-                                                                                            double* partials) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, T, POL>()))) void k_generate(
+    GenClass C, double* partials) {
   static_assert(!UseLdsK<N, T>::value, "the table classes generate in the split form");
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double w = 0.0;
@@ -679,10 +701,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 // |A|^2 from given momenta (bg_amp2): momenta [count][N][4] physical, gathered in colour order.
 template <int N, typename T>
-__global__ __launch_bounds__((UseLdsK<N, T>::value ? kLdsLanes : 256)) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_amp2(int64_t count, const double* __restrict__ mom,
-                                                const uint32_t* __restrict__ hel,
-                                                const uint8_t* __restrict__ order,
-                                                double* __restrict__ out) {
+__global__ __launch_bounds__((UseLdsK<N, T>::value ? kLdsLanes : 256))
+    __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, T, 0>()))) void k_amp2(
+        int64_t count, const double* __restrict__ mom, const uint32_t* __restrict__ hel,
+        const uint8_t* __restrict__ order, double* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   double p[N][4];

@@ -174,7 +174,7 @@ template <int N>
 constexpr bool rec_prefetch() { return N >= 8; }
 
 template <int N, int POL>
-__global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_rec(
+__global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, float, POL>()))) void k_rec(
     GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials, int64_t ahead) {
   __shared__ LdsTable<N> tab;
   __shared__ unsigned int scrap[rec_prefetch<N>() ? kLdsLanes : 1];

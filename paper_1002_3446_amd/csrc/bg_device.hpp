@@ -46,7 +46,9 @@ __device__ __forceinline__ u32x4 philox4x32(uint32_t c0, uint32_t c1, uint32_t c
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
     const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
     const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    // three-way exclusive or (truth table 0x96) in one instruction
+    const uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);
+    const uint32_t n2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
     c0 = n0;
     c1 = lo1;
     c2 = n2;
@@ -58,7 +60,7 @@ __device__ __forceinline__ u32x4 philox4x32(uint32_t c0, uint32_t c1, uint32_t c
 }
 
 // word -> (r + 1/2) 2^-32, exact in double and strictly inside (0, 1)
-__device__ __forceinline__ double u01(uint32_t r) { return ((double)r + 0.5) * 0x1p-32; }
+__device__ __forceinline__ double u01(uint32_t r) { return ((double)r + 0.5) * coef(0x1p-32); }
 
 // Draw layout of one event: counter (block, event lo, event hi, n), key (seed lo, seed hi).
 //   block 0: x1 uniform, x2 uniform, helicity word, unused
@@ -70,27 +72,33 @@ struct EventRng {
 };
 
 // ----------------------------------------------------------------------------------------
-// Colour ordering as nibbles: nibble i holds the leg at recursion position i+1 (legs 1..n-1).
+// Colour ordering as nibbles: nibble i holds the leg at recursion position i+1 (legs 1..n-1), in
+// one word while all fit (64-bit shifts by a variable count take four times the issue slots).
 // ----------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t nib(uint64_t A, int i) { return (uint32_t)(A >> (4 * i)) & 15u; }
-__device__ __forceinline__ uint64_t set_nib(uint64_t A, int i, uint32_t v) {
-  const uint64_t m = 15ull << (4 * i);
-  return (A & ~m) | ((uint64_t)v << (4 * i));
+template <int N>
+using OrderWord = typename std::conditional<(N <= 9), uint32_t, uint64_t>::type;
+
+template <typename W>
+__device__ __forceinline__ uint32_t nib(W A, int i) { return (uint32_t)(A >> (4 * i)) & 15u; }
+template <typename W>
+__device__ __forceinline__ W set_nib(W A, int i, uint32_t v) {
+  const W m = W(15) << (4 * i);
+  return (A & ~m) | ((W)v << (4 * i));
 }
 
 template <int N>
-__device__ __forceinline__ uint64_t identity_order() {
-  uint64_t A = 0;
+__device__ __forceinline__ OrderWord<N> identity_order() {
+  OrderWord<N> A = 0;
 #pragma unroll
-  for (int i = 0; i < N - 1; ++i) A |= (uint64_t)(i + 1) << (4 * i);
+  for (int i = 0; i < N - 1; ++i) A |= (OrderWord<N>)(i + 1) << (4 * i);
   return A;
 }
 
 // Fisher-Yates over positions 0..N-2 of the nibble list: for t = N-2 .. 1,
 // j = (r_t (t+1)) >> 32, swap entries t and j (Sec. 3: random permutation of legs 2..n).
 template <int N>
-__device__ __forceinline__ uint64_t shuffle_order(const EventRng& rng) {
-  uint64_t A = identity_order<N>();
+__device__ __forceinline__ OrderWord<N> shuffle_order(const EventRng& rng) {
+  OrderWord<N> A = identity_order<N>();
   constexpr int NF = N - 2;
   u32x4 w{};
 #pragma unroll
@@ -238,7 +246,7 @@ __device__ __forceinline__ double pdf_sample(double u, const PdfParams& P) {
   const double* c = P.tab + 4 * seg;
   double x = fma(fma(fma(c[3], theta, c[2]), theta, c[1]), theta, c[0]);
   x = fmin(fmax(x, P.tau), 1.0 - 0x1p-53);
-  double w = exp(A * log_fp64(x));
+  double w = exp(A * log_pos(x));
   const bool lower = u <= 0.5;
   const double uZ = lower ? u * P.Z : (1.0 - u) * P.Z;
   const double c1 = A, c2 = A * (A - 1.0) / 2.0, c3 = c2 * (A - 2.0) / 3.0, c4 = c3 * (A - 3.0) / 4.0;
@@ -247,13 +255,13 @@ __device__ __forceinline__ double pdf_sample(double u, const PdfParams& P) {
     const double F = w * pdf_poly(P, x);
     const double res = lower ? (F - P.Ftau) - uZ : uZ - (P.F1 - F);
     // Newton: dx = -res / f(x), f = (w / x) (1 - x)^b, so d = dx / x = -res / (w (1 - x)^b)
-    d = -res / (w * ipow(1.0 - x, P.b));
+    d = div_fp64(-res, w * ipow(1.0 - x, P.b));
     x = fma(x, d, x);
     if (fabs(d) < 1e-3) {
       w *= 1.0 + d * (c1 + d * (c2 + d * (c3 + d * c4)));
     } else {
       x = fmin(fmax(x, P.tau), 1.0 - 0x1p-53);
-      w = exp(A * log_fp64(x));
+      w = exp(A * log_pos(x));
     }
   }
   return x;
@@ -331,7 +339,7 @@ __host__ __device__ inline double grid_lnf(const ScaleGrid& g, double lmu, doubl
 // ----------------------------------------------------------------------------------------
 __device__ __forceinline__ void rambo_q(double r1, double r2, double r3, double r4, double q[4]) {
   const double c = 2.0 * r1 - 1.0;
-  const double st = sqrt(1.0 - c * c);
+  const double st = sqrt_fp64(1.0 - c * c);
   double sp, cp;
   sincospi_fp64(2.0 * r2, &sp, &cp);
   const double q0 = -log_fp64(r3 * r4);
@@ -344,13 +352,13 @@ __device__ __forceinline__ void rambo_q(double r1, double r2, double r3, double 
 struct RamboMap {
   double bx, by, bz, gamma, a, X;
   __device__ __forceinline__ void init(const double Q[4], double sqrt_shat) {
-    const double M = sqrt(Q[0] * Q[0] - Q[1] * Q[1] - Q[2] * Q[2] - Q[3] * Q[3]);
-    const double iM = 1.0 / M;
+    const double M = sqrt_fp64(Q[0] * Q[0] - Q[1] * Q[1] - Q[2] * Q[2] - Q[3] * Q[3]);
+    const double iM = div_fp64(1.0, M);
     bx = -Q[1] * iM;
     by = -Q[2] * iM;
     bz = -Q[3] * iM;
     gamma = Q[0] * iM;
-    a = 1.0 / (1.0 + gamma);
+    a = div_fp64(1.0, 1.0 + gamma);
     X = sqrt_shat * iM;
   }
   __device__ __forceinline__ void apply(const double q[4], double p[4]) const {

@@ -50,7 +50,7 @@ __device__ __forceinline__ void build_event(const GenClass& C, int64_t i, EventK
   const u32x4 b0 = rng.block(0);
 
   // colour ordering and helicities
-  uint64_t A;
+  OrderWord<N> A;
   if (C.in_order) {
     A = 0;
 #pragma unroll
@@ -58,7 +58,7 @@ __device__ __forceinline__ void build_event(const GenClass& C, int64_t i, EventK
       // a leg index outside 1..N-1 is clamped so that malformed input never addresses
       // outside the event's arrays
       const uint32_t l = C.in_order[i * N + t];
-      A |= (uint64_t)(l < 1u ? 1u : (l > (uint32_t)(N - 1) ? (uint32_t)(N - 1) : l)) << (4 * (t - 1));
+      A |= (OrderWord<N>)(l < 1u ? 1u : (l > (uint32_t)(N - 1) ? (uint32_t)(N - 1) : l)) << (4 * (t - 1));
     }
   } else if (C.random_order) {
     A = shuffle_order<N>(rng);
@@ -81,7 +81,7 @@ __device__ __forceinline__ void build_event(const GenClass& C, int64_t i, EventK
       ev.x2 = pdf_sample(u01(b0.v[1]), C.pdf);
     }
     ev.shat = ev.x1 * ev.x2 * C.sqrt_s * C.sqrt_s;
-    sqrt_shat = sqrt(ev.shat);
+    sqrt_shat = sqrt_fp64(ev.shat);
   } else {
     ev.x1 = ev.x2 = 1.0;
     ev.shat = C.sqrt_s * C.sqrt_s;
@@ -115,13 +115,15 @@ __device__ __forceinline__ void build_event(const GenClass& C, int64_t i, EventK
   for (int t = 1; t < N; ++t) {
     const uint32_t j = ev.leg[t];
     const int slot = 4 * (int)(j >= 2u ? j - 2u : 0u);
+    // 1 or 0 times the momentum, exactly: one multiply-add instead of two selects and an add
+    const double out = j >= 2u ? 1.0 : 0.0;
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) Q[mu] += j >= 2u ? perm.col[(slot + mu) * perm.stride] : 0.0;
+    for (int mu = 0; mu < 4; ++mu) Q[mu] = __builtin_fma(out, perm.col[(slot + mu) * perm.stride], Q[mu]);
   }
   RamboMap map;
   map.init(Q, sqrt_shat);
-  const double rr = 2.0 * sqrt(ev.x1 * ev.x2);
-  const double ch = (ev.x1 + ev.x2) / rr, sh = (ev.x1 - ev.x2) / rr;
+  const double rr = 2.0 * sqrt_fp64(ev.x1 * ev.x2), irr = recip_refine(rr);
+  const double ch = div_refined(ev.x1 + ev.x2, rr, irr), sh = div_refined(ev.x1 - ev.x2, rr, irr);
 #pragma unroll
   for (int p = 0; p < NF; ++p) {
     double pc[4];
@@ -180,43 +182,150 @@ __device__ __forceinline__ double pseudorapidity(double pt, double pz, double e)
   return copysign(log_fp64((e + az) / pt), pz);
 }
 
+// Azimuth and pseudorapidity in FP32 to within kAngleErr (|eta| <= 20), to find the closest pair
+// of jets: t = min / max of |y|, |x| and an odd polynomial for atan t on [0, 1] (least-squares
+// fit weighted towards equal errors, 2.5e-7), then the octant; log2 of (E + |pz|) / pT.
+constexpr float kAngleErr = 4e-6f;
+
+__device__ __forceinline__ float azimuth_f32(float y, float x) {
+  const float ax = fabsf(x), ay = fabsf(y);
+  const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(ax, ay));
+  const float z = t * t;
+  float r = 0.0068117926f;
+  r = __builtin_fmaf(r, z, -0.033604219f);
+  r = __builtin_fmaf(r, z, 0.079623672f);
+  r = __builtin_fmaf(r, z, -0.13233342f);
+  r = __builtin_fmaf(r, z, 0.19807816f);
+  r = __builtin_fmaf(r, z, -0.33317368f);
+  r = __builtin_fmaf(r, z, 0.99999611f) * t;
+  r = ay > ax ? 1.57079633f - r : r;
+  r = x < 0.0f ? 3.14159265f - r : r;
+  return copysignf(r, y);
+}
+
+// Delta R^2 of two jets; no fused multiply-adds: every form of the cuts rounds exactly as written
+__device__ __forceinline__ double delta_r2(double eta_a, double phi_a, double eta_b, double phi_b) {
+#pragma clang fp contract(off)
+  const double pi = 3.14159265358979323846;
+  double dphi = fabs(phi_a - phi_b);
+  dphi = dphi > pi ? 2.0 * pi - dphi : dphi;
+  const double deta = eta_a - eta_b;
+  return deta * deta + dphi * dphi;
+}
+
 // Jet cuts and observables (Sec. 3, Sec. 4) on the outgoing legs (lab frame).  H_T is summed
 // in position order through the lane's LDS column, as the position-order form sums it.
+//
+// R_min is one pair's Delta R, so from four jets on the FP64 arctangents and logarithms (about
+// 160 instructions a jet) are evaluated for the closest pair only: FP32 angles rank the pairs,
+// every pair within their error of the smallest is evaluated in FP64, and the minimum of those
+// is bitwise the minimum over all pairs.  Nearly always that is one pair; a wave repeats while
+// any lane has another.  The |eta| cut is decided in FP32 outside its error and in FP64 within.
+// Angles that FP32 does not resolve (|eta| > 20, infinities, NaN) send every pair to FP64.
+// Three jets have three pairs, which costs the same either way: below four all are evaluated.
 template <int N>
 __device__ __forceinline__ bool cuts(const GenClass& C, const EventKin<N>& ev, PermLds perm, double& ht,
                                      double& rmin) {
-  // no fused multiply-adds: both forms of the cuts round exactly as written
 #pragma clang fp contract(off)
   constexpr int NF = N - 2;
-  double pt[NF], eta[NF], phi[NF];
   bool ok = true;
-#pragma unroll
-  for (int p = 0; p < NF; ++p) {
-    const double* m = ev.pl[p];
-    pt[p] = sqrt(m[1] * m[1] + m[2] * m[2]);
-    eta[p] = pseudorapidity(pt[p], m[3], m[0]);
-    phi[p] = atan2(m[2], m[1]);
-    perm.col[p * perm.stride] = pt[p];
-    ok = ok && (pt[p] > C.pt_min) && (fabs(eta[p]) < C.eta_max);
-  }
+  double dr2min = 1e300;
   ht = 0.0;
+  if constexpr (NF < 4) {
+    double eta[NF], phi[NF];
+#pragma unroll
+    for (int p = 0; p < NF; ++p) {
+      const double* m = ev.pl[p];
+      const double pt = sqrt(m[1] * m[1] + m[2] * m[2]);
+      eta[p] = pseudorapidity(pt, m[3], m[0]);
+      phi[p] = atan2(m[2], m[1]);
+      perm.col[(4 * p + 3) * perm.stride] = pt;
+      ok = ok && (pt > C.pt_min) && (fabs(eta[p]) < C.eta_max);
+    }
+    static_for<0, NF>([&](auto ac) {
+      constexpr int a = decltype(ac)::value;
+      static_for<a + 1, NF>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
+        dr2min = fmin(dr2min, delta_r2(eta[a], phi[a], eta[b], phi[b]));
+      });
+    });
+  } else {
+    constexpr int NP = NF * (NF - 1) / 2;  // pairs a < b at b (b - 1) / 2 + a
+    float eta[NF], phi[NF];
+    const float eta_max = (float)C.eta_max;
+    uint32_t near = 0;  // jets whose |eta| cut FP32 does not decide
+    bool resolved = true;
+#pragma unroll
+    for (int p = 0; p < NF; ++p) {
+      const double* m = ev.pl[p];
+      const double pt = sqrt_fp64(m[1] * m[1] + m[2] * m[2]);
+      const double num = m[0] + fabs(m[3]);
+      perm.col[(4 * p) * perm.stride] = m[1];
+      perm.col[(4 * p + 1) * perm.stride] = m[2];
+      perm.col[(4 * p + 2) * perm.stride] = copysign(num, m[3]);
+      perm.col[(4 * p + 3) * perm.stride] = pt;
+      const float fnum = (float)num, fpt = (float)pt;
+      const bool fine = fnum < 1e30f && fpt > 1e-30f;  // in FP32's range
+      const float e = 0.693147181f * __builtin_amdgcn_logf(fnum * __builtin_amdgcn_rcpf(fpt));
+      eta[p] = copysignf(e, (float)m[3]);
+      phi[p] = azimuth_f32((float)m[2], (float)m[1]);
+      ok = ok && (pt > C.pt_min);
+      const float d = fabsf(e) - eta_max;
+      ok = ok && !(fine && d >= 2.0f * kAngleErr + 1e-6f * eta_max);
+      near |= ((fine && d < -2.0f * kAngleErr - 1e-6f * eta_max) || !ok) ? 0u : 1u << p;
+      resolved = resolved && fine && fabsf(e) <= 20.0f && fabsf(phi[p]) < 4.0f;
+    }
+    float d2[NP];
+    float dmin = INFINITY;
+    static_for<1, NF>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      static_for<0, b>([&](auto ac) {
+        constexpr int a = decltype(ac)::value;
+        float dphi = fabsf(phi[a] - phi[b]);
+        dphi = fminf(dphi, 6.28318531f - dphi);
+        const float deta = eta[a] - eta[b];
+        const float v = __builtin_fmaf(deta, deta, dphi * dphi);
+        d2[b * (b - 1) / 2 + a] = v;
+        dmin = fminf(dmin, v);
+      });
+    });
+    // an FP32 difference of angles is off by at most e = 2 kAngleErr per axis, so Delta R^2 by
+    // 2 sqrt(2) e Delta R + 2 e^2 and 1e-6 of itself; twice that for the two pairs compared
+    const float r = __builtin_amdgcn_sqrtf(dmin);
+    float lim = dmin + (6.0f * 2.0f * kAngleErr) * r + 2e-6f * dmin + 16.0f * kAngleErr * kAngleErr;
+    lim = resolved ? lim : INFINITY;
+    using Mask = typename std::conditional<(NP <= 32), uint32_t, uint64_t>::type;
+    Mask todo = 0;
+    static_for<0, NP>([&](auto pc) {
+      constexpr int p = decltype(pc)::value;
+      todo |= !(d2[p] > lim) ? Mask(1) << p : Mask(0);
+    });
+    while (todo != 0) {
+      const int p = NP <= 32 ? __builtin_ctz((uint32_t)todo) : __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int b = (int)(0.5f + __builtin_amdgcn_sqrtf(2.0f * (float)p + 0.26f)), a = p - b * (b - 1) / 2;
+      double e2[2], f2[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const double* c = perm.col + 4 * (k == 0 ? a : b) * perm.stride;
+        const double num = c[2 * perm.stride];
+        e2[k] = copysign(log_fp64(fabs(num) / c[3 * perm.stride]), num);
+        f2[k] = atan2(c[perm.stride], c[0]);
+      }
+      dr2min = fmin(dr2min, delta_r2(e2[0], f2[0], e2[1], f2[1]));
+    }
+    while (near != 0) {
+      const int p = __builtin_ctz(near);
+      near &= near - 1;
+      const double* c = perm.col + 4 * p * perm.stride;
+      ok = ok && fabs(log_fp64(fabs(c[2 * perm.stride]) / c[3 * perm.stride])) < C.eta_max;
+    }
+  }
 #pragma unroll
   for (int t = 1; t < N; ++t) {
     const uint32_t j = ev.leg[t];
-    ht += j >= 2u ? perm.col[(int)(j >= 2u ? j - 2u : 0u) * perm.stride] : 0.0;
+    ht += j >= 2u ? perm.col[(4 * (int)(j >= 2u ? j - 2u : 0u) + 3) * perm.stride] : 0.0;
   }
-  double dr2min = 1e300;
-  const double pi = 3.14159265358979323846;
-  static_for<0, NF>([&](auto ac) {
-    constexpr int a = decltype(ac)::value;
-    static_for<a + 1, NF>([&](auto bc) {
-      constexpr int b = decltype(bc)::value;
-      double dphi = fabs(phi[a] - phi[b]);
-      dphi = dphi > pi ? 2.0 * pi - dphi : dphi;
-      const double deta = eta[a] - eta[b];
-      dr2min = fmin(dr2min, deta * deta + dphi * dphi);
-    });
-  });
   rmin = sqrt(dr2min);
   return ok && (dr2min > C.dr_min * C.dr_min);
 }
@@ -243,7 +352,7 @@ __device__ __forceinline__ void build_event_positions(const GenClass& C, int64_t
   const u32x4 b0 = rng.block(0);
 
   // colour ordering and helicities
-  uint64_t A;
+  OrderWord<N> A;
   if (C.in_order) {
     A = 0;
 #pragma unroll
@@ -251,7 +360,7 @@ __device__ __forceinline__ void build_event_positions(const GenClass& C, int64_t
       // a leg index outside 1..N-1 is clamped so that malformed input never addresses
       // outside the event's arrays
       const uint32_t l = C.in_order[i * N + t];
-      A |= (uint64_t)(l < 1u ? 1u : (l > (uint32_t)(N - 1) ? (uint32_t)(N - 1) : l)) << (4 * (t - 1));
+      A |= (OrderWord<N>)(l < 1u ? 1u : (l > (uint32_t)(N - 1) ? (uint32_t)(N - 1) : l)) << (4 * (t - 1));
     }
   } else if (C.random_order) {
     A = shuffle_order<N>(rng);
@@ -274,7 +383,7 @@ __device__ __forceinline__ void build_event_positions(const GenClass& C, int64_t
       ev.x2 = pdf_sample(u01(b0.v[1]), C.pdf);
     }
     ev.shat = ev.x1 * ev.x2 * C.sqrt_s * C.sqrt_s;
-    sqrt_shat = sqrt(ev.shat);
+    sqrt_shat = sqrt_fp64(ev.shat);
   } else {
     ev.x1 = ev.x2 = 1.0;
     ev.shat = C.sqrt_s * C.sqrt_s;
@@ -309,8 +418,8 @@ __device__ __forceinline__ void build_event_positions(const GenClass& C, int64_t
   }
   RamboMap map;
   map.init(Q, sqrt_shat);
-  const double rr = 2.0 * sqrt(ev.x1 * ev.x2);
-  const double ch = (ev.x1 + ev.x2) / rr, sh = (ev.x1 - ev.x2) / rr;
+  const double rr = 2.0 * sqrt_fp64(ev.x1 * ev.x2), irr = recip_refine(rr);
+  const double ch = div_refined(ev.x1 + ev.x2, rr, irr), sh = div_refined(ev.x1 - ev.x2, rr, irr);
   const double e1 = 0.5 * C.sqrt_s * ev.x1, e2 = 0.5 * C.sqrt_s * ev.x2;
 #pragma unroll
   for (int t = 0; t < N; ++t) {

@@ -22,7 +22,7 @@ constexpr bool lds_span_table(int n, int prec) { return prec == 32 && n <= 8; }
 // The table classes generate events in two kernels (kinematics at several waves per SIMD,
 // then the recursion at one), joined by a staging buffer of split_words(n) doubles per event.
 constexpr bool split_form(int n, int prec) { return lds_span_table(n, prec); }
-constexpr int split_words(int n) { return 4 * (n - 1) + 6; }
+constexpr int split_words(int n) { return 4 * (n - 1) + 5; }
 
 // Lane forms the library holds per (n, prec): one event per lane where the recursion fits a
 // lane's 512 registers (FP32 n <= 9, FP64 n <= 6); two lanes per event from FP32 n = 9 and

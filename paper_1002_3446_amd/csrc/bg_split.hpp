@@ -19,19 +19,44 @@ namespace bgk {
 // another, word w of event j at buf[((j / 64) * kWords + w) * 64 + j % 64], so that a wave
 // reads one contiguous block.  Words: the centre-of-mass momenta of recursion positions
 // 1..N-1 (position t, component mu at 4 (t - 1) + mu; position 0 is always the beam leg 0,
-// which follows from s_hat), s_hat, x1, x2, the weight factor of the dynamic scale
-// (scale_ratio, 1 with a fixed scale), the helicity word with the cut flag at bit 32, and the
-// leg positions (4 bits each).
+// which follows from s_hat), s_hat, the packed word (event_word); then, written and read only
+// when they are used, x1, x2 (with the log w output) and the weight factor of the dynamic scale
+// (scale_ratio).
 template <int N>
 struct SplitLayout {
-  static constexpr int kMom = 0, kShat = 4 * (N - 1), kX1 = kShat + 1, kX2 = kShat + 2, kR = kShat + 3,
-                       kMeta = kShat + 4, kLegs = kShat + 5, kWords = kShat + 6;
+  static constexpr int kMom = 0, kShat = 4 * (N - 1), kMeta = kShat + 1, kX1 = kShat + 2, kX2 = kShat + 3,
+                       kR = kShat + 4, kWords = kShat + 5;
+  static constexpr int kAlways = kMeta + 1;  // words that every event stages
   static_assert(kWords == split_words(N), "staging words");
   __device__ static int64_t at(int64_t j, int w) { return ((j >> 6) * kWords + w) * 64 + (j & 63); }
 };
 
+// The helicity bits (0..11), the cut flag (12) and the legs at positions 1..N-1 (four bits each
+// from bit 16) of one event in a word.
+template <int N>
+struct EventWord {
+  uint64_t v;
+  __device__ __forceinline__ static EventWord pack(uint32_t hel, bool pass, const uint32_t (&leg)[N]) {
+    uint64_t w = (hel & 0xFFFu) | (pass ? 1u << 12 : 0u);
+#pragma unroll
+    for (int t = 1; t < N; ++t) w |= (uint64_t)(leg[t] & 15u) << (12 + 4 * t);
+    return EventWord{w};
+  }
+  __device__ __forceinline__ uint32_t hel() const { return (uint32_t)v & 0xFFFu; }
+  __device__ __forceinline__ bool pass() const { return (((uint32_t)v >> 12) & 1u) != 0; }
+  __device__ __forceinline__ void legs(uint32_t (&leg)[N]) const {
+    leg[0] = 0;
+#pragma unroll
+    for (int t = 1; t < N; ++t) leg[t] = (uint32_t)(v >> (12 + 4 * t)) & 15u;
+  }
+};
+
 // Kinematics of event i (staging slot j): writes the cut flag and observables and stages
-// the event.  perm: the lane's LDS column (perm_lds_bytes).
+// the event.  perm: the lane's LDS column (perm_lds_bytes).  Bound by VALU issue (92% of the
+// SIMD's slots at n = 8 with three waves), so what counts is instructions: 3638 -> 2880 per wave
+// at n = 8 with the closest pair's angles alone in FP64 (cuts), Horner coefficients in scalar
+// registers (coef), divisions and roots without range scaling and three-way exclusive ors;
+// 461 -> 400 us per 2^22 events at n = 8, 234 -> 199 us at n = 4.
 template <int N>
 __device__ __forceinline__ void kin_one(const GenClass& C, int64_t i, int64_t j, double* __restrict__ buf,
                                         PermLds perm) {
@@ -39,33 +64,32 @@ __device__ __forceinline__ void kin_one(const GenClass& C, int64_t i, int64_t j,
   EventKin<N> ev;
   double ht, rmin;
   build_event<N>(C, i, ev, perm, true);
+  // staged before the cuts, which then have the registers
+#pragma unroll
+  for (int t = 1; t < N; ++t)
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) buf[L::at(j, L::kMom + 4 * (t - 1) + mu)] = ev.pc[t][mu];
+  buf[L::at(j, L::kShat)] = ev.shat;
+  if (C.out.logw) {
+    buf[L::at(j, L::kX1)] = ev.x1;
+    buf[L::at(j, L::kX2)] = ev.x2;
+  }
   const bool pass = cuts<N>(C, ev, perm, ht, rmin);
   if (C.out.pass) C.out.pass[i] = pass ? 1 : 0;
   if (C.out.obs) {
     C.out.obs[2 * i] = ht;
     C.out.obs[2 * i + 1] = rmin;
   }
-#pragma unroll
-  for (int t = 1; t < N; ++t)
-#pragma unroll
-    for (int mu = 0; mu < 4; ++mu) buf[L::at(j, L::kMom + 4 * (t - 1) + mu)] = ev.pc[t][mu];
-  buf[L::at(j, L::kShat)] = ev.shat;
-  buf[L::at(j, L::kX1)] = ev.x1;
-  buf[L::at(j, L::kX2)] = ev.x2;
-  buf[L::at(j, L::kR)] = scale_ratio<N>(C, ht, ev.x1, ev.x2);
-  uint64_t legs = 0;
-#pragma unroll
-  for (int t = 0; t < N; ++t) legs |= (uint64_t)(ev.leg[t] & 15u) << (4 * t);
-  buf[L::at(j, L::kMeta)] = __longlong_as_double((long long)((uint64_t)ev.hel | ((uint64_t)pass << 32)));
-  buf[L::at(j, L::kLegs)] = __longlong_as_double((long long)legs);
+  if (C.dynamic_scale) buf[L::at(j, L::kR)] = scale_ratio<N>(C, ht, ev.x1, ev.x2);
+  buf[L::at(j, L::kMeta)] = __longlong_as_double((long long)EventWord<N>::pack(ev.hel, pass, ev.leg).v);
 }
 
 // One event's staged words in registers.
 template <int N>
 struct Staged {
   double pc[N - 1][4];  // positions 1..N-1
-  double shat, x1, x2, r;
-  uint64_t meta, legs;
+  double shat;
+  EventWord<N> word;
 };
 
 template <int N>
@@ -76,17 +100,28 @@ __device__ __forceinline__ void load_staged(const double* __restrict__ buf, int6
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) s.pc[t - 1][mu] = buf[L::at(j, L::kMom + 4 * (t - 1) + mu)];
   s.shat = buf[L::at(j, L::kShat)];
-  s.x1 = buf[L::at(j, L::kX1)];
-  s.x2 = buf[L::at(j, L::kX2)];
-  s.r = buf[L::at(j, L::kR)];
-  s.meta = (uint64_t)__double_as_longlong(buf[L::at(j, L::kMeta)]);
-  s.legs = (uint64_t)__double_as_longlong(buf[L::at(j, L::kLegs)]);
+  s.word.v = (uint64_t)__double_as_longlong(buf[L::at(j, L::kMeta)]);
+}
+
+// The weight and outputs of a staged event; its optional words are read here, where used.
+template <int N>
+__device__ __forceinline__ double finish_staged(const GenClass& C, int64_t i, int64_t j, const double* __restrict__ buf,
+                                                bool pass, double a2, double shat) {
+  using L = SplitLayout<N>;
+  double x1 = 1.0, x2 = 1.0, r = 1.0;
+  if (C.out.logw) {
+    x1 = buf[L::at(j, L::kX1)];
+    x2 = buf[L::at(j, L::kX2)];
+  }
+  if (C.dynamic_scale) r = buf[L::at(j, L::kR)];
+  return finish_event<N>(C, i, pass, a2, shat, x1, x2, r);
 }
 
 // |A|^2, weight and outputs of event i from its staged words (one lane per event, the span
 // table in tab); returns w.
 template <int N, int POL = 0>
-__device__ __forceinline__ double rec_staged(const GenClass& C, int64_t i, const Staged<N>& s, LdsTable<N>* tab) {
+__device__ __forceinline__ double rec_staged(const GenClass& C, int64_t i, int64_t j, const double* __restrict__ buf,
+                                             const Staged<N>& s, LdsTable<N>* tab) {
   double pc[N][4];
   // position 0: the beam leg 0, as build_event forms it
   const double hb = 0.5 * (C.use_pdf ? sqrt(s.shat) : C.sqrt_s);
@@ -99,19 +134,16 @@ __device__ __forceinline__ double rec_staged(const GenClass& C, int64_t i, const
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) pc[t][mu] = s.pc[t - 1][mu];
   uint32_t leg[N];
-#pragma unroll
-  for (int t = 0; t < N; ++t) leg[t] = (uint32_t)(s.legs >> (4 * t)) & 15u;
-  const uint32_t hel = (uint32_t)s.meta;
-  const bool pass = ((s.meta >> 32) & 1u) != 0;
+  s.word.legs(leg);
   double a2;
   if constexpr (POL == 1) {
     double cs[N][2];
     polarisation_angles<N>(C, i, cs);
     a2 = ordered_amp2_real<N, float, true>(pc, leg, cs, tab);
   } else {
-    a2 = ordered_amp2<N, float, true>(pc, leg, hel, tab);
+    a2 = ordered_amp2<N, float, true>(pc, leg, s.word.hel(), tab);
   }
-  return finish_event<N>(C, i, pass, a2, s.shat, s.x1, s.x2, s.r);
+  return finish_staged<N>(C, i, j, buf, s.word.pass(), a2, s.shat);
 }
 
 // The same from staging slot j.
@@ -120,7 +152,7 @@ __device__ __forceinline__ double rec_one(const GenClass& C, int64_t i, int64_t 
                                           LdsTable<N>* tab) {
   Staged<N> s;
   load_staged<N>(buf, j, s);
-  return rec_staged<N, POL>(C, i, s, tab);
+  return rec_staged<N, POL>(C, i, j, buf, s, tab);
 }
 
 // The same with the event on the G lanes of a group (the grouped recursion; span momenta
@@ -141,15 +173,12 @@ __device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t i, int64_
   for (int t = 1; t < N; ++t)
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) pc[t][mu] = buf[L::at(j, L::kMom + 4 * (t - 1) + mu)];
-  const uint64_t meta = (uint64_t)__double_as_longlong(buf[L::at(j, L::kMeta)]);
-  const uint64_t legs = (uint64_t)__double_as_longlong(buf[L::at(j, L::kLegs)]);
+  const EventWord<N> word{(uint64_t)__double_as_longlong(buf[L::at(j, L::kMeta)])};
   uint32_t leg[N];
-#pragma unroll
-  for (int t = 0; t < N; ++t) leg[t] = (uint32_t)(legs >> (4 * t)) & 15u;
-  const double a2 = ordered_amp2_g<N, T, G, span_k_table<T>()>(pc, leg, (uint32_t)meta, g, ktab, lanes);
+  word.legs(leg);
+  const double a2 = ordered_amp2_g<N, T, G, span_k_table<T>()>(pc, leg, word.hel(), g, ktab, lanes);
   if (g != 0) return 0.0;
-  const bool pass = ((meta >> 32) & 1u) != 0;
-  return finish_event<N>(C, i, pass, a2, shat, buf[L::at(j, L::kX1)], buf[L::at(j, L::kX2)], buf[L::at(j, L::kR)]);
+  return finish_staged<N>(C, i, j, buf, word.pass(), a2, shat);
 }
 
 // Launch: blockDim.x = kKinBlock, perm_lds_bytes(N, kKinBlock) bytes of dynamic LDS,
@@ -183,8 +212,8 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, re
   if (j < cnt) load_staged<N>(buf, j, st);
   const int64_t t = (int64_t)blockIdx.x + ahead;
   if (rec_prefetch<N>() && ahead > 0 && t * kLdsLanes < cnt) {
-    // the tile's words are contiguous (SplitLayout): kWords x 64 doubles
-    constexpr int kBytes = SplitLayout<N>::kWords * kLdsLanes * 8;
+    // the tile's words are contiguous (SplitLayout)
+    constexpr int kBytes = SplitLayout<N>::kAlways * kLdsLanes * 8;
     const char* base = reinterpret_cast<const char*>(buf + t * kLdsLanes * SplitLayout<N>::kWords);
 #pragma unroll
     for (int off = 0; off < kBytes; off += kLdsLanes * 128) {
@@ -195,7 +224,7 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, re
     }
   }
   double w = 0.0;
-  if (j < cnt) w = rec_staged<N, POL>(C, first + j, st, &tab);
+  if (j < cnt) w = rec_staged<N, POL>(C, first + j, j, buf, st, &tab);
   if (partials) block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0}, partials + 4 * (first / kLdsLanes + (int64_t)blockIdx.x));
 }
 

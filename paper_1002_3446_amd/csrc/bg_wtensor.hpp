@@ -244,16 +244,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
     for (int t = 1; t < N; ++t)
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) pc[t][mu] = buf[L::at(je, L::kMom + 4 * (t - 1) + mu)];
-    const uint64_t meta = (uint64_t)__double_as_longlong(buf[L::at(je, L::kMeta)]);
-    const uint64_t legs = (uint64_t)__double_as_longlong(buf[L::at(je, L::kLegs)]);
+    const EventWord<N> word{(uint64_t)__double_as_longlong(buf[L::at(je, L::kMeta)])};
     uint32_t leg[N];
-#pragma unroll
-    for (int t = 0; t < N; ++t) leg[t] = (uint32_t)(legs >> (4 * t)) & 15u;
-    const double a2 = ordered_amp2_w<N, T>(pc, leg, (uint32_t)meta, l >> 2, l & 3, J);
+    word.legs(leg);
+    const double a2 = ordered_amp2_w<N, T>(pc, leg, word.hel(), l >> 2, l & 3, J);
     __syncthreads();  // the next round reuses the currents' LDS
     if (l == 0 && j < cnt) {
-      const double x = finish_event<N>(C, first + j, ((meta >> 32) & 1u) != 0, a2, shat, buf[L::at(je, L::kX1)],
-                                       buf[L::at(je, L::kX2)], buf[L::at(je, L::kR)]);
+      const double x = finish_staged<N>(C, first + j, je, buf, word.pass(), a2, shat);
       w = cs_add(w, CSum{x, 0.0});
       w2 = cs_add(w2, CSum{x * x, 0.0});
     }

@@ -117,11 +117,10 @@ typedef struct {
                         function, no sampling density); -inf when |A|^2 = 0 */
 } bg_outputs;
 
-/* Generate events of ncfg classes (Sec. 3).  One class: a kinematics kernel (one lane per
- * event) and a recursion kernel joined by a staging buffer ((4n + 1) * 8 B per event, chunks
- * of at most 2^22 events), for FP32 n <= 8 and every form with two or four lanes per event
- * or the W-tensor form; the one-lane classes without the LDS span table (FP32 n = 9 with one
- * lane, FP64 n <= 6) and real polarisations beyond FP32 n = 8 as one kernel.  A small setup
+/* Generate events of ncfg classes (Sec. 3).  One class: up to n = 6 (and for FP32 n = 9 with one
+ * lane, real polarisations beyond n = 8 and in FP64) one kernel; else a kinematics kernel (one lane
+ * per event) and a recursion kernel joined by a staging buffer ((4n + 1) * 8 B per event, chunks
+ * of at most 2^22 events).  A small setup
  * launch, once per density and device, tabulates the inverse CDF of the parton density when
  * x1, x2 are sampled.  Several classes (mixed multiplicities): as chosen by
  * bg_set_mixed_launch, either one after another, or the FP32 classes in one persistent
@@ -226,7 +225,8 @@ int bg_hist_read(int naxes, const bg_hist_axis *axes, const int64_t *limbs, doub
 int bg_check_events(int n, int64_t N, const uint32_t *hel, const uint8_t *order, int64_t *first_bad,
                     void *stream);
 
-/* Launch shape for one (n, prec) class: threads per workgroup (64, 128, 192 or 256) and
+/* Launch shape for one (n, prec) class: threads per workgroup (64, 128, 192 or 256; the kernels of
+ * n <= 8 with helicity states always use 64) and
  * events per lane in one tile of the persistent multi-class launch (1..64; a tile holds
  * block * tile_iters events).  The autotuner writes these; (0, 0) restores the built-in
  * default.  Affects speed only: per-event outputs are identical for every shape, totals
@@ -241,7 +241,8 @@ int bg_get_launch(int n, int prec, int *block, int *tile_iters);
  * values BG_EINVAL; 0 restores the default (4 for FP64 n >= 10, 2 for FP32 n >= 10 and
  * FP64 n = 7..9, else 1).  With G lanes each holds 4/G of the four
  * Lorentz components of every current: 1/G of the registers, at the price of cross-lane
- * sums in every Minkowski product.  Affects speed only: |A|^2 agrees to the recursion
+ * sums in every Minkowski product.  At FP64 n = 7, 8 the setting 2 names the only form built,
+ * whose kernels run one lane per event.  Affects speed only: |A|^2 agrees to the recursion
  * precision's rounding between the forms. */
 int bg_set_lanes(int n, int prec, int lanes);
 int bg_get_lanes(int n, int prec, int *lanes);

@@ -66,6 +66,11 @@ def has_lane_pairs(n: int, p: int) -> bool:
     return n >= 9 if p == 32 else n >= 6
 
 
+def kernel_lanes(n: int, p: int, setting: int) -> int:
+    """Lanes per event of the kernel behind a lanes setting (FP64 n = 7, 8: one)."""
+    return 1 if p == 64 and n in (7, 8) else setting
+
+
 def has_lane_quads(n: int, p: int) -> bool:
     return p == 64 and n >= 10
 
@@ -79,15 +84,15 @@ def has_wtensor(n: int, p: int) -> bool:
 
 
 def unit_flags(n: int, p: int, k: int, f: int) -> list[str]:
-    """Extra compiler flags of one kernel unit.  The generation and bg_amp2 units of FP32 n = 8
-    (one lane) and of FP64 n >= 8 (two or four lanes) are built without LLVM's pre-RA machine
-    scheduler: there the recursion fills the register file at one wave per SIMD, and the
-    scheduler's reordering for latency raises register pressure, which costs more (scratch
-    spill, AGPR copies) than the latency it hides.  Measured on generation, alternating runs
-    on one GPU: FP32 n = 8 6.69 -> 6.53-6.61 ms per 2^24 events; FP64 n = 8 11.1 -> 11.0 ms per
-    2^24, n = 9 5.23 -> 5.01, n = 10 unchanged, n = 11 12.99 -> 12.71, n = 12 20.57 -> 18.45 ms
-    per 2^22 (scratch 400 -> 248 B per lane).  FP32 n = 12 lost 0.8% without it and keeps it."""
-    if k < 2 and ((p == 32 and f == 1 and n == 8) or (p == 64 and f in (2, 5) and n >= 8)):
+    """Extra compiler flags of one kernel unit.  The generation and bg_amp2 units of FP64 n >= 9
+    (two or four lanes) are built without LLVM's pre-RA machine scheduler: there the recursion
+    fills the register file at one wave per SIMD, and the scheduler's reordering for latency
+    raises register pressure, which costs more (scratch spill, AGPR copies) than the latency it
+    hides.  Measured on generation, alternating runs on one GPU, per 2^22 events: n = 9 5.23 ->
+    5.01, n = 10 unchanged, n = 11 12.99 -> 12.71, n = 12 20.57 -> 18.45 ms (scratch 400 -> 248 B
+    per lane).  The one-lane recursions keep it: n = 8 FP32 5.55 against 5.51 ms per 2^24 events,
+    FP64 n = 7 bg_amp2 101 against 99 us per 5 10^5."""
+    if k < 2 and p == 64 and f in (2, 5) and n >= 9:
         return ["-mllvm", "-enable-misched=0"]
     return []
 
@@ -107,7 +112,8 @@ def units_for(ns, precs=(32, 64), kinds=KINDS):
                 if k == 2:
                     forms = (1,)
                 else:
-                    forms = tuple(f for f, ok in ((1, has_one_lane(n, p)), (2, has_lane_pairs(n, p)),
+                    one = has_one_lane(n, p) or kernel_lanes(n, p, 2) == 1
+                    forms = tuple(f for f, ok in ((1, one), (2, has_lane_pairs(n, p) and kernel_lanes(n, p, 2) == 2),
                                                   (3, k == 0 and has_real_pol(n, p)),
                                                   (4, has_wtensor(n, p)),
                                                   (5, k < 2 and has_lane_quads(n, p))) if ok)

@@ -57,12 +57,26 @@ using namespace bgk;
     launch_generate_w_n##N##_p64_k0, launch_amp2_w_n##N##_p64_k1, launch_generate4_n##N##_p64_k0,        \
     launch_amp2_4_n##N##_p64_k1}}
 
+// FP64 n = 7, 8: the one-lane kernels answer to the setting 2 (kernel_lanes)
+struct Table {
+  Launchers t[9][2] = {BG_ROW(4),  BG_ROW(5),  BG_ROW(6), BG_ROW(7), BG_ROW(8),
+                       BG_ROW(9), BG_ROW(10), BG_ROW(11), BG_ROW(12)};
+  Table() {
+    for (int n = 7; n <= 8; ++n) {
+      Launchers& l = t[n - 4][1];
+      l.generate2 = l.generate;
+      l.amp2_2 = l.amp2;
+      l.generate = nullptr;
+      l.amp2 = nullptr;
+    }
+  }
+};
+
 const Launchers* table(int n, int prec) {
-  static const Launchers t[9][2] = {BG_ROW(4),  BG_ROW(5),  BG_ROW(6), BG_ROW(7), BG_ROW(8),
-                                    BG_ROW(9), BG_ROW(10), BG_ROW(11), BG_ROW(12)};
+  static const Table t;
   if (n < 4 || n > 12) return nullptr;
   if (prec != 32 && prec != 64) return nullptr;
-  return &t[n - 4][prec == 32 ? 0 : 1];
+  return &t.t[n - 4][prec == 32 ? 0 : 1];
 }
 
 // launch shapes per (n, prec): threads per workgroup, and events per lane in one tile of
@@ -455,10 +469,13 @@ int plan_class(const bg_config& c, const GenClass& G, ClassPlan& P) {
                         : (P.wform ? L->generate_w
                                    : (P.lanes == 4 ? L->generate4 : (P.lanes == 2 ? L->generate2 : L->generate)));
   if (!P.fn) return BG_ENOTSUP;
-  // staged: the W-tensor form, the table classes, and every grouped form (kinematics in
+  P.lanes = kernel_lanes(c.n, c.prec, P.lanes);
+  // 64-lane workgroups: the W-tensor form and the one-lane kernels with an LDS table
+  const bool table_class = P.lanes == 1 && lds_span_table(c.n, c.prec) && !(c.polarisation && c.prec == 64);
+  // staged: the W-tensor form, the split table classes, and every grouped form (kinematics in
   // their own kernel, one lane per event, instead of on every lane of a group)
-  P.staged = P.wform || (P.lanes == 1 && split_form(c.n, c.prec)) || P.lanes > 1;
-  P.block = (P.wform || P.lanes == 1) && P.staged ? kLdsLanes : shape_of(c.n, c.prec).block;
+  P.staged = P.wform || (table_class && split_form(c.n, c.prec)) || P.lanes > 1;
+  P.block = P.wform || table_class ? kLdsLanes : shape_of(c.n, c.prec).block;
   P.nblocks = (P.lanes * G.count + P.block - 1) / P.block;
   return BG_OK;
 }
@@ -473,10 +490,10 @@ int generate_multi(const bg_config* cfgs, const GenClass* G, const bg_outputs* o
   if (!launch_generate_multi_p32) return BG_ENOTSUP;
   std::vector<int> order;  // staged classes first (kinematics workgroup order), then the others
   for (int k : ks)
-    if (split_form(cfgs[k].n, 32)) order.push_back(k);
+    if (lds_span_table(cfgs[k].n, 32)) order.push_back(k);
   const int nstaged = (int)order.size();
   for (int k : ks)
-    if (!split_form(cfgs[k].n, 32)) order.push_back(k);
+    if (!lds_span_table(cfgs[k].n, 32)) order.push_back(k);
   std::vector<MultiClass> mcs(order.size());
   int64_t kin_blocks = 0, stage_words = 0;
   for (size_t c = 0; c < order.size(); ++c) {

@@ -388,27 +388,20 @@ __device__ __forceinline__ cv4<T> polarisation(const double p[4], bool plus) {
 #pragma clang fp contract(off)
   const T px = T(p[1]), py = T(p[2]), pz = T(p[3]);
   const T pt2 = px * px + py * py;
-  T ct, st, cf = T(1), sf = T(0);
+  T ct, st, cf, sf;  // (selects, not branches: the recursion that follows stays one block)
   if constexpr (std::is_same<T, float>::value) {
     const float ipa = __builtin_amdgcn_rsqf(pt2 + pz * pz);
     const float ipt = __builtin_amdgcn_rsqf(pt2);
     ct = pz * ipa;
     st = pt2 > 0.0f ? (pt2 * ipt) * ipa : 0.0f;
-    if (pt2 > 0.0f) {
-      cf = px * ipt;
-      sf = py * ipt;
-    }
+    cf = pt2 > 0.0f ? px * ipt : 1.0f;
+    sf = pt2 > 0.0f ? py * ipt : 0.0f;
   } else {
-    const T pa = sqrt(pt2 + pz * pz);
-    const T pt = sqrt(pt2);
-    const T ipa = T(1) / pa;
+    const T ipa = rsqrt_fp64(pt2 + pz * pz), ipt = rsqrt_fp64(pt2);
     ct = pz * ipa;
-    st = pt * ipa;
-    if (pt2 > T(0)) {
-      const T ipt = T(1) / pt;
-      cf = px * ipt;
-      sf = py * ipt;
-    }
+    st = pt2 > T(0) ? (pt2 * ipt) * ipa : T(0);
+    cf = pt2 > T(0) ? px * ipt : T(1);
+    sf = pt2 > T(0) ? py * ipt : T(0);
   }
   const T r = T(0.70710678118654752440);
   const T h = plus ? r : -r;
@@ -778,6 +771,145 @@ __device__ __forceinline__ void bg_amplitude(const KS& ks, const cv4<T> (&src)[L
 }
 
 // ----------------------------------------------------------------------------------------
+// The same recursion in FP64, one event per lane, for n <= 8.  The currents alone take 2 x 195
+// registers at n = 8, so what else lives across spans stays in LDS: the covariant leg momenta,
+// from which every bracket sums the momenta it needs, and the span scalars, -S/2 of each span.
+// Brackets accumulate V / 2 in one vector:
+//   V / 2 = sum (JA.KB) JB - (JB.KA) JA + (JA.JB) (KA - KP/2) + (JA.JC) JB - S/2 terms,
+// with KA - KB = 2 (KA - KP/2) for the span's own KP, and J = (V / 2) (2 / K^2).
+// ----------------------------------------------------------------------------------------
+template <int L, int LANES>
+struct Fp64Lds {
+  static constexpr int kScalars = Spans<L>::count - L - 1;  // spans of 2..L-1 legs
+  double2 leg[L * 2 * LANES];
+  double2 sc[(kScalars > 0 ? kScalars : 1) * LANES];
+};
+
+template <int L, int LANES>
+struct Fp64Span {
+  double2* leg;  // &leg[0][0][lane], covariant components (0, 1) and (2, 3)
+  double2* sc;   // &sc[0][lane]
+  __device__ __forceinline__ void put_leg(int t, const double (&k)[4]) const {
+    leg[(2 * t) * LANES] = make_double2(k[0], -k[1]);
+    leg[(2 * t + 1) * LANES] = make_double2(-k[2], -k[3]);
+  }
+  template <int A>
+  __device__ __forceinline__ void first(double (&K)[4]) const {
+    const double2 x = leg[(2 * A) * LANES], y = leg[(2 * A + 1) * LANES];
+    K[0] = x.x; K[1] = x.y; K[2] = y.x; K[3] = y.y;
+  }
+  template <int T>
+  __device__ __forceinline__ void add(double (&K)[4]) const {
+    double k[4];
+    first<T>(k);
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) K[mu] += k[mu];
+  }
+  // legs A..B summed left to right
+  template <int A, int B>
+  __device__ __forceinline__ void sum(double (&K)[4]) const {
+    first<A>(K);
+    static_for<A + 1, B + 1>([&](auto t) { add<decltype(t)::value>(K); });
+  }
+  template <int S>
+  __device__ __forceinline__ void put_scalar(double r, double i) const { sc[(S - L) * LANES] = make_double2(r, i); }
+  template <int S>
+  __device__ __forceinline__ double2 scalar() const { return sc[(S - L) * LANES]; }
+};
+
+// Half the bracket sum of span [A..B] (see above) and its -S/2; KP is the span's momentum.
+template <int L, int A, int B, int LANES>
+__device__ __forceinline__ void span_vertex_d(const Fp64Span<L, LANES>& ks, const cv4<double> (&J)[Spans<L>::count],
+                                              const double (&KP)[4], cv4<double>& X, double& sr, double& si) {
+#pragma clang fp contract(off)
+  using SP = Spans<L>;
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) X.re[mu] = X.im[mu] = 0.0;
+  sr = 0.0;
+  si = 0.0;
+  double ka[4];
+  static_for<A, B>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
+    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
+    double kb[4];
+    if constexpr (i == A)
+      ks.template first<A>(ka);
+    else
+      ks.template add<i>(ka);
+    ks.template sum<i + 1, B>(kb);
+    double dr, di, ar, ai, nbr, bi;
+    cdot<LA, LB>(J[PA], J[PB], dr, di);
+    rdot<LA>(J[PA], kb, ar, ai);
+    rdot_nr<LB>(J[PB], ka, nbr, bi);
+    caxpy<LB>(ar, ai, J[PB], X);
+    caxpy_nci<LA>(nbr, bi, J[PA], X);
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+      const double dk = mu == 0 ? fmac(-0.5, KP[0], ka[0]) : fmac(0.5, KP[mu], -ka[mu]);
+      X.re[mu] = fmac(dr, dk, X.re[mu]);
+      X.im[mu] = fmac(di, dk, X.im[mu]);
+    }
+    sr = fmac(-0.5, dr, sr);
+    si = fmac(-0.5, di, si);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    static_for<i + 1, B>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      double dr, ndi;
+      cdot_ni<i == A, j + 1 == B>(J[SP::at(A, i)], J[SP::at(j + 1, B)], dr, ndi);
+      caxpy_nci<i + 1 == j>(dr, ndi, J[SP::at(i + 1, j)], X);
+    });
+  });
+  static_for<A + 1, B>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    const double2 c = ks.template scalar<SP::at(A, j)>();
+    caxpy<j + 1 == B>(c.x, c.y, J[SP::at(j + 1, B)], X);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const double2 c = ks.template scalar<SP::at(i + 1, B)>();
+    caxpy<i == A>(c.x, c.y, J[SP::at(A, i)], X);
+  });
+}
+
+template <int L, int LANES>
+__device__ __forceinline__ void bg_amplitude_d(const Fp64Span<L, LANES>& ks, const cv4<double> (&src)[L],
+                                               const cv4<double>& eps0, double& m_re, double& m_im) {
+  using SP = Spans<L>;
+  cv4<double> J[SP::count];
+  static_for<0, L>([&](auto ac) { J[decltype(ac)::value] = src[decltype(ac)::value]; });
+  static_for<2, L>([&](auto lc) {
+    constexpr int len = decltype(lc)::value;
+    static_for<0, L - len + 1>([&](auto ac) {
+      constexpr int a = decltype(ac)::value, b = a + len - 1, s = SP::at(a, b);
+      // a span's momenta are read afresh: kept from one span to the next they would spill
+      asm volatile("" ::: "memory");
+      cv4<double> X;
+      double sr, si, K[4];
+      ks.template sum<a, b>(K);
+      span_vertex_d<L, a, b, LANES>(ks, J, K, X, sr, si);
+      const double prop = 2.0 / minkowski_sq(K);
+#pragma unroll
+      for (int mu = 0; mu < 4; ++mu) {
+        J[s].re[mu] = X.re[mu] * prop;
+        J[s].im[mu] = X.im[mu] * prop;
+      }
+      ks.template put_scalar<s>(sr, si);
+    });
+  });
+  asm volatile("" ::: "memory");
+  cv4<double> X;
+  double sr, si, K[4], mr, mi;
+  ks.template sum<0, L - 1>(K);
+  span_vertex_d<L, 0, L - 1, LANES>(ks, J, K, X, sr, si);
+  cdot<true, false>(eps0, X, mr, mi);
+  m_re = 2.0 * mr;
+  m_im = 2.0 * mi;
+}
+
+// ----------------------------------------------------------------------------------------
 // Real currents (the paper's choice of sources, Sec. 3): every source is a real unit vector
 // orthogonal to its momentum, eps = cos(psi) e1 + sin(psi) e2 with the transverse basis
 // e1 = (0, cos t cos f, cos t sin f, -sin t), e2 = (0, -sin f, cos f, 0) of the physical
@@ -803,10 +935,8 @@ __device__ __forceinline__ rv4<T> real_polarisation(const double p[4], T c, T s)
     const float ipt = __builtin_amdgcn_rsqf(pt2);
     ct = pz * ipa;
     st = pt2 > 0.0f ? (pt2 * ipt) * ipa : 0.0f;
-    if (pt2 > 0.0f) {
-      cf = px * ipt;
-      sf = py * ipt;
-    }
+    cf = pt2 > 0.0f ? px * ipt : 1.0f;
+    sf = pt2 > 0.0f ? py * ipt : 0.0f;
   } else {
     const T pa = sqrt(pt2 + pz * pz);
     const T pt = sqrt(pt2);

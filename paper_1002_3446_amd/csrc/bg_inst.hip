@@ -28,8 +28,8 @@ using Real = float;
 using Real = double;
 #endif
 
-static_assert(BG_KIND == 2 || (BG_FORM == 1 && has_one_lane(BG_N, BG_PREC)) ||
-                  (BG_FORM == 2 && has_lane_pairs(BG_N, BG_PREC)) || (BG_FORM == 3 && has_real_pol(BG_N, BG_PREC)) ||
+static_assert(BG_KIND == 2 || (BG_FORM == 1 && (has_one_lane(BG_N, BG_PREC) || kernel_lanes(BG_N, BG_PREC, 2) == 1)) ||
+                  (BG_FORM == 2 && has_lane_pairs(BG_N, BG_PREC) && kernel_lanes(BG_N, BG_PREC, 2) == 2) || (BG_FORM == 3 && has_real_pol(BG_N, BG_PREC)) ||
                   (BG_FORM == 4 && has_wtensor(BG_N, BG_PREC)) || (BG_FORM == 5 && has_lane_quads(BG_N, BG_PREC)),
               "this lane form is not built for (n, prec)");
 
@@ -42,10 +42,16 @@ static_assert(BG_KIND == 2 || (BG_FORM == 1 && has_one_lane(BG_N, BG_PREC)) ||
 #if BG_KIND == 0 && BG_FORM == 1
 hipError_t BG_NAME(launch_generate_n, BG_N, BG_PREC, BG_KIND)(const GenClass& C, const GenWork& W, int block,
                                                               hipStream_t s) {
-#if BG_PREC == 32 && BG_N <= 8
+#if BG_N <= 6
+  (void)block;
+  static_assert(!split_form(BG_N, BG_PREC), "one kernel");
+  const int64_t nb = (C.count + kLdsLanes - 1) / kLdsLanes;
+  hipLaunchKernelGGL((k_generate_lds<BG_N, Real, 0>), dim3((unsigned)nb), dim3(kLdsLanes), 0, s, C, W.partials);
+  return hipGetLastError();
+#elif BG_N <= 8
   (void)block;
   static_assert(split_form(BG_N, BG_PREC), "split-form classes");
-  return launch_generate_split<BG_N>(C, W, s);
+  return launch_generate_split<BG_N, Real>(C, W, s);
 #else
   const int64_t nb = (C.count + block - 1) / block;
   hipLaunchKernelGGL((k_generate<BG_N, Real>), dim3((unsigned)nb), dim3(block), perm_lds_bytes(BG_N, block), s, C,
@@ -56,9 +62,14 @@ hipError_t BG_NAME(launch_generate_n, BG_N, BG_PREC, BG_KIND)(const GenClass& C,
 #elif BG_KIND == 0 && BG_FORM == 3
 hipError_t BG_NAME(launch_generate_real_n, BG_N, BG_PREC, BG_KIND)(const GenClass& C, const GenWork& W, int block,
                                                                    hipStream_t s) {
-#if BG_PREC == 32 && BG_N <= 8
+#if BG_PREC == 32 && BG_N <= 6
   (void)block;
-  return launch_generate_split<BG_N, 1>(C, W, s);
+  const int64_t nb = (C.count + kLdsLanes - 1) / kLdsLanes;
+  hipLaunchKernelGGL((k_generate_lds<BG_N, Real, 1>), dim3((unsigned)nb), dim3(kLdsLanes), 0, s, C, W.partials);
+  return hipGetLastError();
+#elif BG_PREC == 32 && BG_N <= 8
+  (void)block;
+  return launch_generate_split<BG_N, Real, 1>(C, W, s);
 #else
   const int64_t nb = (C.count + block - 1) / block;
   hipLaunchKernelGGL((k_generate<BG_N, Real, 1>), dim3((unsigned)nb), dim3(block), perm_lds_bytes(BG_N, block), s,

@@ -512,9 +512,22 @@ struct LdsTable {
   float p[(Spans<N - 1>::count - N) * kLdsLanes];
 };
 
+// |A|^2 past an optimisation barrier: without it the compiler sinks parts of the recursion below
+// the branches of the outputs that follow, where its live values spill (FP64 n = 8: 3 KB of
+// scratch per lane).
+__device__ __forceinline__ double rec_done(double a2) {
+  opaque(a2);
+  return a2;
+}
+
+// The LDS of a one-lane recursion's workgroup (kLdsLanes lanes): the FP32 span table, or the FP64
+// leg momenta and span scalars.
+template <int N, typename T>
+using RecLds = typename std::conditional<std::is_same<T, float>::value, LdsTable<N>, Fp64Lds<N - 1, kLdsLanes>>::type;
+
 template <int N, typename T, bool LDS>
 __device__ __forceinline__ double ordered_amp2(const double (&p)[N][4], const uint32_t (&leg)[N], uint32_t hel,
-                                               LdsTable<N>* tab) {
+                                               RecLds<N, T>* tab) {
   double esum = 0.0;
 #pragma unroll
   for (int t = 0; t < N; ++t) esum += fabs(p[t][0]);
@@ -531,7 +544,13 @@ __device__ __forceinline__ double ordered_amp2(const double (&p)[N][4], const ui
   }
   const cv4<T> e0 = polarisation<T>(p[0], (hel >> leg[0]) & 1u);
   double mr, mi;
-  if constexpr (LDS) {
+  if constexpr (LDS && std::is_same<T, double>::value) {
+    __syncthreads();  // as below
+    const Fp64Span<N - 1, kLdsLanes> ks{tab->leg + threadIdx.x, tab->sc + threadIdx.x};
+#pragma unroll
+    for (int t = 0; t < N - 1; ++t) ks.put_leg(t, k[t]);
+    bg_amplitude_d<N - 1, kLdsLanes>(ks, src, e0, mr, mi);
+  } else if constexpr (LDS) {
     // the generation kernel carries its momentum permutation (doubles) in this memory: the
     // barrier keeps the compiler from moving the table fill above those accesses (the
     // workgroup is one wave, so it costs nothing else)
@@ -543,7 +562,7 @@ __device__ __forceinline__ double ordered_amp2(const double (&p)[N][4], const ui
     SpanKLegs<N - 1, T> ks{k};
     bg_amplitude<N - 1, T>(ks, src, e0, mr, mi);
   }
-  return ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2));
+  return rec_done(ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2)));
 }
 
 // Angles of the real polarisations of an event (random_polarisation): leg k takes word k % 4
@@ -566,7 +585,7 @@ __device__ __forceinline__ void polarisation_angles(const GenClass& C, int64_t i
 // ordered_amp2.
 template <int N, typename T, bool LDS>
 __device__ __forceinline__ double ordered_amp2_real(const double (&p)[N][4], const uint32_t (&leg)[N],
-                                                    const double (&cs)[N][2], LdsTable<N>* tab) {
+                                                    const double (&cs)[N][2], RecLds<N, T>* tab) {
   double esum = 0.0;
 #pragma unroll
   for (int t = 0; t < N; ++t) esum += fabs(p[t][0]);
@@ -607,7 +626,7 @@ __device__ __forceinline__ double ordered_amp2_real(const double (&p)[N][4], con
     SpanKLegs<N - 1, T> ks{k};
     m = bg_amplitude_r<N - 1, T>(ks, src, e0);
   }
-  return ldexp(m * m, 2 * ex * (4 - N) - (N - 2));
+  return rec_done(ldexp(m * m, 2 * ex * (4 - N) - (N - 2)));
 }
 
 // The same with the event spread over the G lanes of a group; g is this lane's place in it.
@@ -662,7 +681,7 @@ __device__ __forceinline__ double ordered_amp2_g(const double (&p)[N][4], const 
     const SpanKGroup<N - 1, G, T, fwd_afresh<N, T, G>()> ks{k, lsd.sg};
     bg_amplitude_g<N - 1, G, T>(ls, ks, src, e0, mr, mi);
   }
-  return ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2));
+  return rec_done(ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2)));
 }
 
 // Compensated (sum w, sum w^2) of a workgroup of up to 256 lanes, in a fixed tree order;
@@ -747,10 +766,12 @@ __device__ __forceinline__ double finish_event(const GenClass& C, int64_t i, boo
 // One event: draws -> kinematics -> cuts -> |A|^2 -> weight; writes outputs; returns w.
 // With G > 1 lanes per event every lane of the group evaluates the kinematics (the same
 // values), the recursion is shared, and lane g = 0 writes the outputs and returns w
-// (the others return 0).  Not used for the table classes, which run split (bg_split.hpp).
-template <int N, typename T, int G = 1, int POL = 0, bool KLDS = false>
+// (the others return 0).
+// With LDS (one lane) the recursion uses the workgroup's table tab, which may lie over the memory
+// of perm: the kinematics are done with it by then.
+template <int N, typename T, int G = 1, int POL = 0, bool LDS = false>
 __device__ __forceinline__ double generate_one(const GenClass& C, int64_t i, PermLds perm, int g = 0,
-                                               T* ktab = nullptr, int lanes = 0) {
+                                               RecLds<N, T>* tab = nullptr) {
   static_assert(POL == 0 || G == 1, "real polarisations run one lane per event");
   using Kin = typename std::conditional<G == 1, EventKin<N>, EventKinPos<N>>::type;
   Kin ev;
@@ -764,44 +785,64 @@ __device__ __forceinline__ double generate_one(const GenClass& C, int64_t i, Per
     build_event_positions<N>(C, i, ev, g == 0);
     pass = cuts_positions<N>(C, ev, ht, rmin);
   }
+  const double r = scale_ratio<N>(C, ht, ev.x1, ev.x2);
+  if (C.out.obs && g == 0) {
+    C.out.obs[2 * i] = ht;
+    C.out.obs[2 * i + 1] = rmin;
+  }
   // |A|^2 is Lorentz invariant: evaluated in the partonic centre-of-mass frame
   double a2;
   if constexpr (POL == 1) {
     double cs[N][2];
     polarisation_angles<N>(C, i, cs);
-    a2 = ordered_amp2_real<N, T, false>(ev.pc, ev.leg, cs, nullptr);
+    a2 = ordered_amp2_real<N, T, LDS>(ev.pc, ev.leg, cs, tab);
   } else if constexpr (G == 1) {
-    a2 = ordered_amp2<N, T, false>(ev.pc, ev.leg, ev.hel, nullptr);
+    a2 = ordered_amp2<N, T, LDS>(ev.pc, ev.leg, ev.hel, tab);
   } else {
-    a2 = ordered_amp2_g<N, T, G, KLDS>(ev.pc, ev.leg, ev.hel, g, ktab, lanes);
+    a2 = ordered_amp2_g<N, T, G, false>(ev.pc, ev.leg, ev.hel, g);
   }
   if (g != 0) return 0.0;
-  if (C.out.obs) {
-    C.out.obs[2 * i] = ht;
-    C.out.obs[2 * i + 1] = rmin;
-  }
-  return finish_event<N>(C, i, pass, a2, ev.shat, ev.x1, ev.x2, scale_ratio<N>(C, ht, ev.x1, ev.x2));
+  return finish_event<N>(C, i, pass, a2, ev.shat, ev.x1, ev.x2, r);
 }
 
 // Waves per SIMD the compiler may leave room for in the one-lane recursion kernels.  A limit of
 // one pads the register allocation beyond 256, so that a second wave never fits, and is kept
 // only where the recursion needs that many: below, several waves hide the latency of the loads
 // and of the FP64 chains (n = 4 FP32 recursion kernel, 2^22 events: 242 us at one wave, 170 us
-// at seven, HBM bound).
+// at seven).  FP64 n = 6 fits 256 registers when told to (264 otherwise).
 template <int N, typename T, int POL>
 constexpr int rec_waves() {
   constexpr int words = (Spans<N - 1>::count * (POL == 0 ? 8 : 4) + 2 * N) * (int)(sizeof(T) / 4);
-  return words > 210 ? 1 : 8;
+  return words > (sizeof(T) == 8 && UseLdsK<N, T>::value && POL == 0 ? 270 : 210) ? 1 : 8;
+}
+template <int N, typename T, int POL>
+constexpr int rec_waves_min() { return sizeof(T) == 8 && POL == 0 && N == 6 ? 2 : 1; }
+
+// Single-class generation in one kernel, the classes with n <= 6: one event per lane, the
+// kinematics' momentum permutation and the recursion's table in the same LDS, one compensated
+// partial per 64 events.  Launch: kLdsLanes threads; partials may be NULL.
+template <int N, typename T, int POL>
+__global__ __launch_bounds__(kLdsLanes)
+    __attribute__((amdgpu_waves_per_eu(rec_waves_min<N, T, POL>(), rec_waves<N, T, POL>()))) void k_generate_lds(
+        GenClass C, double* partials) {
+  constexpr unsigned kTab = sizeof(RecLds<N, T>), kPerm = perm_lds_bytes(N, kLdsLanes);
+  __shared__ __align__(16) unsigned char lds[kTab > kPerm ? kTab : kPerm];
+  const int64_t i = (int64_t)blockIdx.x * kLdsLanes + threadIdx.x;
+  double w = 0.0;
+  if (i < C.count)
+    w = generate_one<N, T, 1, POL, true>(C, i, PermLds{reinterpret_cast<double*>(lds) + threadIdx.x, kLdsLanes}, 0,
+                                         reinterpret_cast<RecLds<N, T>*>(lds));
+  if (partials) block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0}, partials + 4 * (int64_t)blockIdx.x);
 }
 
-// Single-class generation of a class without the span table (FP32 n = 9, FP64 n <= 6): one
-// event per lane, one compensated partial per workgroup.  Launch: blockDim.x in
-// {64, 128, 192, 256} with perm_lds_bytes(N, blockDim.x) bytes of dynamic LDS; partials may
-// be NULL.
+// Single-class generation in one kernel without the table (FP32 n = 9 with one lane, real
+// polarisations beyond FP32 n = 8 and in FP64): one event per lane, one compensated partial per
+// workgroup.  Launch: blockDim.x in {64, 128, 192, 256} with perm_lds_bytes(N, blockDim.x) bytes of
+// dynamic LDS; partials may be NULL.
 template <int N, typename T, int POL = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, T, POL>()))) void k_generate(
     GenClass C, double* partials) {
-  static_assert(!UseLdsK<N, T>::value, "the table classes generate in the split form");
+  static_assert(POL == 1 || !UseLdsK<N, T>::value, "the table classes have their own kernels");
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double w = 0.0;
   if (i < C.count) w = generate_one<N, T, 1, POL>(C, i, dyn_perm());
@@ -811,7 +852,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, rec_wave
 // |A|^2 from given momenta (bg_amp2): momenta [count][N][4] physical, gathered in colour order.
 template <int N, typename T>
 __global__ __launch_bounds__((UseLdsK<N, T>::value ? kLdsLanes : 256))
-    __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, T, 0>()))) void k_amp2(
+    __attribute__((amdgpu_waves_per_eu(rec_waves_min<N, T, 0>(), rec_waves<N, T, 0>()))) void k_amp2(
         int64_t count, const double* __restrict__ mom, const uint32_t* __restrict__ hel,
         const uint8_t* __restrict__ order, double* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -827,7 +868,7 @@ __global__ __launch_bounds__((UseLdsK<N, T>::value ? kLdsLanes : 256))
     for (int mu = 0; mu < 4; ++mu) p[t][mu] = q[mu];
   }
   if constexpr (UseLdsK<N, T>::value) {
-    __shared__ LdsTable<N> tab;
+    __shared__ RecLds<N, T> tab;
     out[i] = ordered_amp2<N, T, true>(p, leg, hel[i], &tab);
   } else {
     out[i] = ordered_amp2<N, T, false>(p, leg, hel[i], nullptr);

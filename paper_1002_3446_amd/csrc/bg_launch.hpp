@@ -9,31 +9,39 @@
 
 namespace bgk {
 
-// FP32 classes with n <= 8 keep their span momenta and propagators in an LDS table
-// (SpanKLds) and run with 64-lane workgroups: at n = 8 four workgroups use 143 KB of a
-// compute unit's 160 KB.  Larger n and FP64 sum the FP64 leg momenta at every use.
+// Classes with n <= 8 run the recursion one event per lane in 64-lane workgroups with a table in
+// LDS: FP32 every span momentum and propagator (LdsTable; n = 8: four workgroups use 131 KB of a
+// compute unit's 160 KB), FP64 the leg momenta and span scalars (Fp64Lds; 139 KB).  Larger n sum
+// the FP64 leg momenta at every use.
 constexpr int kLdsLanes = 64;
 
-// Dynamic LDS of the generation kernels without the span table: the per-lane column of the
+// Dynamic LDS of the generation kernels without that table: the per-lane column of the
 // leg-to-position momentum permutation, 4 (n - 2) doubles per lane.
 constexpr unsigned perm_lds_bytes(int n, int block) { return 8u * 4u * (unsigned)(n - 2) * (unsigned)block; }
-constexpr bool lds_span_table(int n, int prec) { return prec == 32 && n <= 8; }
+constexpr bool lds_span_table(int n, int prec) { return (prec == 32 || prec == 64) && n <= 8; }
 
-// The table classes generate events in two kernels (kinematics at several waves per SIMD,
-// then the recursion at one), joined by a staging buffer of split_words(n) doubles per event.
-constexpr bool split_form(int n, int prec) { return lds_span_table(n, prec); }
+// Of those, n = 7, 8 generate events in two kernels (kinematics at several waves per SIMD, then
+// the recursion at one), joined by a staging buffer of split_words(n) doubles per event.  Up to
+// n = 6 the recursion needs no more registers than the kinematics hide their latency with, so
+// one kernel does both and the staging traffic and a launch go (k_generate_lds; us per call against the
+// two kernels: FP32 n = 4, 2^22 events 224 / 328, 2^21 events n = 5 172 / 222, n = 6 299 / 308; FP64
+// n = 5 229 / 256, n = 6 334 / 395).
+constexpr bool split_form(int n, int prec) { return lds_span_table(n, prec) && n >= 7; }
 constexpr int split_words(int n) { return 4 * (n - 1) + 5; }
 
-// Lane forms the library holds per (n, prec): one event per lane where the recursion fits a
-// lane's 512 registers (FP32 n <= 9, FP64 n <= 6); two lanes per event from FP32 n = 9 and
-// FP64 n = 6 on (the one-lane form spills kilobytes per lane beyond that); four lanes for
-// FP64 n >= 10, where two still spill (FP64 n = 12: 2.9 KB per lane with two, 448 B with
-// four).  Which form runs is a launch
-// setting (bg_set_lanes), defaulting to default_lanes.
+// Lane forms of a class as a launch setting (bg_set_lanes), defaulting to default_lanes: one
+// event per lane (FP32 n <= 9, FP64 n <= 6); two lanes per event from FP32 n = 9 and FP64 n = 6 on
+// (the one-lane form would spill kilobytes per lane at large n); four lanes for FP64 n >= 10, where
+// two still spill (FP64 n = 12: 2.9 KB per lane with two, 448 B with four).  FP64 n = 7, 8 hold one
+// form only, selected by the setting 2: the recursion with one event per lane, whose LDS leg
+// momenta and span scalars leave its registers to the currents (kernel_lanes).  It took the
+// place of the two-lane form there (bg_amp2, n = 7, 5 10^5 events: 162 -> 99 us; generation, n = 8,
+// 1.5 10^6 events: 965 -> 765 us).
 constexpr bool has_one_lane(int n, int prec) { return prec == 32 ? n <= 9 : n <= 6; }
 constexpr bool has_lane_pairs(int n, int prec) { return prec == 32 ? n >= 9 : n >= 6; }
 constexpr bool has_lane_quads(int n, int prec) { return prec == 64 && n >= 10; }
 constexpr int default_lanes(int n, int prec) { return prec == 32 ? (n >= 10 ? 2 : 1) : (n >= 10 ? 4 : (n >= 7 ? 2 : 1)); }
+constexpr int kernel_lanes(int n, int prec, int setting) { return prec == 64 && (n == 7 || n == 8) ? 1 : setting; }
 
 // Classes built with real polarisations (real currents: half the registers of complex ones,
 // so one lane per event fits every FP32 class).
@@ -89,7 +97,7 @@ struct Launchers {
   GenerateFn generate;   // one lane per event (the split form for the table classes)
   Amp2Fn amp2;
   GradFn grad;
-  GenerateFn generate2;  // two lanes per event (where has_lane_pairs)
+  GenerateFn generate2;  // the setting 2 (where has_lane_pairs): two lanes per event, or kernel_lanes
   Amp2Fn amp2_2;
   GenerateFn generate_real;  // real polarisations, one lane per event (where has_real_pol)
   GenerateFn generate_w;     // W-tensor form, 16 lanes per event (where has_wtensor)

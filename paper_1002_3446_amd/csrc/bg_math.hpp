@@ -62,6 +62,22 @@ __host__ __device__ __forceinline__ double sqrt_fp64(double x) {
 #endif
 }
 
+// 1 / sqrt(x) of a normal positive x within about one ulp: two Newton steps on the hardware's
+// estimate (x = 0 gives no number).
+__host__ __device__ __forceinline__ double rsqrt_fp64(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double g = x * y;
+    y = std::fma(0.5 * y, std::fma(-g, y, 1.0), y);
+  }
+  return y;
+#else
+  return 1.0 / std::sqrt(x);
+#endif
+}
+
 // ln 2 as a 42-bit head (so that e * head is exact for every binary exponent e of a double)
 // plus the FP64 rounding of the remainder
 constexpr double kLn2Hi = 0x1.62e42fefa3800p-1;

@@ -1,4 +1,5 @@
-// Generation of a table-recursion class (FP32, n <= 8) as two kernels: k_kin evaluates the
+// Generation of a class as two kernels (n = 7, 8 one event per lane; two or four lanes per event;
+// the staged classes of the persistent multi-class launch): k_kin evaluates the
 // kinematics (draws, parton fractions, RAMBO, boost, cuts) at several waves per SIMD, which
 // hides the latency of its long FP64 chains, and hands each event's centre-of-mass momenta,
 // s_hat, x1, x2, helicity word, cut flag and leg positions to k_rec through a staging
@@ -119,9 +120,9 @@ __device__ __forceinline__ double finish_staged(const GenClass& C, int64_t i, in
 
 // |A|^2, weight and outputs of event i from its staged words (one lane per event, the span
 // table in tab); returns w.
-template <int N, int POL = 0>
+template <int N, typename T, int POL>
 __device__ __forceinline__ double rec_staged(const GenClass& C, int64_t i, int64_t j, const double* __restrict__ buf,
-                                             const Staged<N>& s, LdsTable<N>* tab) {
+                                             const Staged<N>& s, RecLds<N, T>* tab) {
   double pc[N][4];
   // position 0: the beam leg 0, as build_event forms it
   const double hb = 0.5 * (C.use_pdf ? sqrt(s.shat) : C.sqrt_s);
@@ -139,20 +140,20 @@ __device__ __forceinline__ double rec_staged(const GenClass& C, int64_t i, int64
   if constexpr (POL == 1) {
     double cs[N][2];
     polarisation_angles<N>(C, i, cs);
-    a2 = ordered_amp2_real<N, float, true>(pc, leg, cs, tab);
+    a2 = ordered_amp2_real<N, T, true>(pc, leg, cs, tab);
   } else {
-    a2 = ordered_amp2<N, float, true>(pc, leg, s.word.hel(), tab);
+    a2 = ordered_amp2<N, T, true>(pc, leg, s.word.hel(), tab);
   }
   return finish_staged<N>(C, i, j, buf, s.word.pass(), a2, s.shat);
 }
 
 // The same from staging slot j.
-template <int N, int POL = 0>
+template <int N, typename T = float, int POL = 0>
 __device__ __forceinline__ double rec_one(const GenClass& C, int64_t i, int64_t j, const double* __restrict__ buf,
-                                          LdsTable<N>* tab) {
+                                          RecLds<N, T>* tab) {
   Staged<N> s;
   load_staged<N>(buf, j, s);
-  return rec_staged<N, POL>(C, i, j, buf, s, tab);
+  return rec_staged<N, T, POL>(C, i, j, buf, s, tab);
 }
 
 // The same with the event on the G lanes of a group (the grouped recursion; span momenta
@@ -202,10 +203,10 @@ __global__ __launch_bounds__(kKinBlock) void k_kin(GenClass C, int64_t first, in
 template <int N>
 constexpr bool rec_prefetch() { return N >= 8; }
 
-template <int N, int POL>
-__global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, float, POL>()))) void k_rec(
+template <int N, typename T, int POL>
+__global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, T, POL>()))) void k_rec(
     GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials, int64_t ahead) {
-  __shared__ LdsTable<N> tab;
+  __shared__ RecLds<N, T> tab;
   __shared__ unsigned int scrap[rec_prefetch<N>() ? kLdsLanes : 1];
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   Staged<N> st;
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, re
     }
   }
   double w = 0.0;
-  if (j < cnt) w = rec_staged<N, POL>(C, first + j, j, buf, st, &tab);
+  if (j < cnt) w = rec_staged<N, T, POL>(C, first + j, j, buf, st, &tab);
   if (partials) block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0}, partials + 4 * (first / kLdsLanes + (int64_t)blockIdx.x));
 }
 
@@ -268,7 +269,7 @@ hipError_t launch_generate_split_g(const GenClass& C, const GenWork& W, int bloc
 
 // Both kernels over the class in chunks of W.stage_cap events (a multiple of 64) through the
 // caller's staging buffer; one partial per 64 events, in event order, whatever the chunking.
-template <int N, int POL = 0>
+template <int N, typename T, int POL = 0>
 hipError_t launch_generate_split(const GenClass& C, const GenWork& W, hipStream_t s) {
   if (C.count <= 0) return hipSuccess;
   if (!W.stage || W.stage_cap < kLdsLanes || W.stage_cap % kLdsLanes != 0) return hipErrorInvalidValue;
@@ -279,7 +280,7 @@ hipError_t launch_generate_split(const GenClass& C, const GenWork& W, hipStream_
                        perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage);
     e = hipGetLastError();
     if (e != hipSuccess) break;
-    hipLaunchKernelGGL((k_rec<N, POL>), dim3((unsigned)((cnt + kLdsLanes - 1) / kLdsLanes)), dim3(kLdsLanes), 0, s, C,
+    hipLaunchKernelGGL((k_rec<N, T, POL>), dim3((unsigned)((cnt + kLdsLanes - 1) / kLdsLanes)), dim3(kLdsLanes), 0, s, C,
                        first, cnt, W.stage, W.partials, W.ahead);
     e = hipGetLastError();
   }

@@ -145,13 +145,20 @@ def _ptr(t, dtype, shape, name):
         raise ValueError(f"{name}: expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:   # torch.Size is a tuple
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
     return t.data_ptr()
 
 
 def _stream(device):
-    return torch.cuda.current_stream(device).cuda_stream
+    """Handle of torch's current stream on a CUDA device (its current device if it has no
+    index).  The Stream object torch.cuda.current_stream would build costs 3 us a call."""
+    device = torch.device(device)
+    if device.type != "cuda":
+        return torch.cuda.current_stream(device).cuda_stream   # torch's own error
+    torch.cuda.init()   # nothing to do but for a process's first call
+    index = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
 
 _OUT_SPEC = {  # name -> (dtype, shape given N and n)

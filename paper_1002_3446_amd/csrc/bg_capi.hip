@@ -265,7 +265,7 @@ int from_hip(hipError_t e) { return e == hipSuccess ? BG_OK : BG_EHIP; }
 // ----------------------------------------------------------------------------------------
 // Device workspace.  Every per-call buffer (compensated-sum partials, staging between the
 // kinematics and recursion kernels, the gradient's intermediate adjoints, the multi-class
-// work list) is allocated stream-ordered on the caller's stream from a memory pool the
+// work list) is a small kept buffer (Workspace) or allocated stream-ordered on the caller's stream from a memory pool the
 // library creates once per device; the pool keeps up to kPoolKeep bytes reserved between
 // calls, so that repeated calls do not map fresh device memory each time.
 // ----------------------------------------------------------------------------------------
@@ -310,14 +310,111 @@ int ws_alloc(void** p, size_t bytes, hipStream_t s) {
   return BG_OK;
 }
 
-// Stream-ordered device workspace, released on the stream when the owner goes out of scope.
+// Small workspaces are kept between calls: a stream-ordered allocation and release cost 12 us of
+// host time, three times the launches of a short call (one generation call of 1000 events, n = 6:
+// 48 us with them, 27 without).  Up to kKeepBuffers buffers of at most kKeepBytes per device, each
+// of one stream, with an event recorded after the last call that used it.  A call takes a free
+// buffer of its stream and waits for the event all the same (a stream's handle may come back for
+// another stream), so calls on different streams and threads neither share a buffer nor wait for
+// each other; a buffer whose stream made none of the last kStaleTakes takes goes to the stream
+// that asks.  A buffer too small for its stream is given back to the memory pool for a larger
+// one.  A capturing stream takes none (a graph must own its memory), nor does a call that finds
+// no slot: they allocate.
+constexpr int kKeepBuffers = 8;
+constexpr size_t kKeepBytes = size_t(4) << 20;
+constexpr uint64_t kStaleTakes = 4096;
+
+struct KeptBuffer {
+  void* p = nullptr;
+  size_t cap = 0;
+  hipEvent_t done = nullptr;
+  hipStream_t last = nullptr;
+  uint64_t taken = 0;  // the device's take count when it was last taken
+  bool used = false;
+};
+
+std::mutex g_kept_mu;
+KeptBuffer g_kept[64][kKeepBuffers];
+uint64_t g_takes[64];
+
+// Device workspace of one call on a stream: a kept buffer, or stream-ordered memory released on
+// the stream when the owner goes out of scope.
 struct Workspace {
   void* p = nullptr;
   hipStream_t s;
+  KeptBuffer* kept = nullptr;
+
+  int alloc(size_t bytes) {
+    if (bytes > 0 && bytes <= kKeepBytes && take_kept(bytes)) return BG_OK;
+    return ws_alloc(&p, bytes, s);
+  }
   ~Workspace() {
-    if (p) (void)hipFreeAsync(p, s);
+    if (kept) {
+      (void)hipEventRecord(kept->done, s);
+      std::lock_guard<std::mutex> lk(g_kept_mu);
+      kept->used = false;
+    } else if (p) {
+      (void)hipFreeAsync(p, s);
+    }
   }
   double* d() const { return static_cast<double*>(p); }
+
+ private:
+  bool take_kept(size_t bytes) {
+    int dev = 0;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return false;
+    }
+    std::lock_guard<std::mutex> lk(g_kept_mu);
+    const uint64_t now = ++g_takes[dev];
+    // this stream's smallest buffer that fits; else the best slot to put one in: its own smaller
+    // buffer, an empty slot, a stale one
+    KeptBuffer *fit = nullptr, *slot = nullptr;
+    int rank = 3;
+    for (KeptBuffer& b : g_kept[dev]) {
+      if (b.used) continue;
+      const bool own = b.p && b.last == s;
+      if (own && b.cap >= bytes) {
+        if (!fit || b.cap < fit->cap) fit = &b;
+        continue;
+      }
+      const int r = own ? 0 : (!b.p ? 1 : (now - b.taken > kStaleTakes ? 2 : 3));
+      if (r < rank) {
+        rank = r;
+        slot = &b;
+      }
+    }
+    if (!fit && !slot) return false;
+    KeptBuffer* b = fit ? fit : slot;
+    if (!b->done && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      b->done = nullptr;
+      return false;
+    }
+    if (b->p && hipStreamWaitEvent(s, b->done, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (b->cap < bytes) {
+      size_t cap_bytes = size_t(1) << 16;
+      while (cap_bytes < bytes) cap_bytes *= 2;
+      void* q = nullptr;
+      if (ws_alloc(&q, cap_bytes, s) != BG_OK) return false;
+      if (b->p) (void)hipFreeAsync(b->p, s);
+      b->p = q;
+      b->cap = cap_bytes;
+    }
+    b->last = s;
+    b->taken = now;
+    fit = b;
+    fit->used = true;
+    kept = fit;
+    p = fit->p;
+    return true;
+  }
 };
 
 // ----------------------------------------------------------------------------------------
@@ -537,8 +634,8 @@ int generate_multi(const bg_config* cfgs, const GenClass* G, const bg_outputs* o
   std::memcpy(blob.data() + o_cls, mcs.data(), mcs.size() * sizeof(MultiClass));
   std::memcpy(blob.data() + o_tiles, tiles.data(), tiles.size() * sizeof(Tile));
   Workspace ws{nullptr, s}, stage{nullptr, s};
-  int st = ws_alloc(&ws.p, bytes, s);
-  if (st == BG_OK) st = ws_alloc(&stage.p, (size_t)stage_words * sizeof(double), s);
+  int st = ws.alloc(bytes);
+  if (st == BG_OK) st = stage.alloc((size_t)stage_words * sizeof(double));
   if (st != BG_OK) return st;
   unsigned char* w = static_cast<unsigned char*>(ws.p);
   // pageable source: the copy is staged before hipMemcpyAsync returns, so blob may go
@@ -824,7 +921,7 @@ int bg_generate(const bg_config* cfgs, int ncfg, const int64_t* counts, const bg
     for (int k : todo) soff[k] = bytes;
   bytes += shared_stage;
   Workspace ws{nullptr, s};
-  if (int st = ws_alloc(&ws.p, bytes, s); st != BG_OK) return st;
+  if (int st = ws.alloc(bytes); st != BG_OK) return st;
   // the one-lane recursion prefetches the tile half a resident round ahead (two workgroups per
   // CU): a full round ahead, more than half of the prefetched lines left L2 before their use
   // (the recursion kernel read 58% more from HBM, for the same time)
@@ -981,7 +1078,7 @@ int bg_amp2_grad(const bg_config* cfg, int64_t N, const double* uniforms, const 
   hipStream_t s = (hipStream_t)stream;
   Workspace ws{nullptr, s};
   // the recursion's adjoints between the two gradient kernels: 12 (n - 1) + 1 words per event
-  if (int st = ws_alloc(&ws.p, (size_t)N * (12 * (cfg->n - 1) + 1) * sizeof(double), s); st != BG_OK) return st;
+  if (int st = ws.alloc((size_t)N * (12 * (cfg->n - 1) + 1) * sizeof(double)); st != BG_OK) return st;
   G.pbuf = ws.d();
   const Shape sh = shape_of(cfg->n, cfg->prec);
   return from_hip(L->grad(G, sh.block, s));

@@ -84,17 +84,21 @@ def has_wtensor(n: int, p: int) -> bool:
 
 
 def unit_flags(n: int, p: int, k: int, f: int) -> list[str]:
-    """Extra compiler flags of one kernel unit.  The generation and bg_amp2 units of FP64 n >= 9
-    (two or four lanes) are built without LLVM's pre-RA machine scheduler: there the recursion
-    fills the register file at one wave per SIMD, and the scheduler's reordering for latency
-    raises register pressure, which costs more (scratch spill, AGPR copies) than the latency it
-    hides.  Measured on generation, alternating runs on one GPU, per 2^22 events: n = 9 5.23 ->
-    5.01, n = 10 unchanged, n = 11 12.99 -> 12.71, n = 12 20.57 -> 18.45 ms (scratch 400 -> 248 B
-    per lane).  The one-lane recursions keep it: n = 8 FP32 5.55 against 5.51 ms per 2^24 events,
-    FP64 n = 7 bg_amp2 101 against 99 us per 5 10^5."""
-    if k < 2 and p == 64 and f in (2, 5) and n >= 9:
-        return ["-mllvm", "-enable-misched=0"]
-    return []
+    """Extra compiler flags of one kernel unit.  The generation and bg_amp2 units of FP64 n = 9
+    (two lanes), n >= 10 with two lanes and n >= 11 with four are built without LLVM's pre-RA
+    machine scheduler: there the recursion fills the register file, and the scheduler's
+    reordering for latency raises register pressure, which costs more (scratch spill, AGPR
+    copies) than the latency it hides: four lanes, 2^18 events, n = 11 611 against 598 us, n = 12
+    1023 against 868 us; n = 10 keeps it, 420 against 430 us.  The one-lane recursions keep it
+    too: n = 8 FP32 5.55 (without) against 5.51 ms per 2^24 events, FP64 n = 7 bg_amp2 101
+    against 99 us per 5 10^5.  The four-lane units' matrix sums write vector registers: into
+    accumulation registers, as the compiler would place them, every sum costs two copies."""
+    flags = []
+    if k < 2 and p == 64 and (f == 2 and n >= 9 or f == 5 and n >= 11):
+        flags += ["-mllvm", "-enable-misched=0"]
+    if k < 2 and p == 64 and f == 5:
+        flags += ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+    return flags
 
 
 def units_for(ns, precs=(32, 64), kinds=KINDS):

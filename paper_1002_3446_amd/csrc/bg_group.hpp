@@ -215,9 +215,7 @@ struct SpanKGroup {
   const double (&sg)[C];     // their metric signs
   // With AFRESH, every use sums afresh: an optimisation barrier on the first term keeps the
   // compiler from merging the sums of one span over the whole kernel and holding them in
-  // registers (the gradient kernels, which hold currents and adjoints, and the FP64 forward
-  // forms that would otherwise spill gain registers; elsewhere the forward kernels lose more
-  // to the extra FP64 adds than they gain).
+  // registers (the gradient kernels, which hold currents and adjoints, gain registers).
   template <int A, int B>
   __device__ __forceinline__ void sum(double d[C]) const {
 #pragma unroll
@@ -417,6 +415,350 @@ __device__ __forceinline__ void bg_amplitude_g(const LaneShare<G, T>& ls, const 
   cdot_g<G>(ls, eps0, V, mr, mi);
   m_re = double(mr);
   m_im = double(mi);
+}
+
+// ----------------------------------------------------------------------------------------
+// FP64 with an event on a pair of lanes (n = 6, n >= 9).  What limits these classes is where a lane
+// keeps its currents (n = 12: 498 registers of 512), so, as in the one-lane FP64 form
+// (bg_amplitude_d), the covariant leg momenta and the span scalars -S/2 live in LDS and brackets
+// accumulate V / 2 in one vector.  Lane 0 holds the components (0, 1), lane 1 (3, 2): the first
+// slot of a source then has a zero imaginary part on both lanes (LX, LY: leaf operands), the
+// second slot the metric sign -1 on both, and only the first slot's sign (+, -) differs.
+// Generation, 2^18 events: n = 9 313 -> 272 us, n = 10 (four lanes before) 576 -> 433 us.
+// ----------------------------------------------------------------------------------------
+struct cvp {
+  double re[2], im[2];
+};
+
+// LDS per lane: legs [L][lane] as (K_first, K_second), then scalars [span][lane] with the real part
+// in the pair's even lane and the imaginary part in its odd one.
+template <int L>
+constexpr int pair_lds_bytes() { return 16 * L + 8 * (Spans<L>::count - L - 1); }
+
+template <int L>
+struct PairSpan {
+  double2* leg;      // &leg[0][lane]
+  double* sc;        // &sc[0][lane]
+  const double2* rd; // &sc[0][lane & ~1], the pair's scalar
+  int lanes;         // lanes per workgroup (row stride)
+  double sg;         // metric sign of the first slot
+  int g;             // lane of the pair
+  __device__ __forceinline__ PairSpan(unsigned char* lds, int lane, int lanes_)
+      : leg(reinterpret_cast<double2*>(lds) + lane),
+        sc(reinterpret_cast<double*>(lds + 16 * L * lanes_) + lane),
+        rd(reinterpret_cast<const double2*>(lds + 16 * L * lanes_) + (lane >> 1)),
+        lanes(lanes_),
+        sg((lane & 1) ? -1.0 : 1.0),
+        g(lane & 1) {}
+  template <int A>
+  __device__ __forceinline__ void add(double (&K)[2]) const {
+    const double2 k = leg[A * lanes];
+    K[0] += k.x;
+    K[1] += k.y;
+  }
+  // legs A..B summed left to right
+  template <int A, int B>
+  __device__ __forceinline__ void sum(double (&K)[2]) const {
+    const double2 k = leg[A * lanes];
+    K[0] = k.x;
+    K[1] = k.y;
+    static_for<A + 1, B + 1>([&](auto t) { add<decltype(t)::value>(K); });
+  }
+  template <int S>
+  __device__ __forceinline__ void put_scalar(double r, double i) const { sc[(S - L) * lanes] = g ? i : r; }
+  template <int S>
+  __device__ __forceinline__ double2 scalar() const { return rd[(S - L) * (lanes / 2)]; }
+};
+
+// x . y over the pair; xs: x with the first slot times its metric sign (pair_signed)
+template <bool LX, bool LY>
+__device__ __forceinline__ void pdot(const cvp& xs, const cvp& y, double& r, double& i) {
+  r = xs.re[0] * y.re[0];
+  r = fmac(-xs.re[1], y.re[1], r);
+  r = fmac(xs.im[1], y.im[1], r);
+  i = -xs.re[1] * y.im[1];
+  i = fmac(-xs.im[1], y.re[1], i);
+  if constexpr (!LX && !LY) r = fmac(-xs.im[0], y.im[0], r);
+  if constexpr (!LY) i = fmac(xs.re[0], y.im[0], i);
+  if constexpr (!LX) i = fmac(xs.im[0], y.re[0], i);
+  r = group_sum<2>(r);
+  i = group_sum<2>(i);
+}
+
+// x . K over the pair for a covariant real K
+template <bool LX>
+__device__ __forceinline__ void prdot(const cvp& x, const double (&k)[2], double& r, double& i) {
+  r = group_sum<2>(fmac(x.re[1], k[1], x.re[0] * k[0]));
+  if constexpr (LX)
+    i = group_sum<2>(x.im[1] * k[1]);
+  else
+    i = group_sum<2>(fmac(x.im[1], k[1], x.im[0] * k[0]));
+}
+
+template <bool LY>
+__device__ __forceinline__ void paxpy(double cr, double ci, const cvp& y, cvp& acc) {
+  acc.re[0] = fmac(cr, y.re[0], acc.re[0]);
+  acc.im[0] = fmac(ci, y.re[0], acc.im[0]);
+  if constexpr (!LY) {
+    acc.re[0] = fmac(-ci, y.im[0], acc.re[0]);
+    acc.im[0] = fmac(cr, y.im[0], acc.im[0]);
+  }
+  acc.re[1] = fmac(-ci, y.im[1], fmac(cr, y.re[1], acc.re[1]));
+  acc.im[1] = fmac(ci, y.re[1], fmac(cr, y.im[1], acc.im[1]));
+}
+
+template <bool LX>
+__device__ __forceinline__ cvp pair_signed(double sg, const cvp& x) {
+  cvp s = x;
+  s.re[0] = sg * x.re[0];
+  if constexpr (!LX) s.im[0] = sg * x.im[0];
+  return s;
+}
+
+// Half the bracket sum of span [A..B] and its -S/2; KP is the span's momentum.
+template <int L, int A, int B>
+__device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (&J)[Spans<L>::count],
+                                              const double (&KP)[2], cvp& X, double& sr, double& si) {
+#pragma clang fp contract(off)
+  using SP = Spans<L>;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) X.re[c] = X.im[c] = 0.0;
+  sr = 0.0;
+  si = 0.0;
+  double ka[2];
+  static_for<A, B>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
+    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
+    double kb[2];
+    if constexpr (i == A)
+      ks.template sum<A, A>(ka);
+    else
+      ks.template add<i>(ka);
+    ks.template sum<i + 1, B>(kb);
+    const cvp xs = pair_signed<LA>(ks.sg, J[PA]);
+    double dr, di, ar, ai, br, bi;
+    pdot<LA, LB>(xs, J[PB], dr, di);
+    prdot<LA>(J[PA], kb, ar, ai);
+    prdot<LB>(J[PB], ka, br, bi);
+    paxpy<LB>(ar, ai, J[PB], X);
+    paxpy<LA>(-br, -bi, J[PA], X);
+    const double d0 = ks.sg * fmac(-0.5, KP[0], ka[0]), d1 = fmac(0.5, KP[1], -ka[1]);
+    X.re[0] = fmac(dr, d0, X.re[0]);
+    X.im[0] = fmac(di, d0, X.im[0]);
+    X.re[1] = fmac(dr, d1, X.re[1]);
+    X.im[1] = fmac(di, d1, X.im[1]);
+    sr = fmac(-0.5, dr, sr);
+    si = fmac(-0.5, di, si);
+    // the four-gluon pairs of this left current
+    static_for<i + 1, B>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      double er, ei;
+      pdot<LA, j + 1 == B>(xs, J[SP::at(j + 1, B)], er, ei);
+      paxpy<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
+    });
+  });
+  static_for<A + 1, B>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    const double2 c = ks.template scalar<SP::at(A, j)>();
+    paxpy<j + 1 == B>(c.x, c.y, J[SP::at(j + 1, B)], X);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const double2 c = ks.template scalar<SP::at(i + 1, B)>();
+    paxpy<i == A>(c.x, c.y, J[SP::at(A, i)], X);
+  });
+}
+
+template <int L>
+__device__ __forceinline__ void bg_amplitude_p(const PairSpan<L>& ks, const cvp (&src)[L], const cvp& eps0,
+                                               double& m_re, double& m_im) {
+  using SP = Spans<L>;
+  cvp J[SP::count];
+  static_for<0, L>([&](auto ac) { J[decltype(ac)::value] = src[decltype(ac)::value]; });
+  static_for<2, L>([&](auto lc) {
+    constexpr int len = decltype(lc)::value;
+    static_for<0, L - len + 1>([&](auto ac) {
+      constexpr int a = decltype(ac)::value, b = a + len - 1, s = SP::at(a, b);
+      asm volatile("" ::: "memory");  // momenta and scalars are read afresh in every span
+      cvp X;
+      double sr, si, K[2];
+      ks.template sum<a, b>(K);
+      span_vertex_p<L, a, b>(ks, J, K, X, sr, si);
+      double part;
+      {
+#pragma clang fp contract(off)
+        part = ks.sg * (K[0] * K[0]) - K[1] * K[1];
+      }
+      const double prop = 2.0 / group_sum<2>(part);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        J[s].re[c] = X.re[c] * prop;
+        J[s].im[c] = X.im[c] * prop;
+      }
+      ks.template put_scalar<s>(sr, si);
+    });
+  });
+  asm volatile("" ::: "memory");
+  cvp X;
+  double sr, si, K[2], mr, mi;
+  ks.template sum<0, L - 1>(K);
+  span_vertex_p<L, 0, L - 1>(ks, J, K, X, sr, si);
+  pdot<true, false>(pair_signed<true>(ks.sg, eps0), X, mr, mi);
+  m_re = 2.0 * mr;
+  m_im = 2.0 * mi;
+}
+
+// ----------------------------------------------------------------------------------------
+// FP64 with an event on four lanes (n >= 10 as bg_set_lanes names it), one Lorentz component per
+// lane.  Three quarters of a product's instructions would be its cross-lane sum (by DPP two moves
+// and an add per step and part: twelve for four multiply-adds), so the sums run on the matrix
+// cores: with A constant over its rows, D = A B of v_mfma_f64_4x4x4 gives every lane of a column
+// sum_k A_k B_k over the column's four lanes, the metric or plain ones in A.  Each costs four
+// issue slots (measured: 16.5 cycles, 32 to its result, no overlap with FP64 vector work) in place
+// of six.  Its columns are the lanes l, l + 16, l + 32, l + 48: lane 16 c + e holds component c of
+// event e of the wave.  Generation, 2^18 events, with the sums by DPP, scalars and momenta in
+// registers and one wave per SIMD: n = 11 819 -> 598 us, n = 12 1172 -> 868 us.  The instruction ignores the execution mask, so every lane of a wave runs
+// the recursion (callers clamp the event index).  No element of A is zero: a column's infinities
+// and NaN stay its own.
+// ----------------------------------------------------------------------------------------
+struct cvq {
+  double re, im;
+};
+
+__device__ __forceinline__ double quad_sum(double a, double x) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, x, 0.0, 0, 0, 0);
+}
+
+// LDS per wave: legs [L][lane], then scalars [span][event] as (re, im)
+template <int L>
+constexpr int quad_lds_bytes() { return 64 * 8 * L + 16 * 16 * (Spans<L>::count - L - 1); }
+
+template <int L>
+struct QuadSpan {
+  double* leg;   // &leg[0][lane], covariant
+  double* put;   // this lane's part of scalar 0
+  const double2* get;
+  double sg;     // metric sign of the lane's component
+  int c;         // component
+  __device__ __forceinline__ QuadSpan(unsigned char* lds, int lane)
+      : leg(reinterpret_cast<double*>(lds) + lane),
+        put(reinterpret_cast<double*>(lds + 64 * 8 * L) + 2 * (lane & 15) + ((lane >> 4) & 1)),
+        get(reinterpret_cast<const double2*>(lds + 64 * 8 * L) + (lane & 15)),
+        sg(lane < 16 ? 1.0 : -1.0),
+        c(lane >> 4) {}
+  template <int A, int B>
+  __device__ __forceinline__ double sum() const {
+    double k = leg[A * 64];
+    static_for<A + 1, B + 1>([&](auto t) { k += leg[decltype(t)::value * 64]; });
+    return k;
+  }
+  // (components 2, 3 write what 0, 1 write)
+  template <int S>
+  __device__ __forceinline__ void put_scalar(double r, double i) const { put[(S - L) * 32] = (c & 1) ? i : r; }
+  template <int S>
+  __device__ __forceinline__ double2 scalar() const { return get[(S - L) * 16]; }
+  __device__ __forceinline__ void dot(const cvq& x, const cvq& y, double& r, double& i) const {
+    r = quad_sum(sg, fmac(-x.im, y.im, x.re * y.re));
+    i = quad_sum(sg, fmac(x.im, y.re, x.re * y.im));
+  }
+  __device__ __forceinline__ void rdot(const cvq& x, double k, double& r, double& i) const {
+    r = quad_sum(1.0, x.re * k);
+    i = quad_sum(1.0, x.im * k);
+  }
+};
+
+__device__ __forceinline__ void qaxpy(double cr, double ci, const cvq& y, cvq& acc) {
+  acc.re = fmac(-ci, y.im, fmac(cr, y.re, acc.re));
+  acc.im = fmac(ci, y.re, fmac(cr, y.im, acc.im));
+}
+
+// Half the bracket sum of span [A..B] and its -S/2 (as span_vertex_p); KP is the span's momentum.
+template <int L, int A, int B>
+__device__ __forceinline__ void span_vertex_q(const QuadSpan<L>& ks, const cvq (&J)[Spans<L>::count], double KP, cvq& X,
+                                              double& sr, double& si) {
+#pragma clang fp contract(off)
+  using SP = Spans<L>;
+  X.re = X.im = sr = si = 0.0;
+  double ka = 0.0;
+  static_for<A, B>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
+    ka = i == A ? ks.template sum<A, A>() : ka + ks.template sum<i, i>();
+    const double kb = ks.template sum<i + 1, B>();
+    double dr, di, ar, ai, br, bi;
+    ks.dot(J[PA], J[PB], dr, di);
+    ks.rdot(J[PA], kb, ar, ai);
+    ks.rdot(J[PB], ka, br, bi);
+    const double dk = ks.sg * fmac(-0.5, KP, ka);
+    X.re = fmac(dr, dk, X.re);
+    X.im = fmac(di, dk, X.im);
+    sr = fmac(-0.5, dr, sr);
+    si = fmac(-0.5, di, si);
+    // the four-gluon pairs of this left current; each sum is used one product after it was
+    // issued, so that its latency is covered in the order written (the unit is built without the
+    // pre-RA scheduler)
+    double er = 0.0, ei = 0.0;
+    static_for<i + 1, B>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      double nr, ni;
+      ks.dot(J[PA], J[SP::at(j + 1, B)], nr, ni);
+      if constexpr (j == i + 1) {
+        qaxpy(ar, ai, J[PB], X);
+        qaxpy(-br, -bi, J[PA], X);
+      } else {
+        qaxpy(er, ei, J[SP::at(i + 1, j - 1)], X);
+      }
+      er = nr;
+      ei = ni;
+    });
+    if constexpr (i + 1 < B) {
+      qaxpy(er, ei, J[SP::at(i + 1, B - 1)], X);
+    } else {
+      qaxpy(ar, ai, J[PB], X);
+      qaxpy(-br, -bi, J[PA], X);
+    }
+  });
+  static_for<A + 1, B>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    const double2 s = ks.template scalar<SP::at(A, j)>();
+    qaxpy(s.x, s.y, J[SP::at(j + 1, B)], X);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const double2 s = ks.template scalar<SP::at(i + 1, B)>();
+    qaxpy(s.x, s.y, J[SP::at(A, i)], X);
+  });
+}
+
+template <int L>
+__device__ __forceinline__ void bg_amplitude_q(const QuadSpan<L>& ks, const cvq (&src)[L], const cvq& eps0,
+                                               double& m_re, double& m_im) {
+  using SP = Spans<L>;
+  cvq J[SP::count];
+  static_for<0, L>([&](auto ac) { J[decltype(ac)::value] = src[decltype(ac)::value]; });
+  static_for<2, L>([&](auto lc) {
+    constexpr int len = decltype(lc)::value;
+    static_for<0, L - len + 1>([&](auto ac) {
+      constexpr int a = decltype(ac)::value, b = a + len - 1, s = SP::at(a, b);
+      asm volatile("" ::: "memory");  // momenta and scalars are read afresh in every span
+      cvq X;
+      double sr, si;
+      const double K = ks.template sum<a, b>();
+      span_vertex_q<L, a, b>(ks, J, K, X, sr, si);
+      const double prop = 2.0 / quad_sum(ks.sg, K * K);
+      J[s].re = X.re * prop;
+      J[s].im = X.im * prop;
+      ks.template put_scalar<s>(sr, si);
+    });
+  });
+  asm volatile("" ::: "memory");
+  cvq X;
+  double sr, si, mr, mi;
+  span_vertex_q<L, 0, L - 1>(ks, J, ks.template sum<0, L - 1>(), X, sr, si);
+  ks.dot(eps0, X, mr, mi);
+  m_re = 2.0 * mr;
+  m_im = 2.0 * mi;
 }
 
 }  // namespace bgk

@@ -629,16 +629,10 @@ __device__ __forceinline__ double ordered_amp2_real(const double (&p)[N][4], con
   return rec_done(ldexp(m * m, 2 * ex * (4 - N) - (N - 2)));
 }
 
-// The same with the event spread over the G lanes of a group; g is this lane's place in it.
-// With ktab (this lane's column of a workgroup table of span_k_lds_bytes per lane, row
-// stride `lanes`), the span momenta come from LDS (SpanKGroupLds), else from registers.
-// Whether the grouped forward recursion forms each span momentum afresh at every use (FP64
-// with two lanes from n = 9, with four from n = 11): keeping every span's sums live would
-// spill there (n = 12, four lanes: 656 against 400 B of scratch per lane; n = 9, two lanes:
-// 512 against 288 B), and the extra FP64 additions cost less than the spill traffic.
-template <int N, typename T, int G>
-constexpr bool fwd_afresh() { return std::is_same<T, double>::value && (N >= 11 || (G == 2 && N >= 9)); }
-
+// The same with the event spread over the G lanes of a group (FP32; FP64 groups:
+// ordered_amp2_p, ordered_amp2_q); g is this lane's place in it.  With ktab (this lane's column
+// of a workgroup table of span_k_lds_bytes per lane, row stride `lanes`), the span momenta come
+// from LDS (SpanKGroupLds), else from registers.
 template <int N, typename T, int G, bool KLDS = false>
 __device__ __forceinline__ double ordered_amp2_g(const double (&p)[N][4], const uint32_t (&leg)[N], uint32_t hel,
                                                  int g, T* ktab = nullptr, int lanes = 0) {
@@ -678,9 +672,75 @@ __device__ __forceinline__ double ordered_amp2_g(const double (&p)[N][4], const 
     ks.fill();
     bg_amplitude_g<N - 1, G, T>(ls, ks, src, e0, mr, mi);
   } else {
-    const SpanKGroup<N - 1, G, T, fwd_afresh<N, T, G>()> ks{k, lsd.sg};
+    const SpanKGroup<N - 1, G, T> ks{k, lsd.sg};
     bg_amplitude_g<N - 1, G, T>(ls, ks, src, e0, mr, mi);
   }
+  return rec_done(ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2)));
+}
+
+// FP64 on a lane pair (PairSpan); lds: the workgroup's pair_lds_bytes<N - 1>() per lane.
+template <int N>
+__device__ __forceinline__ double ordered_amp2_p(const double (&p)[N][4], const uint32_t (&leg)[N], uint32_t hel,
+                                                 unsigned char* lds) {
+  const PairSpan<N - 1> ks(lds, (int)threadIdx.x, (int)blockDim.x);
+  double esum = 0.0;
+#pragma unroll
+  for (int t = 0; t < N; ++t) esum += fabs(p[t][0]);
+  const int ex = ilogb(0.5 * esum);
+  const double sc = ldexp(1.0, -ex);
+  cvp src[N - 1], e0;
+  auto share = [&](const cv4<double>& e) {
+    cvp s;
+    s.re[0] = ks.g ? e.re[3] : 0.0;
+    s.im[0] = 0.0;
+    s.re[1] = ks.g ? e.re[2] : e.re[1];
+    s.im[1] = ks.g ? e.im[2] : e.im[1];
+    return s;
+  };
+#pragma unroll
+  for (int t = 1; t < N; ++t) {
+    const double sg = leg[t] < 2u ? -sc : sc;
+    const double first = ks.g ? p[t][3] : p[t][0], second = ks.g ? p[t][2] : p[t][1];
+    ks.leg[(t - 1) * ks.lanes] = make_double2(ks.sg * (sg * first), -(sg * second));
+    src[t - 1] = share(polarisation<double>(p[t], (hel >> leg[t]) & 1u));
+  }
+  e0 = share(polarisation<double>(p[0], (hel >> leg[0]) & 1u));
+  double mr, mi;
+  bg_amplitude_p<N - 1>(ks, src, e0, mr, mi);
+  return rec_done(ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2)));
+}
+
+// FP64 on four lanes (QuadSpan: lane 16 c + e of the wave holds component c of event e); lds: the
+// wave's quad_lds_bytes<N - 1>().  Called by every lane of the wave.
+template <int N>
+__device__ __forceinline__ double ordered_amp2_q(const double (&p)[N][4], const uint32_t (&leg)[N], uint32_t hel,
+                                                 unsigned char* lds) {
+  const QuadSpan<N - 1> ks(lds, (int)(threadIdx.x & 63u));
+  double esum = 0.0;
+#pragma unroll
+  for (int t = 0; t < N; ++t) esum += fabs(p[t][0]);
+  const int ex = ilogb(0.5 * esum);
+  const double sc = ldexp(1.0, -ex);
+  cvq src[N - 1], e0;
+  auto share = [&](cv4<double> e) {
+    // (past a barrier: the compiler would branch on the component instead of selecting)
+#pragma unroll
+    for (int mu = 1; mu < 4; ++mu) opaque(e.re[mu]);
+    opaque(e.im[1]);
+    opaque(e.im[2]);
+    return cvq{ks.c == 1 ? e.re[1] : (ks.c == 2 ? e.re[2] : (ks.c == 3 ? e.re[3] : 0.0)),
+               ks.c == 1 ? e.im[1] : (ks.c == 2 ? e.im[2] : 0.0)};
+  };
+#pragma unroll
+  for (int t = 1; t < N; ++t) {
+    const double sg = leg[t] < 2u ? -sc : sc;
+    const double mine = ks.c < 2 ? (ks.c == 0 ? p[t][0] : p[t][1]) : (ks.c == 2 ? p[t][2] : p[t][3]);
+    ks.leg[(t - 1) * 64] = ks.sg * (sg * mine);
+    src[t - 1] = share(polarisation<double>(p[t], (hel >> leg[t]) & 1u));
+  }
+  e0 = share(polarisation<double>(p[0], (hel >> leg[0]) & 1u));
+  double mr, mi;
+  bg_amplitude_q<N - 1>(ks, src, e0, mr, mi);
   return rec_done(ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2)));
 }
 
@@ -875,29 +935,67 @@ __global__ __launch_bounds__((UseLdsK<N, T>::value ? kLdsLanes : 256))
   }
 }
 
-// Whether the grouped recursion of precision T reads its span momenta from the LDS table:
-// in FP32 it replaces FP64 sums and conversions at every use; in FP64, whose currents fill
-// the registers, the table's reads add to the scratch spill, so FP64 sums in registers.
+// Whether the grouped recursion of precision T reads its span momenta from the LDS table: in
+// FP32 it replaces FP64 sums and conversions at every use; FP64 groups keep legs and scalars
+// there instead.
 template <typename T>
 constexpr bool span_k_table() {
   return sizeof(T) == 4;
 }
 
-// Dynamic LDS of the grouped kernels for workgroups of `block` lanes: the span-momentum table
+// Dynamic LDS of the grouped kernels for workgroups of `block` lanes: the FP32 span-momentum
+// table, or the FP64 lane pair's legs and scalars
 template <int N, typename T, int G>
 constexpr int grouped_lds_bytes(int block) {
-  return span_k_table<T>() ? span_k_lds_bytes<N - 1, G, T>() * block : 0;
+  return span_k_table<T>() ? span_k_lds_bytes<N - 1, G, T>() * block
+                           : (G == 2 ? pair_lds_bytes<N - 1>() * block : quad_lds_bytes<N - 1>() * (block / 64));
+}
+
+// Waves per SIMD of the grouped kernels.  Four-lane FP64 runs two, which cover the latency of
+// the matrix sums and the LDS: at n = 12 that means 588 B of scratch per lane, but one wave
+// without scratch is slower (2^18 events: n = 11 731 -> 598 us, n = 12 1000 -> 868 us; n = 10 fits).
+// Elsewhere the currents take more than half the registers.
+template <typename T, int G>
+constexpr int group_waves() { return sizeof(T) == 8 && G == 4 ? 2 : 1; }
+
+// The event of a lane within its workgroup's blockDim.x / G, and the lane's place in its group:
+// adjacent lanes, or the matrix cores' columns for FP64 on four lanes.
+template <typename T, int G>
+__device__ __forceinline__ void group_place(int& event, int& g) {
+  if constexpr (G == 4 && sizeof(T) == 8) {
+    event = (int)(threadIdx.x >> 6) * 16 + (int)(threadIdx.x & 15u);
+    g = (int)(threadIdx.x >> 4) & 3;
+  } else {
+    event = (int)threadIdx.x / G;
+    g = (int)threadIdx.x % G;
+  }
+}
+
+// |A|^2 of an event on the G lanes of a group; gdyn: the workgroup's dynamic LDS.
+template <int N, typename T, int G>
+__device__ __forceinline__ double grouped_amp2(const double (&p)[N][4], const uint32_t (&leg)[N], uint32_t hel, int g,
+                                               unsigned char* gdyn) {
+  if constexpr (G == 2 && sizeof(T) == 8)
+    return ordered_amp2_p<N>(p, leg, hel, gdyn);
+  else if constexpr (G == 4 && sizeof(T) == 8)
+    return ordered_amp2_q<N>(p, leg, hel, gdyn + (threadIdx.x >> 6) * quad_lds_bytes<N - 1>());
+  else
+    return ordered_amp2_g<N, T, G, span_k_table<T>()>(p, leg, hel, g, reinterpret_cast<T*>(gdyn) + threadIdx.x,
+                                                      (int)blockDim.x);
 }
 
 // bg_amp2 with G lanes per event.  Dynamic LDS: grouped_lds_bytes.
 template <int N, typename T, int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_amp2_g(
+__global__ __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(group_waves<T, G>(), group_waves<T, G>()))) void k_amp2_g(
     int64_t count, const double* __restrict__ mom, const uint32_t* __restrict__ hel, const uint8_t* __restrict__ order,
     double* __restrict__ out) {
-  extern __shared__ unsigned char gdyn[];
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  const int g = (int)(threadIdx.x % G);
-  if (i >= count) return;
+  extern __shared__ __align__(16) unsigned char gdyn[];
+  int event, g;
+  group_place<T, G>(event, g);
+  // every lane runs the recursion (QuadSpan); those past the end repeat the last event
+  const int64_t ii = (int64_t)blockIdx.x * (blockDim.x / G) + event;
+  const int64_t i = ii < count ? ii : count - 1;
   double p[N][4];
   uint32_t leg[N];
 #pragma unroll
@@ -908,10 +1006,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) p[t][mu] = q[mu];
   }
-  const double a2 = ordered_amp2_g<N, T, G, span_k_table<T>()>(p, leg, hel[i], g,
-                                                               reinterpret_cast<T*>(gdyn) + threadIdx.x,
-                                                               (int)blockDim.x);
-  if (g == 0) out[i] = a2;
+  const double a2 = grouped_amp2<N, T, G>(p, leg, hel[i], g, gdyn);
+  if (g == 0 && ii < count) out[i] = a2;
 }
 
 }  // namespace bgk

@@ -156,12 +156,11 @@ __device__ __forceinline__ double rec_one(const GenClass& C, int64_t i, int64_t 
   return rec_staged<N, T, POL>(C, i, j, buf, s, tab);
 }
 
-// The same with the event on the G lanes of a group (the grouped recursion; span momenta
-// from this lane's column ktab of the workgroup's LDS table where span_k_table); lane g = 0
-// writes the outputs and returns w, the others return 0.
+// The same with the event on the G lanes of a group (grouped_amp2; gdyn: the workgroup's dynamic
+// LDS); with live, lane g = 0 writes the outputs and returns w, the others return 0.
 template <int N, typename T, int G>
 __device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t i, int64_t j, const double* __restrict__ buf,
-                                            int g, T* ktab, int lanes) {
+                                            int g, bool live, unsigned char* gdyn) {
   using L = SplitLayout<N>;
   const double shat = buf[L::at(j, L::kShat)];
   double pc[N][4];
@@ -177,8 +176,8 @@ __device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t i, int64_
   const EventWord<N> word{(uint64_t)__double_as_longlong(buf[L::at(j, L::kMeta)])};
   uint32_t leg[N];
   word.legs(leg);
-  const double a2 = ordered_amp2_g<N, T, G, span_k_table<T>()>(pc, leg, word.hel(), g, ktab, lanes);
-  if (g != 0) return 0.0;
+  const double a2 = grouped_amp2<N, T, G>(pc, leg, word.hel(), g, gdyn);
+  if (g != 0 || !live) return 0.0;
   return finish_staged<N>(C, i, j, buf, word.pass(), a2, shat);
 }
 
@@ -234,13 +233,17 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, re
 // blockDim.x / G; workgroup b writes the partial of its blockDim.x / G events at
 // first G / blockDim.x + b, as the one-kernel form numbers them.
 template <int N, typename T, int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_rec_g(
+__global__ __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(group_waves<T, G>(), group_waves<T, G>()))) void k_rec_g(
     GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials) {
-  extern __shared__ unsigned char gdyn[];
-  const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  const int g = (int)(threadIdx.x % G);
-  double w = 0.0;
-  if (j < cnt) w = rec_one_g<N, T, G>(C, first + j, j, buf, g, reinterpret_cast<T*>(gdyn) + threadIdx.x, (int)blockDim.x);
+  extern __shared__ __align__(16) unsigned char gdyn[];
+  int event, g;
+  group_place<T, G>(event, g);
+  // every lane runs the recursion (QuadSpan); those past the end repeat the last event
+  const int64_t jj = (int64_t)blockIdx.x * (blockDim.x / G) + event;
+  const bool live = jj < cnt;
+  const int64_t j = live ? jj : cnt - 1;
+  const double w = rec_one_g<N, T, G>(C, first + j, j, buf, g, live, gdyn);
   if (partials)
     block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0},
                        partials + 4 * (first * G / (int64_t)blockDim.x + (int64_t)blockIdx.x));

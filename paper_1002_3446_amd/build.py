@@ -84,17 +84,18 @@ def has_wtensor(n: int, p: int) -> bool:
 
 
 def unit_flags(n: int, p: int, k: int, f: int) -> list[str]:
-    """Extra compiler flags of one kernel unit.  The generation and bg_amp2 units of FP64 n = 9
-    (two lanes), n >= 10 with two lanes and n >= 11 with four are built without LLVM's pre-RA
-    machine scheduler: there the recursion fills the register file, and the scheduler's
-    reordering for latency raises register pressure, which costs more (scratch spill, AGPR
-    copies) than the latency it hides: four lanes, 2^18 events, n = 11 611 against 598 us, n = 12
-    1023 against 868 us; n = 10 keeps it, 420 against 430 us.  The one-lane recursions keep it
-    too: n = 8 FP32 5.55 (without) against 5.51 ms per 2^24 events, FP64 n = 7 bg_amp2 101
-    against 99 us per 5 10^5.  The four-lane units' matrix sums write vector registers: into
-    accumulation registers, as the compiler would place them, every sum costs two copies."""
+    """Extra compiler flags of one kernel unit.  The generation and bg_amp2 units whose recursion
+    fills the register file are built without LLVM's pre-RA machine scheduler: its reordering for
+    latency raises register pressure, which costs more (scratch spill, AGPR copies) than the
+    latency it hides.  With against without, us: two FP32 lanes, 5 10^5 events, n = 10 518 / 511,
+    n = 11 743 / 720, 10^6 events n = 12 2053 / 2012 (n = 9 373 / 372: keeps it); four FP64 lanes,
+    2^18 events, n = 11 611 / 598, n = 12 1023 / 868 (n = 10 420 / 430: keeps it); two FP64 lanes
+    from n = 9.  The one-lane recursions and the gradients keep it too: n = 8 FP32 5.51 / 5.55 ms
+    per 2^24 events, FP64 n = 7 bg_amp2 99 / 101 per 5 10^5, gradient n = 8 FP32 2169 / 2192.
+    The four-lane units' matrix sums write vector registers: into accumulation registers, as the
+    compiler would place them, every sum costs two copies."""
     flags = []
-    if k < 2 and p == 64 and (f == 2 and n >= 9 or f == 5 and n >= 11):
+    if k < 2 and (p == 64 and (f == 2 and n >= 9 or f == 5 and n >= 11) or p == 32 and f == 2 and n >= 10):
         flags += ["-mllvm", "-enable-misched=0"]
     if k < 2 and p == 64 and f == 5:
         flags += ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]

@@ -237,27 +237,28 @@ __device__ __forceinline__ void bg_reverse(const double (&k)[L][4], const cv4<T>
   static_for<0, L>([&](auto tc) { srcb[decltype(tc)::value] = Jb[decltype(tc)::value]; });
 }
 
-// Adjoint of polarisation(): accumulates dL/dp (spatial components) from eb.
-template <typename T>
-__device__ __forceinline__ void polarisation_adj(const double p[4], bool plus, const cv4<T>& eb, double pb[4]) {
+// Adjoint of polarisation(): accumulates dL/dp (spatial components) from the adjoints of the
+// source's words that are not identically zero (re[1..3], im[1], im[2]).  With the unit vectors
+// along and across the polar angle, t = (ct cf, ct sf, -st) and f = (-sf, cf, 0):
+//   d(ct) = -st (t.dp) / |p|,  d(st) = ct (t.dp) / |p|,  d(cf) = -sf (f.dp) / pT,  d(sf) = cf (f.dp) / pT.
+// (Written with two reciprocal roots; a division per term took 14 divisions a leg, a quarter of
+// the second gradient kernel.)
+__device__ __forceinline__ void polarisation_adj(const double p[4], bool plus, const double (&er)[4],
+                                                 const double (&ei)[4], double pb[4]) {
   const double px = p[1], py = p[2], pz = p[3];
   const double pt2 = px * px + py * py;
   if (!(pt2 > 0.0)) return;  // a leg along the beam axis: its direction is fixed
-  const double pa = sqrt(pt2 + pz * pz), pt = sqrt(pt2);
-  const double ct = pz / pa, cf = px / pt, sf = py / pt;
-  const double r = 0.70710678118654752440;
-  const double hs = plus ? 1.0 : -1.0;
-  const double e1r = double(eb.re[1]), e1i = double(eb.im[1]);
-  const double e2r = double(eb.re[2]), e2i = double(eb.im[2]);
-  const double e3r = double(eb.re[3]);
-  const double ctb = -hs * r * (cf * e1r + sf * e2r);
-  const double stb = hs * r * e3r;
-  const double cfb = -hs * r * ct * e1r - r * e2i;
-  const double sfb = r * e1i - hs * r * ct * e2r;
-  const double pa3 = pa * pa * pa, pt3 = pt2 * pt;
-  pb[1] += ctb * (-pz * px / pa3) + stb * (px * pz * pz / (pt * pa3)) + cfb * (py * py / pt3) + sfb * (-px * py / pt3);
-  pb[2] += ctb * (-pz * py / pa3) + stb * (py * pz * pz / (pt * pa3)) + cfb * (-px * py / pt3) + sfb * (px * px / pt3);
-  pb[3] += ctb * (pt2 / pa3) + stb * (-pt * pz / pa3);
+  const double ipa = rsqrt_fp64(pt2 + pz * pz), ipt = rsqrt_fp64(pt2);
+  const double ct = pz * ipa, st = (pt2 * ipt) * ipa, cf = px * ipt, sf = py * ipt;
+  const double r = 0.70710678118654752440, hr = plus ? r : -r;
+  const double ctb = -hr * (cf * er[1] + sf * er[2]);
+  const double stb = hr * er[3];
+  const double cfb = -hr * ct * er[1] - r * ei[2];
+  const double sfb = r * ei[1] - hr * ct * er[2];
+  const double tb = (stb * ct - ctb * st) * ipa, fb = (sfb * cf - cfb * sf) * ipt;
+  pb[1] += tb * (ct * cf) - fb * sf;
+  pb[2] += tb * (ct * sf) + fb * cf;
+  pb[3] -= tb * st;
 }
 
 struct RamboMapAdj {
@@ -300,39 +301,35 @@ __device__ __forceinline__ void rambo_apply_adj(const RamboMap& m, const double 
 // Adjoint of RamboMap::init: accumulates dL/dQ and dL/dsqrt(s_hat).
 __device__ __forceinline__ void rambo_init_adj(const RamboMap& m, const double Q[4], const RamboMapAdj& A,
                                                double Qb[4], double& sb) {
-  const double Mv = sqrt(Q[0] * Q[0] - Q[1] * Q[1] - Q[2] * Q[2] - Q[3] * Q[3]);
-  sb += A.Xb / Mv;
-  double Mb = -A.Xb * m.X / Mv;
+  const double iM = m.iM;
+  sb += A.Xb * iM;
+  double Mb = -A.Xb * m.X * iM;
   const double gammab = A.gammab - A.ab * m.a * m.a;
-  Qb[0] += gammab / Mv;
-  Mb += -gammab * m.gamma / Mv;
+  Qb[0] += gammab * iM;
+  Mb += -gammab * m.gamma * iM;
   const double b[3] = {m.bx, m.by, m.bz};
   const double bb[3] = {A.bxb, A.byb, A.bzb};
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    Qb[j + 1] += -bb[j] / Mv;
-    Mb += -bb[j] * b[j] / Mv;
+    Qb[j + 1] += -bb[j] * iM;
+    Mb += -bb[j] * b[j] * iM;
   }
-  const double M2b = Mb / (2.0 * Mv);
+  const double M2b = 0.5 * Mb * iM;
   Qb[0] += 2.0 * Q[0] * M2b;
 #pragma unroll
   for (int j = 0; j < 3; ++j) Qb[j + 1] += -2.0 * Q[j + 1] * M2b;
 }
 
-// Adjoint of rambo_q: rho adjoints from q adjoints.
-__device__ __forceinline__ void rambo_q_adj(double r1, double r2, double r3, double r4, const double qb[4],
+// Adjoint of rambo_q: rho adjoints from q and its adjoints, without the angles (q holds them):
+// d q / d phi = (0, -q2, q1, 0), d q / d c = q0 (0, -c cos phi / st, -c sin phi / st, 1), q / q0 for
+// d q / d q0, and st^2 = 1 - c^2.
+__device__ __forceinline__ void rambo_q_adj(double r1, double r3, double r4, const double q[4], const double qb[4],
                                             double rb[4]) {
   const double c = 2.0 * r1 - 1.0;
-  const double st = sqrt(1.0 - c * c);
-  double sp, cp;
-  sincospi_fp64(2.0 * r2, &sp, &cp);
-  const double q0 = -log_fp64(r3 * r4);
-  const double q0b = qb[0] + qb[1] * st * cp + qb[2] * st * sp + qb[3] * c;
-  const double stb = q0 * (qb[1] * cp + qb[2] * sp);
-  const double cpb = q0 * st * qb[1], spb = q0 * st * qb[2];
-  const double cb = q0 * qb[3] - stb * c / st;
-  rb[0] = 2.0 * cb;
-  rb[1] = 2.0 * 3.14159265358979323846 * (cp * spb - sp * cpb);
+  const double across = q[1] * qb[1] + q[2] * qb[2];
+  const double q0b = qb[0] + (across + q[3] * qb[3]) / q[0];
+  rb[0] = 2.0 * (q[0] * qb[3] - across * c / (1.0 - c * c));
+  rb[1] = 2.0 * 3.14159265358979323846 * (q[1] * qb[2] - q[2] * qb[1]);
   rb[2] = -q0b / r3;
   rb[3] = -q0b / r4;
 }
@@ -449,7 +446,7 @@ __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const Gr
       double qbt[4], rb[4];
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) qbt[mu] = qb[t][mu] + Qb[mu];
-      rambo_q_adj(u[0], u[1], u[2], u[3], qbt, rb);
+      rambo_q_adj(u[0], u[2], u[3], K.q[t], qbt, rb);
       double* o = gu + pidx * 4;
       o[0] = gw * rb[0]; o[1] = gw * rb[1]; o[2] = gw * rb[2]; o[3] = gw * rb[3];
     }
@@ -467,13 +464,18 @@ __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const Gr
 // The recursion's adjoints go to the second kernel (k_grad_back), which takes them through
 // the helicity sources, the momentum scaling, RAMBO and x1, x2: kept in one kernel, those
 // values stay live across the reverse sweep and spill to scratch.  Per position t = 1..N-1
-// twelve words: the contravariant adjoint of the scaled recursion momentum (4), then the
-// source adjoint's real (4) and imaginary (4) parts; then a flag (0: |A|^2 = 0, nothing to
-// do).  Layout [word][event], so neighbouring lanes write neighbouring words.
+// nine words in the recursion's precision: the contravariant adjoint of the scaled recursion
+// momentum (4), then the adjoints of the source's words that are not identically zero, re[1..3],
+// im[1], im[2]; then a flag (0: |A|^2 = 0, nothing to do).  Layout [word][event], so
+// neighbouring lanes write neighbouring words.  (All eight source words in FP64 took 680 B an
+// event at n = 8 instead of 256, which bounded the second kernel.)
 template <int N>
 struct GradRaw {
-  static constexpr int words = 12 * (N - 1) + 1;
-  __host__ __device__ static constexpr int at(int t, int w) { return 12 * (t - 1) + w; }
+  static constexpr int words = grad_words(N), kFlag = words - 1;
+  __host__ __device__ static constexpr int at(int t, int w) { return 9 * (t - 1) + w; }
+  // word of the source adjoint's component mu, -1 where the source is zero
+  __host__ __device__ static constexpr int re(int mu) { return mu == 0 ? -1 : 3 + mu; }
+  __host__ __device__ static constexpr int im(int mu) { return mu == 1 || mu == 2 ? 6 + mu : -1; }
 };
 
 // One event per lane: forward (CM momenta, recursion), log w_int, reverse sweep, momentum
@@ -509,25 +511,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   T mr, mi;
   cdot(e0, V, mr, mi);
   const double m2 = double(mr) * double(mr) + double(mi) * double(mi);
+  using R = GradRaw<N>;
+  T* o = static_cast<T*>(G.pbuf) + i;
   if (!grad_logw<N>(G, i, K, m2, true)) {
-    G.pbuf[(GradRaw<N>::words - 1) * G.count + i] = 0.0;  // nothing for the second kernel
+    o[R::kFlag * G.count] = T(0);  // nothing for the second kernel
     return;
   }
   // reverse sweep: d log|m|^2 / dm = 2 m / |m|^2
   cv4<T> srcb[L], e0b;
   T kb[L][4];
   bg_reverse<L, T>(k, J, Sr, Si, e0, V, T(2.0 * double(mr) / m2), T(2.0 * double(mi) / m2), srcb, e0b, kb);
-  double* o = G.pbuf + i;
 #pragma unroll
   for (int t = 1; t < N; ++t) {
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
-      o[GradRaw<N>::at(t, mu) * G.count] = double(kb[t - 1][mu]);
-      o[GradRaw<N>::at(t, 4 + mu) * G.count] = double(srcb[t - 1].re[mu]);
-      o[GradRaw<N>::at(t, 8 + mu) * G.count] = double(srcb[t - 1].im[mu]);
+      o[R::at(t, mu) * G.count] = kb[t - 1][mu];
+      if (R::re(mu) >= 0) o[R::at(t, R::re(mu)) * G.count] = srcb[t - 1].re[mu];
+      if (R::im(mu) >= 0) o[R::at(t, R::im(mu)) * G.count] = srcb[t - 1].im[mu];
     }
   }
-  o[(GradRaw<N>::words - 1) * G.count] = 1.0;
+  o[R::kFlag * G.count] = T(1);
 }
 
 // Whether the gradient kernel keeps its span scalars distributed over the lanes of a group:
@@ -540,7 +543,9 @@ constexpr bool grad_dist_scalars() {
 // GL lanes per event (the grouped recursion and its reverse sweep, bg_group_adj.hpp); every
 // lane evaluates the kinematics, lane g writes its components of the raw adjoints.  The
 // forward values pass an optimisation barrier before the sweep, so the compiler does not keep
-// the forward pass's intermediates live across it.  Workgroups of 256 lanes.
+// the forward pass's intermediates live across it.  Workgroups of 256 lanes, with
+// SpanKGroupLds::kBytes of dynamic LDS per lane.  Bound by VALU issue at one wave per SIMD (87% at
+// n = 8: 20892 instructions a wave).
 template <int N, typename T, int GL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_grad_g(GradArgs G) {
   constexpr int L = N - 1, C = 4 / GL;
@@ -575,7 +580,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       e0.im[c] = ls.template pick<true>(e.im, c);
     }
   }
-  SpanKGroup<L, GL, T, true> ks{k, lsd.sg};
+  extern __shared__ __align__(16) unsigned char gdyn[];  // SpanKGroupLds::kBytes per lane
+  const SpanKGroupLds<L, GL, T> ks(k, lsd.sg, gdyn, (int)threadIdx.x, (int)blockDim.x);
   cvl<T, C> J[SP::count];
   SS S(g);
   cvl<T, C> V;
@@ -583,8 +589,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   T mr, mi;
   cdot_g<GL>(ls, e0, V, mr, mi);
   const double m2 = double(mr) * double(mr) + double(mi) * double(mi);
+  using R = GradRaw<N>;
+  T* o = static_cast<T*>(G.pbuf) + i;
   if (!grad_logw<N>(G, i, K, m2, g == 0)) {
-    if (g == 0) G.pbuf[(GradRaw<N>::words - 1) * G.count + i] = 0.0;  // nothing for the second kernel
+    if (g == 0) o[R::kFlag * G.count] = T(0);  // nothing for the second kernel
     return;
   }
   static_for<0, SP::count>([&](auto sc) {
@@ -608,30 +616,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   cvl<T, C> srcb[L], e0b;
   T kb[L][C];
   bg_reverse_g<L, GL, T>(ls, ks, J, S, e0, V, T(2.0 * double(mr) / m2), T(2.0 * double(mi) / m2), srcb, e0b, kb);
-  // this lane's components of the raw adjoints (contravariant momentum adjoints)
-  double* o = G.pbuf + i;
+  // this lane's components of the raw adjoints (contravariant momentum adjoints), past an
+  // optimisation barrier: the compiler sinks the sweep into the branches of the stores otherwise
+  // (6 KB of scratch per lane at n = 8)
 #pragma unroll
-  for (int t = 1; t < N; ++t) {
+  for (int t = 0; t < L; ++t) {
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const int mu = g * C + c;
-      o[GradRaw<N>::at(t, mu) * G.count] = double(ls.sg[c] * kb[t - 1][c]);
-      o[GradRaw<N>::at(t, 4 + mu) * G.count] = double(srcb[t - 1].re[c]);
-      o[GradRaw<N>::at(t, 8 + mu) * G.count] = double(srcb[t - 1].im[c]);
+      opaque(kb[t][c]);
+      opaque(srcb[t].re[c]);
+      opaque(srcb[t].im[c]);
     }
   }
-  if (g == 0) o[(GradRaw<N>::words - 1) * G.count] = 1.0;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int mu = g * C + c;
+#pragma unroll
+    for (int t = 1; t < N; ++t) o[R::at(t, mu) * G.count] = ls.sg[c] * kb[t - 1][c];
+    if (mu >= 1) {
+#pragma unroll
+      for (int t = 1; t < N; ++t) o[R::at(t, 3 + mu) * G.count] = srcb[t - 1].re[c];
+    }
+    if (mu == 1 || mu == 2) {
+#pragma unroll
+      for (int t = 1; t < N; ++t) o[R::at(t, 6 + mu) * G.count] = srcb[t - 1].im[c];
+    }
+  }
+  if (g == 0) o[R::kFlag * G.count] = T(1);
 }
 
 // Second gradient kernel (one lane per event): from the recursion's adjoints that k_grad or
 // k_grad_g left in pbuf, the helicity sources' and momenta's adjoints (CM frame), RAMBO's
-// conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were completed by the first.
-template <int N>
+// conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were completed by the first.  Bound by
+// the draws' and their adjoints' rows (a lane's words lie together, 192 B at n = 8) and the FP64
+// chains at two waves per SIMD: 5141 -> 2731 instructions and 680 -> 256 B of adjoints an event,
+// n = 8 FP32 442 -> 332 us per 2^20 events, n = 6 FP64 46 -> 39 per 2 10^5.
+template <int N, typename T>
 __global__ __launch_bounds__(256) void k_grad_back(GradArgs G) {
+  using R = GradRaw<N>;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= G.count) return;
-  const double* o = G.pbuf + i;
-  if (o[(GradRaw<N>::words - 1) * G.count] == 0.0) return;
+  const T* __restrict__ o = static_cast<const T*>(G.pbuf) + i;
+  if (o[R::kFlag * G.count] == T(0)) return;
   GradKin<N> K;
   grad_front<N>(G, i, K);
   double pb[N][4];
@@ -642,15 +668,15 @@ __global__ __launch_bounds__(256) void k_grad_back(GradArgs G) {
   for (int t = 1; t < N; ++t) {
     const double sg = K.leg[t] < 2u ? -K.sc : K.sc;
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) pb[t][mu] = sg * o[GradRaw<N>::at(t, mu) * G.count];
+    for (int mu = 0; mu < 4; ++mu) pb[t][mu] = sg * (double)o[R::at(t, mu) * G.count];
     if (K.leg[t] >= 2u) {
-      cv4<double> eb;
+      double er[4] = {0.0, 0.0, 0.0, 0.0}, ei[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int mu = 0; mu < 4; ++mu) {
-        eb.re[mu] = o[GradRaw<N>::at(t, 4 + mu) * G.count];
-        eb.im[mu] = o[GradRaw<N>::at(t, 8 + mu) * G.count];
+      for (int mu = 1; mu < 4; ++mu) {
+        er[mu] = (double)o[R::at(t, R::re(mu)) * G.count];
+        if (R::im(mu) >= 0) ei[mu] = (double)o[R::at(t, R::im(mu)) * G.count];
       }
-      polarisation_adj<double>(K.pc[t], (K.hel >> K.leg[t]) & 1u, eb, pb[t]);
+      polarisation_adj(K.pc[t], (K.hel >> K.leg[t]) & 1u, er, ei, pb[t]);
     } else {
       rsb += 0.5 * (pb[t][0] - pb[t][3]);  // leg 1: p = (rs/2)(1, 0, 0, -1)
     }

@@ -1087,9 +1087,9 @@ int bg_amp2_grad(const bg_config* cfg, int64_t N, const double* uniforms, const 
   G.log_const = log_weight_const(cfg->n, cfg->alpha_s);
   hipStream_t s = (hipStream_t)stream;
   Workspace ws{nullptr, s};
-  // the recursion's adjoints between the two gradient kernels: 12 (n - 1) + 1 words per event
-  if (int st = ws.alloc((size_t)N * (12 * (cfg->n - 1) + 1) * sizeof(double)); st != BG_OK) return st;
-  G.pbuf = ws.d();
+  // the recursion's adjoints between the two gradient kernels
+  if (int st = ws.alloc((size_t)N * grad_words(cfg->n) * (cfg->prec / 8)); st != BG_OK) return st;
+  G.pbuf = ws.p;
   const Shape sh = shape_of(cfg->n, cfg->prec);
   return from_hip(L->grad(G, sh.block, s));
 }

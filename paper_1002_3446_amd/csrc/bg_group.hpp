@@ -60,7 +60,7 @@ struct LaneShare {
   T sg[C];     // sigma of each held component
   __device__ __forceinline__ explicit LaneShare(int g) : mu0(g * C) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) sg[c] = (mu0 + c == 0) ? T(1) : T(-1);
+    for (int c = 0; c < C; ++c) sg[c] = c == 0 && mu0 == 0 ? T(1) : T(-1);  // only the first varies
   }
   // the held components of a full four-vector, without dynamic register indexing: one select
   // for two lanes in the forward kernels; bit masks for four lanes, and for two in the
@@ -103,8 +103,8 @@ __device__ __forceinline__ T group_bcast(T x) {
 }
 
 // Whether a group keeps its span scalars distributed over its lanes: where the currents of
-// every span already take most of a lane's registers (FP32 n = 12 with two lanes, FP64 from
-// n = 9), replicating the scalars on every lane would spill.
+// every span already take most of a lane's registers (FP32 n = 12 with two lanes), replicating
+// the scalars on every lane would spill.
 template <int L, int G, typename T>
 constexpr bool dist_scalars() {
   return G > 1 && Spans<L>::count * 2 * (4 / G) * (int)(sizeof(T) / 4) > 240;
@@ -206,84 +206,66 @@ __device__ __forceinline__ void caxpy_l(T cr, T ci, const cvl<T, C>& y, cvl<T, C
   }
 }
 
-// Covariant span momenta of this lane's components, summed left to right in FP64 over the
-// legs and cast to T; propagators 1/K^2 from the group sum of FP64 partials.
-template <int L, int G, typename T, bool AFRESH = false>
-struct SpanKGroup {
-  static constexpr int C = 4 / G;
-  const double (&k)[L][C];   // covariant FP64 leg components held by this lane
-  const double (&sg)[C];     // their metric signs
-  // With AFRESH, every use sums afresh: an optimisation barrier on the first term keeps the
-  // compiler from merging the sums of one span over the whole kernel and holding them in
-  // registers (the gradient kernels, which hold currents and adjoints, gain registers).
-  template <int A, int B>
-  __device__ __forceinline__ void sum(double d[C]) const {
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      d[c] = k[A][c];
-      if constexpr (AFRESH) opaque(d[c]);
-    }
-    static_for<A + 1, B + 1>([&](auto t) {
-#pragma unroll
-      for (int c = 0; c < C; ++c) d[c] += k[decltype(t)::value][c];
-    });
-  }
-  template <int A, int B>
-  __device__ __forceinline__ void K(T (&out)[C]) const {
-    double d[C];
-    sum<A, B>(d);
-#pragma unroll
-    for (int c = 0; c < C; ++c) out[c] = T(d[c]);
-  }
-  template <int A, int B>
-  __device__ __forceinline__ T prop() const {
-    double d[C];
-    sum<A, B>(d);
-    double part;
-    {
-#pragma clang fp contract(off)
-      part = sg[0] * (d[0] * d[0]);
-#pragma unroll
-      for (int c = 1; c < C; ++c) part = part + sg[c] * (d[c] * d[c]);
-    }
-    const double k2 = group_sum<G>(part);
-    if constexpr (std::is_same<T, float>::value)
-      return __builtin_amdgcn_rcpf(float(k2));
-    else
-      return 1.0 / k2;
-  }
-};
-
-// The same span momenta read from a per-workgroup LDS table filled once per event: for every
-// span of 2..L-1 legs this lane's covariant components, summed left to right in FP64 over
-// its legs and cast to T (bitwise the values SpanKGroup forms at each use), layout
-// [span][component][lane] so that a wave's reads are contiguous.  Single legs and the
-// propagators still come from the FP64 leg momenta.  One table read replaces the FP64 sums
-// and conversions at every use, and nothing of the sums stays live in registers.
+// Covariant span momenta and propagators, read from a per-workgroup LDS table filled once per
+// event: for every span of 2..L-1 legs this lane's components, summed left to right in FP64 over
+// its legs and cast to T, and 1/K^2 from the group sum of the FP64 partials.  Layout [span][lane]
+// of C components, so that a wave's reads are contiguous, then the propagators, one per group: G
+// spans to a row.  One table read replaces the FP64 sums and conversions at every use, and nothing
+// of them stays live in registers but the legs in T.  (The propagators too: formed at their use
+// they keep the FP64 legs live.  Without / with, and with the unit's scheduler choice: FP32
+// n = 12 2.09 / 2.01 ms per 2^20 events; the gradient's n = 8 kernel, where the sums were formed
+// at every use, 1730 / 1517 us per 2^20.)
 template <int L, int G, typename T>
-struct SpanKGroupLds : SpanKGroup<L, G, T> {
-  using Base = SpanKGroup<L, G, T>;
-  static constexpr int C = Base::C;
+struct SpanKGroupLds {
+  static constexpr int C = 4 / G;
   static constexpr int kSpans = Spans<L>::count - L - 1;  // spans of 2..L-1 legs
-  T* kt;      // &table[0][0][lane]
-  int lanes;  // lanes per workgroup (the table's row stride)
-  __device__ __forceinline__ SpanKGroupLds(const double (&k_)[L][C], const double (&sg_)[C], T* kt_, int lanes_)
-      : Base{k_, sg_}, kt(kt_), lanes(lanes_) {}
-  __device__ __forceinline__ void fill() const {
+  static constexpr int kBytes = kSpans * C * (int)sizeof(T) + (kSpans + G - 1) / G * (int)sizeof(T);  // per lane
+  struct alignas(C * sizeof(T)) Row {
+    T v[C];
+  };
+  Row* kt;    // &table[0][lane]
+  T* pt;      // &props[0][first lane of the group]
+  int lanes;  // lanes per workgroup (the row stride)
+  T leg[L][C];
+  __device__ __forceinline__ SpanKGroupLds(const double (&k)[L][C], const double (&sg)[C], unsigned char* lds, int lane,
+                                           int lanes_)
+      : kt(reinterpret_cast<Row*>(lds) + lane),
+        pt(reinterpret_cast<T*>(reinterpret_cast<Row*>(lds) + kSpans * lanes_) + (lane - lane % G)),
+        lanes(lanes_) {
     using SP = Spans<L>;
-    static_for<0, L - 1>([&](auto ac) {
+    static_for<0, L>([&](auto ac) {
       constexpr int a = decltype(ac)::value;
       double acc[C];
 #pragma unroll
-      for (int c = 0; c < C; ++c) acc[c] = this->k[a][c];
+      for (int c = 0; c < C; ++c) {
+        acc[c] = k[a][c];
+        leg[a][c] = T(acc[c]);
+      }
       static_for<a + 1, L>([&](auto bc) {
         constexpr int b = decltype(bc)::value;
-#pragma unroll
-        for (int c = 0; c < C; ++c) acc[c] += this->k[b][c];
         if constexpr (b - a + 1 < L) {
           constexpr int q = SP::at(a, b) - L;
+          Row r;
 #pragma unroll
-          for (int c = 0; c < C; ++c) kt[(q * C + c) * lanes] = T(acc[c]);
+          for (int c = 0; c < C; ++c) {
+            acc[c] += k[b][c];
+            r.v[c] = T(acc[c]);
+          }
+          kt[q * lanes] = r;
+          double part;
+          {
+#pragma clang fp contract(off)
+            part = sg[0] * (acc[0] * acc[0]);
+#pragma unroll
+            for (int c = 1; c < C; ++c) part = part + sg[c] * (acc[c] * acc[c]);
+          }
+          const double k2 = group_sum<G>(part);
+          T prop;
+          if constexpr (std::is_same<T, float>::value)
+            prop = __builtin_amdgcn_rcpf(float(k2));
+          else
+            prop = 1.0 / k2;
+          pt[q / G * lanes + q % G] = prop;  // every lane of the group writes the same
         }
       });
     });
@@ -294,21 +276,21 @@ struct SpanKGroupLds : SpanKGroup<L, G, T> {
   __device__ __forceinline__ void K(T (&out)[C]) const {
     if constexpr (A == B) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) out[c] = T(this->k[A][c]);
+      for (int c = 0; c < C; ++c) out[c] = leg[A][c];
     } else {
       constexpr int q = Spans<L>::at(A, B) - L;
       static_assert(q >= 0 && q < kSpans, "span of 2..L-1 legs");
+      const Row r = kt[q * lanes];
 #pragma unroll
-      for (int c = 0; c < C; ++c) out[c] = kt[(q * C + c) * lanes];
+      for (int c = 0; c < C; ++c) out[c] = r.v[c];
     }
   }
+  template <int A, int B>
+  __device__ __forceinline__ T prop() const {
+    constexpr int q = Spans<L>::at(A, B) - L;
+    return pt[q / G * lanes + q % G];
+  }
 };
-
-// LDS bytes per lane of SpanKGroupLds
-template <int L, int G, typename T>
-constexpr int span_k_lds_bytes() {
-  return SpanKGroupLds<L, G, T>::kSpans * (4 / G) * (int)sizeof(T);
-}
 
 // One span [A..B]: its bracket sum V (contravariant, this lane's components).
 template <int L, int A, int B, int G, typename T, typename KS, typename SS>

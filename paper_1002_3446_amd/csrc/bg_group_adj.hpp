@@ -219,17 +219,4 @@ __device__ __forceinline__ void bg_reverse_g(const LaneShare<G, T>& ls, const KS
   static_for<0, L>([&](auto tc) { srcb[decltype(tc)::value] = Jb[decltype(tc)::value]; });
 }
 
-// The full four-vector from the lanes' shares (G = 2): own components and the partner's.
-template <typename U>
-__device__ __forceinline__ void gather_pair(int g, const U (&own)[2], U (&full)[4]) {
-  U other[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) other[c] = dpp_mov<kDppSwap1>(own[c]);
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    full[c] = g == 0 ? own[c] : other[c];
-    full[2 + c] = g == 0 ? other[c] : own[c];
-  }
-}
-
 }  // namespace bgk

@@ -136,9 +136,10 @@ hipError_t BG_NAME(launch_grad_n, BG_N, BG_PREC, BG_KIND)(const GradArgs& G, int
   } else {
     (void)block;
     const int64_t nb = (GL * G.count + 255) / 256;
-    hipLaunchKernelGGL((k_grad_g<BG_N, Real, GL>), dim3((unsigned)nb), dim3(256), 0, s, G);
+    hipLaunchKernelGGL((k_grad_g<BG_N, Real, GL>), dim3((unsigned)nb), dim3(256),
+                       (SpanKGroupLds<BG_N - 1, GL, Real>::kBytes * 256), s, G);
   }
-  hipLaunchKernelGGL((k_grad_back<BG_N>), dim3((unsigned)((G.count + 255) / 256)), dim3(256), 0, s, G);
+  hipLaunchKernelGGL((k_grad_back<BG_N, Real>), dim3((unsigned)((G.count + 255) / 256)), dim3(256), 0, s, G);
   return hipGetLastError();
 }
 #else

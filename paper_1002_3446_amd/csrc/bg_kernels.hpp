@@ -630,12 +630,11 @@ __device__ __forceinline__ double ordered_amp2_real(const double (&p)[N][4], con
 }
 
 // The same with the event spread over the G lanes of a group (FP32; FP64 groups:
-// ordered_amp2_p, ordered_amp2_q); g is this lane's place in it.  With ktab (this lane's column
-// of a workgroup table of span_k_lds_bytes per lane, row stride `lanes`), the span momenta come
-// from LDS (SpanKGroupLds), else from registers.
-template <int N, typename T, int G, bool KLDS = false>
+// ordered_amp2_p, ordered_amp2_q); g is this lane's place in it.  The span momenta and propagators
+// come from the workgroup's table lds (SpanKGroupLds).
+template <int N, typename T, int G>
 __device__ __forceinline__ double ordered_amp2_g(const double (&p)[N][4], const uint32_t (&leg)[N], uint32_t hel,
-                                                 int g, T* ktab = nullptr, int lanes = 0) {
+                                                 int g, unsigned char* lds) {
   constexpr int C = 4 / G;
   double esum = 0.0;
 #pragma unroll
@@ -667,14 +666,8 @@ __device__ __forceinline__ double ordered_amp2_g(const double (&p)[N][4], const 
     }
   }
   double mr, mi;
-  if constexpr (KLDS) {
-    const SpanKGroupLds<N - 1, G, T> ks(k, lsd.sg, ktab, lanes);
-    ks.fill();
-    bg_amplitude_g<N - 1, G, T>(ls, ks, src, e0, mr, mi);
-  } else {
-    const SpanKGroup<N - 1, G, T> ks{k, lsd.sg};
-    bg_amplitude_g<N - 1, G, T>(ls, ks, src, e0, mr, mi);
-  }
+  const SpanKGroupLds<N - 1, G, T> ks(k, lsd.sg, lds, (int)threadIdx.x, (int)blockDim.x);
+  bg_amplitude_g<N - 1, G, T>(ls, ks, src, e0, mr, mi);
   return rec_done(ldexp(__builtin_fma(mr, mr, mi * mi), 2 * ex * (4 - N) - (N - 2)));
 }
 
@@ -828,7 +821,7 @@ __device__ __forceinline__ double finish_event(const GenClass& C, int64_t i, boo
 // values), the recursion is shared, and lane g = 0 writes the outputs and returns w
 // (the others return 0).
 // With LDS (one lane) the recursion uses the workgroup's table tab, which may lie over the memory
-// of perm: the kinematics are done with it by then.
+// of perm: the kinematics are done with it by then.  With G > 1, tab holds SpanKGroupLds.
 template <int N, typename T, int G = 1, int POL = 0, bool LDS = false>
 __device__ __forceinline__ double generate_one(const GenClass& C, int64_t i, PermLds perm, int g = 0,
                                                RecLds<N, T>* tab = nullptr) {
@@ -859,7 +852,7 @@ __device__ __forceinline__ double generate_one(const GenClass& C, int64_t i, Per
   } else if constexpr (G == 1) {
     a2 = ordered_amp2<N, T, LDS>(ev.pc, ev.leg, ev.hel, tab);
   } else {
-    a2 = ordered_amp2_g<N, T, G, false>(ev.pc, ev.leg, ev.hel, g);
+    a2 = ordered_amp2_g<N, T, G>(ev.pc, ev.leg, ev.hel, g, reinterpret_cast<unsigned char*>(tab));
   }
   if (g != 0) return 0.0;
   return finish_event<N>(C, i, pass, a2, ev.shat, ev.x1, ev.x2, r);
@@ -935,20 +928,12 @@ __global__ __launch_bounds__((UseLdsK<N, T>::value ? kLdsLanes : 256))
   }
 }
 
-// Whether the grouped recursion of precision T reads its span momenta from the LDS table: in
-// FP32 it replaces FP64 sums and conversions at every use; FP64 groups keep legs and scalars
-// there instead.
-template <typename T>
-constexpr bool span_k_table() {
-  return sizeof(T) == 4;
-}
-
 // Dynamic LDS of the grouped kernels for workgroups of `block` lanes: the FP32 span-momentum
 // table, or the FP64 lane pair's legs and scalars
 template <int N, typename T, int G>
 constexpr int grouped_lds_bytes(int block) {
-  return span_k_table<T>() ? span_k_lds_bytes<N - 1, G, T>() * block
-                           : (G == 2 ? pair_lds_bytes<N - 1>() * block : quad_lds_bytes<N - 1>() * (block / 64));
+  return sizeof(T) == 4 ? SpanKGroupLds<N - 1, G, T>::kBytes * block
+                        : (G == 2 ? pair_lds_bytes<N - 1>() * block : quad_lds_bytes<N - 1>() * (block / 64));
 }
 
 // Waves per SIMD of the grouped kernels.  Four-lane FP64 runs two, which cover the latency of
@@ -980,8 +965,7 @@ __device__ __forceinline__ double grouped_amp2(const double (&p)[N][4], const ui
   else if constexpr (G == 4 && sizeof(T) == 8)
     return ordered_amp2_q<N>(p, leg, hel, gdyn + (threadIdx.x >> 6) * quad_lds_bytes<N - 1>());
   else
-    return ordered_amp2_g<N, T, G, span_k_table<T>()>(p, leg, hel, g, reinterpret_cast<T*>(gdyn) + threadIdx.x,
-                                                      (int)blockDim.x);
+    return ordered_amp2_g<N, T, G>(p, leg, hel, g, gdyn);
 }
 
 // bg_amp2 with G lanes per event.  Dynamic LDS: grouped_lds_bytes.

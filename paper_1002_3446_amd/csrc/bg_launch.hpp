@@ -60,6 +60,9 @@ constexpr int grad_lanes(int n, int prec) {
   return prec == 32 ? (n <= 5 ? 1 : (n <= 8 ? 2 : 4)) : (n <= 4 ? 1 : (n <= 6 ? 2 : 4));
 }
 
+// Words per event between the two gradient kernels (GradRaw).
+constexpr int grad_words(int n) { return 9 * (n - 1) + 1; }
+
 struct GradArgs {
   int64_t count;
   double sqrt_s;
@@ -75,7 +78,8 @@ struct GradArgs {
   double* grad_x;
   double* logw;
   double log_const;  // log of the event-independent factors of w_int
-  double* pbuf;      // workspace [12 (n - 1) + 1][count]: recursion adjoints between the two kernels
+  void* pbuf;        // workspace [grad_words(n)][count] in the recursion's precision: its adjoints
+                     // between the two kernels
 };
 
 // Device memory a generation launch works in: per-workgroup partials (NULL: no totals) and,

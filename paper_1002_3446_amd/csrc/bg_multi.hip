@@ -86,7 +86,7 @@ __device__ __attribute__((noinline)) int staged_run(const MultiClass* __restrict
 template <int N>
 __device__ __attribute__((noinline)) int paired_run(const MultiClass* __restrict__ classes,
                                                     const Tile* __restrict__ tiles, int ntiles, int* counter,
-                                                    int* s_tile, int t, double* partials) {
+                                                    int* s_tile, int t, void* lds, double* partials) {
   const int g = (int)(threadIdx.x & 1u);
   while (t < ntiles) {
     const Tile tl = tiles[t];
@@ -94,7 +94,7 @@ __device__ __attribute__((noinline)) int paired_run(const MultiClass* __restrict
     if (mc.n != N) return t;
     CSum w{0.0, 0.0}, w2{0.0, 0.0};
     for (int64_t i = tl.first + (threadIdx.x >> 1); i < tl.first + tl.count; i += kMultiBlock / 2) {
-      const double x = generate_one<N, float, 2>(mc.C, i, PermLds{nullptr, 0}, g);
+      const double x = generate_one<N, float, 2>(mc.C, i, PermLds{nullptr, 0}, g, reinterpret_cast<LdsTable<N>*>(lds));
       w = cs_add(w, CSum{x, 0.0});
       w2 = cs_add(w2, CSum{x * x, 0.0});
     }
@@ -108,20 +108,23 @@ __device__ __attribute__((noinline)) int paired_run(const MultiClass* __restrict
 __global__ __launch_bounds__(kMultiBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_generate_multi(
     const MultiClass* __restrict__ classes, const Tile* __restrict__ tiles, int ntiles, int* counter,
     const double* __restrict__ stage, double* partials) {
-  __shared__ LdsTable<8> lds;  // the span table of the staged classes (n <= 8 fits n = 8's)
+  // the span table of the class at work: of the staged classes (n <= 8 fits n = 8's), or of the
+  // pairs' (n = 12 is the largest; four workgroups use 138 KB of a compute unit's 160 KB)
+  constexpr int kPairs = SpanKGroupLds<11, 2, float>::kBytes * kMultiBlock, kStaged = (int)sizeof(LdsTable<8>);
+  __shared__ __align__(16) unsigned char lds[kPairs > kStaged ? kPairs : kStaged];
   __shared__ int s_tile;
   int t = next_tile(counter, &s_tile);
   while (t < ntiles) {
     switch (classes[tiles[t].cls].n) {
-      case 4: t = staged_run<4>(classes, tiles, ntiles, counter, &s_tile, t, stage, &lds, partials); break;
-      case 5: t = staged_run<5>(classes, tiles, ntiles, counter, &s_tile, t, stage, &lds, partials); break;
-      case 6: t = staged_run<6>(classes, tiles, ntiles, counter, &s_tile, t, stage, &lds, partials); break;
-      case 7: t = staged_run<7>(classes, tiles, ntiles, counter, &s_tile, t, stage, &lds, partials); break;
-      case 8: t = staged_run<8>(classes, tiles, ntiles, counter, &s_tile, t, stage, &lds, partials); break;
-      case 9: t = paired_run<9>(classes, tiles, ntiles, counter, &s_tile, t, partials); break;
-      case 10: t = paired_run<10>(classes, tiles, ntiles, counter, &s_tile, t, partials); break;
-      case 11: t = paired_run<11>(classes, tiles, ntiles, counter, &s_tile, t, partials); break;
-      default: t = paired_run<12>(classes, tiles, ntiles, counter, &s_tile, t, partials); break;
+      case 4: t = staged_run<4>(classes, tiles, ntiles, counter, &s_tile, t, stage, lds, partials); break;
+      case 5: t = staged_run<5>(classes, tiles, ntiles, counter, &s_tile, t, stage, lds, partials); break;
+      case 6: t = staged_run<6>(classes, tiles, ntiles, counter, &s_tile, t, stage, lds, partials); break;
+      case 7: t = staged_run<7>(classes, tiles, ntiles, counter, &s_tile, t, stage, lds, partials); break;
+      case 8: t = staged_run<8>(classes, tiles, ntiles, counter, &s_tile, t, stage, lds, partials); break;
+      case 9: t = paired_run<9>(classes, tiles, ntiles, counter, &s_tile, t, lds, partials); break;
+      case 10: t = paired_run<10>(classes, tiles, ntiles, counter, &s_tile, t, lds, partials); break;
+      case 11: t = paired_run<11>(classes, tiles, ntiles, counter, &s_tile, t, lds, partials); break;
+      default: t = paired_run<12>(classes, tiles, ntiles, counter, &s_tile, t, lds, partials); break;
     }
   }
 }

@@ -579,6 +579,19 @@ int plan_class(const bg_config& c, const GenClass& G, ClassPlan& P) {
   return BG_OK;
 }
 
+// Whether a staged class runs its recursion on the events that pass the cuts only (PassList): no
+// output of |A|^2 or log w, cuts that can reject, and a recursion long enough.  The list's two
+// launches and its writes take 10 to 18 us, lost where every event passes, and nothing is gained
+// within the first round or two of waves (2^17 lanes).  us per call of weights, observables and
+// totals, every event / list, at 14 TeV (0.4% pass at n = 8), and with cuts that all pass:
+//   n = 7 FP32 2^17 63 / 55 (60 / 69 all), 2^20 253 / 134 (230 / 249);  n = 8 FP32 2^17 77 / 66 (74 / 85),
+//   2^18 131 / 87, 2^20 383 / 159 (370 / 386), FP64 2^20 548 / 164 (531 / 550);
+//   n = 12 FP32 2^15 90 / 92, 2^16 155 / 102, 2^17 279 / 117 (278 / 288), 2^20 2000 / 293 (1989 / 2016).
+bool pass_listed(const bg_config& c, const ClassPlan& P, const GenClass& G) {
+  return P.staged && !P.wform && !G.out.amp2 && !G.out.logw && (c.pt_min > 0 || c.dr_min > 0) &&
+         P.lanes * G.count >= (int64_t(1) << 17) && G.count * event_cost(c.n, c.prec) >= 3e5;
+}
+
 // Persistent multi-class launch over the FP32 classes ks (see bg_multi.hip).  Returns
 // BG_ENOTSUP, with nothing enqueued, when the classes' staging would exceed
 // kMultiStageMax (the caller then runs them one after another).
@@ -916,10 +929,13 @@ int bg_generate(const bg_config* cfgs, int ncfg, const int64_t* counts, const bg
   // the split form's staging: one buffer per class when classes may run side by side,
   // else one buffer reused by every class in turn
   size_t shared_stage = 0;
+  bool listed[16] = {false};
   for (int k : todo) {
     if (!P[k].staged) continue;
     scap[k] = std::min<int64_t>(kStageChunk, (G[k].count + 255) / 256 * 256);  // a multiple of 256
-    const size_t sb = (size_t)scap[k] * split_words(cfgs[k].n) * sizeof(double);
+    size_t sb = (size_t)scap[k] * split_words(cfgs[k].n) * sizeof(double);
+    listed[k] = pass_listed(cfgs[k], P[k], G[k]);
+    if (listed[k]) sb += (size_t)pass_words(scap[k]) * sizeof(uint64_t);
     if (concurrent) {
       soff[k] = bytes;
       bytes += sb;
@@ -937,7 +953,8 @@ int bg_generate(const bg_config* cfgs, int ncfg, const int64_t* counts, const bg
   // (the recursion kernel read 58% more from HBM, for the same time)
   auto run_class = [&](int k, hipStream_t t) {
     GenWork W{outs[k].acc ? ws.d() + off[k] / sizeof(double) : nullptr,
-              scap[k] > 0 ? ws.d() + soff[k] / sizeof(double) : nullptr, scap[k], (int64_t)cu_count() * 2};
+              scap[k] > 0 ? ws.d() + soff[k] / sizeof(double) : nullptr, scap[k], (int64_t)cu_count() * 2, nullptr};
+    if (listed[k]) W.passed = reinterpret_cast<uint64_t*>(W.stage + scap[k] * split_words(cfgs[k].n));
     int st = from_hip(P[k].fn(G[k], W, P[k].block, t));
     if (st == BG_OK && W.partials)
       st = from_hip(launch_finalize(W.partials, P[k].nblocks, W.partials + 4 * P[k].nblocks, outs[k].acc, t));

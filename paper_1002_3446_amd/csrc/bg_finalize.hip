@@ -134,4 +134,60 @@ hipError_t launch_finalize(const double* partials, int64_t nparts, double* level
   return hipGetLastError();
 }
 
+// The slots of the events whose bits are set, in event order, into word `word` of the staging slots,
+// and their number into *total.  A workgroup takes kListMasks masks: it adds up the masks before
+// them (512 KB from L2 at most, in a chunk of 2^22 events), then each wave a share of them in turn,
+// a lane per event, so that the list is written in whole lines.
+constexpr int kListMasks = 256;
+__global__ __launch_bounds__(1024) void k_pass_list(const uint64_t* __restrict__ masks, int64_t nmasks, double* stage,
+                                                    int word, int words, uint64_t* total) {
+  __shared__ int64_t before[16], own[kListMasks / 64], start[kListMasks];
+  __shared__ uint64_t mask[kListMasks];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t q0 = (int64_t)blockIdx.x * kListMasks;
+  int64_t sum = 0;
+  for (int64_t m = tid; m < q0; m += 1024) sum += __popcll(masks[m]);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) before[wave] = sum;
+  const uint64_t mine = tid < kListMasks && q0 + tid < nmasks ? masks[q0 + tid] : 0;
+  int64_t upto = __popcll(mine);  // inclusive over the wave's masks
+  if (tid < kListMasks) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int64_t o = __shfl_up(upto, off);
+      if (lane >= off) upto += o;
+    }
+    start[tid] = upto - __popcll(mine);
+    mask[tid] = mine;
+    if (lane == 63) own[wave] = upto;
+  }
+  __syncthreads();
+  int64_t base = 0;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) base += before[v];
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+    uint64_t n = (uint64_t)base;
+    for (int v = 0; v < kListMasks / 64; ++v) n += (uint64_t)own[v];
+    *total = n;
+  }
+  constexpr int kShare = kListMasks / 16;
+  for (int v = 0; v < wave * kShare / 64; ++v) base += own[v];
+#pragma unroll 4
+  for (int m = wave * kShare; m < (wave + 1) * kShare; ++m) {
+    const uint64_t bits = mask[m];
+    const int64_t at = base + start[m] + __popcll(bits & ((uint64_t(1) << lane) - 1));
+    if ((bits >> lane) & 1)
+      stage[((at >> 6) * words + word) * 64 + (at & 63)] = __longlong_as_double((q0 + m) * 64 + lane);
+  }
+}
+
+hipError_t launch_pass_list(const GenWork& W, int64_t cnt, int word, int words, hipStream_t s) {
+  const int64_t nmasks = (cnt + 63) / 64;
+  if (nmasks <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_pass_list, dim3((unsigned)((nmasks + kListMasks - 1) / kListMasks)), dim3(1024), 0, s, W.passed,
+                     nmasks, W.stage, word, words, W.passed + W.stage_cap / 64);
+  return hipGetLastError();
+}
+
 }  // namespace bgk

@@ -90,7 +90,15 @@ struct GenWork {
   int64_t stage_cap;
   int64_t ahead;  // one-lane recursion kernel: tiles between a workgroup and the tile whose
                   // staged words it pulls into the L2 cache for a later workgroup (0: none)
+  uint64_t* passed;  // pass_words(stage_cap) words: the recursion runs on the events that pass the cuts
+                     // only (PassList); NULL: on every event
 };
+
+// Words of a PassList over cap events (a multiple of 64): one mask per 64 events, then their count.
+constexpr int64_t pass_words(int64_t cap) { return cap / 64 + 1; }
+// The list of a chunk of cnt events from its masks, into word `word` of the staging slots of `words`
+// words; the count behind the masks of W.stage_cap events.
+hipError_t launch_pass_list(const GenWork& W, int64_t cnt, int word, int words, hipStream_t s);
 
 using GenerateFn = hipError_t (*)(const GenClass& C, const GenWork& W, int block, hipStream_t s);
 using Amp2Fn = hipError_t (*)(int64_t count, const double* mom, const uint32_t* hel, const uint8_t* order,

@@ -52,6 +52,24 @@ struct EventWord {
   }
 };
 
+// The events that pass the cuts, where nothing of the others is asked for but their weight, which is
+// zero (no |A|^2, no log w; the rule: pass_listed).  k_kin leaves one mask per 64 events, k_pass_list
+// turns the masks into the list of the passing events' slots in event order, k_rec / k_rec_g run
+// on that list, leaving each weight in its event's slot, and k_sum_weights forms the partials from
+// the slots in the recursion kernels' launch shapes: every value and the totals are bitwise those
+// of the route over every event, which is also what runs when all of them pass.  List and weights
+// lie in the words of the slots that only the log w output uses.
+struct PassList {
+  const uint64_t* count;  // passing events; NULL: no list, every event
+  double* stage;
+};
+
+// Slot of the list's entry l
+template <int N>
+__device__ __forceinline__ int64_t pass_slot(const double* __restrict__ buf, int64_t l) {
+  return __double_as_longlong(buf[SplitLayout<N>::at(l, SplitLayout<N>::kX1)]);
+}
+
 // Kinematics of event i (staging slot j): writes the cut flag and observables and stages
 // the event.  perm: the lane's LDS column (perm_lds_bytes).  Bound by VALU issue (92% of the
 // SIMD's slots at n = 8 with three waves), so what counts is instructions: 3638 -> 2880 per wave
@@ -60,7 +78,7 @@ struct EventWord {
 // 461 -> 400 us per 2^22 events at n = 8, 234 -> 199 us at n = 4.
 template <int N>
 __device__ __forceinline__ void kin_one(const GenClass& C, int64_t i, int64_t j, double* __restrict__ buf,
-                                        PermLds perm) {
+                                        PermLds perm, uint64_t* passed = nullptr) {
   using L = SplitLayout<N>;
   EventKin<N> ev;
   double ht, rmin;
@@ -83,6 +101,14 @@ __device__ __forceinline__ void kin_one(const GenClass& C, int64_t i, int64_t j,
   }
   if (C.dynamic_scale) buf[L::at(j, L::kR)] = scale_ratio<N>(C, ht, ev.x1, ev.x2);
   buf[L::at(j, L::kMeta)] = __longlong_as_double((long long)EventWord<N>::pack(ev.hel, pass, ev.leg).v);
+  if (passed) {
+    const uint64_t m = __ballot(pass);
+    if ((threadIdx.x & 63u) == 0) passed[j >> 6] = m;
+    if (!pass) {
+      if (C.out.weight) C.out.weight[i] = 0.0;
+      buf[L::at(j, L::kX2)] = 0.0;
+    }
+  }
 }
 
 // One event's staged words in registers.
@@ -184,10 +210,11 @@ __device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t i, int64_
 // Launch: blockDim.x = kKinBlock, perm_lds_bytes(N, kKinBlock) bytes of dynamic LDS,
 // ceil(cnt / kKinBlock) workgroups; events first .. first + cnt - 1 into slots 0 .. cnt - 1.
 template <int N>
-__global__ __launch_bounds__(kKinBlock) void k_kin(GenClass C, int64_t first, int64_t cnt, double* __restrict__ buf) {
+__global__ __launch_bounds__(kKinBlock) void k_kin(GenClass C, int64_t first, int64_t cnt, double* __restrict__ buf,
+                                                   uint64_t* __restrict__ passed) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= cnt) return;
-  kin_one<N>(C, first + j, j, buf, dyn_perm());
+  kin_one<N>(C, first + j, j, buf, dyn_perm(), passed);
 }
 
 // Launch: blockDim.x = kLdsLanes, ceil(cnt / kLdsLanes) workgroups, first a multiple of
@@ -204,10 +231,16 @@ constexpr bool rec_prefetch() { return N >= 8; }
 
 template <int N, typename T, int POL>
 __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, rec_waves<N, T, POL>()))) void k_rec(
-    GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials, int64_t ahead) {
+    GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials, int64_t ahead,
+    PassList list) {
   __shared__ RecLds<N, T> tab;
   __shared__ unsigned int scrap[rec_prefetch<N>() ? kLdsLanes : 1];
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t listed = list.count ? (int64_t)*list.count : cnt;
+  if (listed < cnt) {
+    if ((int64_t)blockIdx.x * blockDim.x >= listed) return;
+    j = j < listed ? pass_slot<N>(buf, j) : cnt;
+  }
   Staged<N> st;
   if (j < cnt) load_staged<N>(buf, j, st);
   const int64_t t = (int64_t)blockIdx.x + ahead;
@@ -225,6 +258,10 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, re
   }
   double w = 0.0;
   if (j < cnt) w = rec_staged<N, T, POL>(C, first + j, j, buf, st, &tab);
+  if (listed < cnt) {
+    if (j < cnt) list.stage[SplitLayout<N>::at(j, SplitLayout<N>::kX2)] = w;
+    return;
+  }
   if (partials) block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0}, partials + 4 * (first / kLdsLanes + (int64_t)blockIdx.x));
 }
 
@@ -235,18 +272,43 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, re
 template <int N, typename T, int G>
 __global__ __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(group_waves<T, G>(), group_waves<T, G>()))) void k_rec_g(
-    GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials) {
+    GenClass C, int64_t first, int64_t cnt, const double* __restrict__ buf, double* partials, PassList list) {
   extern __shared__ __align__(16) unsigned char gdyn[];
   int event, g;
   group_place<T, G>(event, g);
   // every lane runs the recursion (QuadSpan); those past the end repeat the last event
   const int64_t jj = (int64_t)blockIdx.x * (blockDim.x / G) + event;
-  const bool live = jj < cnt;
-  const int64_t j = live ? jj : cnt - 1;
+  const int64_t listed = list.count ? (int64_t)*list.count : cnt;
+  if ((int64_t)blockIdx.x * (blockDim.x / G) >= listed) return;
+  const bool live = jj < listed;
+  int64_t j = live ? jj : listed - 1;
+  if (listed < cnt) j = pass_slot<N>(buf, j);
   const double w = rec_one_g<N, T, G>(C, first + j, j, buf, g, live, gdyn);
+  if (listed < cnt) {
+    if (g == 0 && live) list.stage[SplitLayout<N>::at(j, SplitLayout<N>::kX2)] = w;
+    return;
+  }
   if (partials)
     block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0},
                        partials + 4 * (first * G / (int64_t)blockDim.x + (int64_t)blockIdx.x));
+}
+
+// The partials of k_rec (G = 1) or k_rec_g from the weights in the slots, with their launch shapes.
+template <int N, typename T, int G>
+__global__ __launch_bounds__(256) void k_sum_weights(int64_t first, int64_t cnt, const double* __restrict__ buf,
+                                                     double* partials, const uint64_t* count) {
+  if ((int64_t)*count >= cnt) return;  // every event passed: the recursion kernel wrote them
+  int event = (int)threadIdx.x, g = 0;
+  if constexpr (G > 1) group_place<T, G>(event, g);
+  const int64_t j = (int64_t)blockIdx.x * (blockDim.x / G) + event;
+  const double w = g == 0 && j < cnt ? buf[SplitLayout<N>::at(j, SplitLayout<N>::kX2)] : 0.0;
+  block_reduce_store(CSum{w, 0.0}, CSum{w * w, 0.0},
+                     partials + 4 * (first * G / (int64_t)blockDim.x + (int64_t)blockIdx.x));
+}
+
+// A chunk's list (after launch_pass_list); each chunk uses W.passed anew.
+inline PassList pass_list(const GenWork& W) {
+  return W.passed ? PassList{W.passed + W.stage_cap / 64, W.stage} : PassList{nullptr, nullptr};
 }
 
 // The kinematics kernel and the grouped recursion kernel over the class in chunks of
@@ -260,11 +322,14 @@ hipError_t launch_generate_split_g(const GenClass& C, const GenWork& W, int bloc
   for (int64_t first = 0; first < C.count && e == hipSuccess; first += W.stage_cap) {
     const int64_t cnt = std::min<int64_t>(W.stage_cap, C.count - first);
     hipLaunchKernelGGL((k_kin<N>), dim3((unsigned)((cnt + kKinBlock - 1) / kKinBlock)), dim3(kKinBlock),
-                       perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage);
-    e = hipGetLastError();
+                       perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage, W.passed);
+    e = W.passed ? launch_pass_list(W, cnt, SplitLayout<N>::kX1, SplitLayout<N>::kWords, s) : hipGetLastError();
     if (e != hipSuccess) break;
     hipLaunchKernelGGL((k_rec_g<N, T, G>), dim3((unsigned)((cnt * G + block - 1) / block)), dim3(block),
-                       (grouped_lds_bytes<N, T, G>(block)), s, C, first, cnt, W.stage, W.partials);
+                       (grouped_lds_bytes<N, T, G>(block)), s, C, first, cnt, W.stage, W.partials, pass_list(W));
+    if (W.passed && W.partials)
+      hipLaunchKernelGGL((k_sum_weights<N, T, G>), dim3((unsigned)((cnt * G + block - 1) / block)), dim3(block), 0, s,
+                         first, cnt, W.stage, W.partials, W.passed + W.stage_cap / 64);
     e = hipGetLastError();
   }
   return e;
@@ -280,11 +345,14 @@ hipError_t launch_generate_split(const GenClass& C, const GenWork& W, hipStream_
   for (int64_t first = 0; first < C.count && e == hipSuccess; first += W.stage_cap) {
     const int64_t cnt = std::min<int64_t>(W.stage_cap, C.count - first);
     hipLaunchKernelGGL((k_kin<N>), dim3((unsigned)((cnt + kKinBlock - 1) / kKinBlock)), dim3(kKinBlock),
-                       perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage);
-    e = hipGetLastError();
+                       perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage, W.passed);
+    e = W.passed ? launch_pass_list(W, cnt, SplitLayout<N>::kX1, SplitLayout<N>::kWords, s) : hipGetLastError();
     if (e != hipSuccess) break;
     hipLaunchKernelGGL((k_rec<N, T, POL>), dim3((unsigned)((cnt + kLdsLanes - 1) / kLdsLanes)), dim3(kLdsLanes), 0, s, C,
-                       first, cnt, W.stage, W.partials, W.ahead);
+                       first, cnt, W.stage, W.partials, W.passed ? 0 : W.ahead, pass_list(W));
+    if (W.passed && W.partials)
+      hipLaunchKernelGGL((k_sum_weights<N, T, 1>), dim3((unsigned)((cnt + kLdsLanes - 1) / kLdsLanes)), dim3(kLdsLanes),
+                         0, s, first, cnt, W.stage, W.partials, W.passed + W.stage_cap / 64);
     e = hipGetLastError();
   }
   return e;

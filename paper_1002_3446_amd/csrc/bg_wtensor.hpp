@@ -272,7 +272,7 @@ hipError_t launch_generate_w(const GenClass& C, const GenWork& W, hipStream_t s)
   for (int64_t first = 0; first < C.count && e == hipSuccess; first += W.stage_cap) {
     const int64_t cnt = std::min<int64_t>(W.stage_cap, C.count - first);
     hipLaunchKernelGGL((k_kin<N>), dim3((unsigned)((cnt + kKinBlock - 1) / kKinBlock)), dim3(kKinBlock),
-                       perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage);
+                       perm_lds_bytes(N, kKinBlock), s, C, first, cnt, W.stage, (uint64_t*)nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) break;
     hipLaunchKernelGGL((k_rec_w<N, T>), dim3((unsigned)((cnt + 63) / 64)), dim3(64), (w_lds_bytes<N, T>()), s, C,

@@ -348,9 +348,36 @@ struct GradKin {
   double sc;
 };
 
+// The draws of a workgroup's events in LDS, a row of 4 (N - 2) words each (and a word of padding: the
+// rows start in all banks), and their adjoints on the way back.  A lane's words lie together in
+// memory and it takes them in the order of its colour ordering: read from there they cost a chain of
+// two loads and a line per lane and word, while the workgroup's rows are one contiguous block,
+// whose loads depend on nothing (second kernel, n = 8 FP32, 2^20 events:
+// 332 -> 274 us; n = 6 FP64, 2 10^5: 39 -> 34).  Called by every lane of the workgroup.
 template <int N>
-__device__ __forceinline__ void grad_front(const GradArgs& G, int64_t i, GradKin<N>& K) {
-  constexpr int NF = N - 2;
+struct DrawRows {
+  static constexpr int W = 4 * (N - 2), kStride = W + 1;
+  static constexpr int bytes(int events) { return events * kStride * 8; }
+  template <typename F>
+  __device__ __forceinline__ static void each(int64_t first, int64_t count, int events, const F& f) {
+    const int n = (int)(count - first < events ? count - first : events) * W;
+#pragma unroll 8
+    for (int w = (int)threadIdx.x; w < n; w += (int)blockDim.x) f(w, w / W * kStride + w % W);
+  }
+  __device__ __forceinline__ static void load(double* rows, const double* u, int64_t first, int64_t count, int events) {
+    each(first, count, events, [&](int w, int slot) { rows[slot] = u[first * W + w]; });
+    __syncthreads();
+  }
+  __device__ __forceinline__ static void store(const double* rows, double* u, int64_t first, int64_t count,
+                                               int events) {
+    __syncthreads();
+    each(first, count, events, [&](int w, int slot) { u[first * W + w] = rows[slot]; });
+  }
+};
+
+// (row: the event's draws, DrawRows)
+template <int N>
+__device__ __forceinline__ void grad_front(const GradArgs& G, int64_t i, const double* row, GradKin<N>& K) {
   K.leg[0] = 0;
 #pragma unroll
   for (int t = 1; t < N; ++t) {
@@ -375,7 +402,7 @@ __device__ __forceinline__ void grad_front(const GradArgs& G, int64_t i, GradKin
   for (int t = 1; t < N; ++t) {
     const bool out = K.leg[t] >= 2u;
     const uint32_t pidx = out ? K.leg[t] - 2u : 0u;
-    const double* u = G.u + (i * NF + pidx) * 4;
+    const double* u = row + 4 * pidx;
     rambo_q(u[0], u[1], u[2], u[3], K.q[t]);
     if (out) {
 #pragma unroll
@@ -402,14 +429,11 @@ __device__ __forceinline__ void grad_front(const GradArgs& G, int64_t i, GradKin
 // |m|^2 vanishes or is not finite.
 template <int N>
 __device__ __forceinline__ bool grad_logw(const GradArgs& G, int64_t i, const GradKin<N>& K, double m2, bool store) {
-  constexpr int NF = N - 2;
   const double ln2 = 0.69314718055994530942;
   double lw = log(m2) + (double)(2 * K.ex * (4 - N) - (N - 2)) * ln2 + (N - 5) * log(K.shat) + G.log_const;
   if (G.use_pdf) lw += G.pdf_a * (log(K.x1) + log(K.x2)) + G.pdf_b * (log1p(-K.x1) + log1p(-K.x2));
   if (!(m2 > 0.0) || !isfinite(m2)) {
-    if (store) {
-      double* gu = G.grad_u + i * NF * 4;
-      for (int c = 0; c < NF * 4; ++c) gu[c] = 0.0;
+    if (store) {  // (the second kernel writes the draws' zeros)
       G.grad_x[2 * i] = 0.0;
       G.grad_x[2 * i + 1] = 0.0;
       if (G.logw) G.logw[i] = -INFINITY;
@@ -421,11 +445,11 @@ __device__ __forceinline__ bool grad_logw(const GradArgs& G, int64_t i, const Gr
 }
 
 // From the CM momentum adjoints pb (polarisation adjoints included) and the sqrt(s_hat)
-// adjoint of the beams: RAMBO's conformal map, q(rho), and x1, x2; writes the gradients.
+// adjoint of the beams: RAMBO's conformal map, q(rho), and x1, x2; writes the gradient in x1, x2
+// and puts that in the draws in their place in row.
 template <int N>
 __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const GradKin<N>& K, const double (&pb)[N][4],
-                                          double rsb) {
-  constexpr int NF = N - 2;
+                                          double rsb, double* row) {
   const double gw = G.gout ? G.gout[i] : 1.0;
   RamboMapAdj A{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   double qb[N][4];
@@ -437,18 +461,16 @@ __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const Gr
   }
   double Qb[4] = {0.0, 0.0, 0.0, 0.0};
   rambo_init_adj(K.map, K.Q, A, Qb, rsb);
-  double* gu = G.grad_u + i * NF * 4;
 #pragma unroll
   for (int t = 1; t < N; ++t) {
     if (K.leg[t] >= 2u) {
-      const uint32_t pidx = K.leg[t] - 2u;
-      const double* u = G.u + (i * NF + pidx) * 4;
+      double* u = row + 4 * (K.leg[t] - 2u);
       double qbt[4], rb[4];
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) qbt[mu] = qb[t][mu] + Qb[mu];
       rambo_q_adj(u[0], u[2], u[3], K.q[t], qbt, rb);
-      double* o = gu + pidx * 4;
-      o[0] = gw * rb[0]; o[1] = gw * rb[1]; o[2] = gw * rb[2]; o[3] = gw * rb[3];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) u[c] = gw * rb[c];
     }
   }
   // s_hat = x1 x2 S:  d sqrt(s_hat) / dx_i = sqrt(s_hat) / (2 x_i)
@@ -484,10 +506,13 @@ template <int N, typename T>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_grad(GradArgs G) {
   constexpr int L = N - 1;
   using SP = Spans<L>;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  extern __shared__ __align__(16) unsigned char gdyn[];  // DrawRows
+  double* rows = reinterpret_cast<double*>(gdyn);
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x, i = first + threadIdx.x;
+  DrawRows<N>::load(rows, G.u, first, G.count, (int)blockDim.x);
   if (i >= G.count) return;
   GradKin<N> K;
-  grad_front<N>(G, i, K);
+  grad_front<N>(G, i, rows + threadIdx.x * DrawRows<N>::kStride, K);
   double k[L][4];
   cv4<T> src[L];
 #pragma unroll
@@ -543,19 +568,29 @@ constexpr bool grad_dist_scalars() {
 // GL lanes per event (the grouped recursion and its reverse sweep, bg_group_adj.hpp); every
 // lane evaluates the kinematics, lane g writes its components of the raw adjoints.  The
 // forward values pass an optimisation barrier before the sweep, so the compiler does not keep
-// the forward pass's intermediates live across it.  Workgroups of 256 lanes, with
-// SpanKGroupLds::kBytes of dynamic LDS per lane.  Bound by VALU issue at one wave per SIMD (87% at
+// the forward pass's intermediates live across it.  Workgroups of kLdsLanes lanes, with
+// grad_lds_bytes of dynamic LDS: the draws' rows, then the span table.  Bound by VALU issue at one wave per SIMD (87% at
 // n = 8: 20892 instructions a wave).
 template <int N, typename T, int GL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_grad_g(GradArgs G) {
+constexpr int grad_lds_bytes() {
+  return SpanKGroupLds<N - 1, GL, T>::kBytes * kLdsLanes > DrawRows<N>::bytes(kLdsLanes / GL)
+             ? SpanKGroupLds<N - 1, GL, T>::kBytes * kLdsLanes
+             : DrawRows<N>::bytes(kLdsLanes / GL);
+}
+
+template <int N, typename T, int GL>
+__global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_grad_g(GradArgs G) {
   constexpr int L = N - 1, C = 4 / GL;
   using SP = Spans<L>;
   using SS = SpanScalars<L, GL, T, grad_dist_scalars<L, GL, T>()>;
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / GL;
-  const int g = (int)(threadIdx.x % GL);
+  extern __shared__ __align__(16) unsigned char gdyn[];
+  const int event = (int)threadIdx.x / GL, g = (int)threadIdx.x % GL;
+  const int64_t first = (int64_t)blockIdx.x * (kLdsLanes / GL), i = first + event;
+  DrawRows<N>::load(reinterpret_cast<double*>(gdyn), G.u, first, G.count, kLdsLanes / GL);
   if (i >= G.count) return;
   GradKin<N> K;
-  grad_front<N>(G, i, K);
+  grad_front<N>(G, i, reinterpret_cast<double*>(gdyn) + event * DrawRows<N>::kStride, K);
+  __syncthreads();  // the span table takes the rows' place
   const LaneShare<GL, T> ls(g);
   const LaneShare<GL, double> lsd(g);
   double k[L][C];  // covariant, this lane's components
@@ -580,8 +615,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       e0.im[c] = ls.template pick<true>(e.im, c);
     }
   }
-  extern __shared__ __align__(16) unsigned char gdyn[];  // SpanKGroupLds::kBytes per lane
-  const SpanKGroupLds<L, GL, T> ks(k, lsd.sg, gdyn, (int)threadIdx.x, (int)blockDim.x);
+  const SpanKGroupLds<L, GL, T> ks(k, lsd.sg, gdyn, (int)threadIdx.x, kLdsLanes);
   cvl<T, C> J[SP::count];
   SS S(g);
   cvl<T, C> V;
@@ -647,19 +681,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 // Second gradient kernel (one lane per event): from the recursion's adjoints that k_grad or
 // k_grad_g left in pbuf, the helicity sources' and momenta's adjoints (CM frame), RAMBO's
-// conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were completed by the first.  Bound by
-// the draws' and their adjoints' rows (a lane's words lie together, 192 B at n = 8) and the FP64
-// chains at two waves per SIMD: 5141 -> 2731 instructions and 680 -> 256 B of adjoints an event,
-// n = 8 FP32 442 -> 332 us per 2^20 events, n = 6 FP64 46 -> 39 per 2 10^5.
+// conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were
+// completed by the first, but for the draws' zeros.  Bound by
+// its 700 B an event (2.7 TB/s) and the FP64 chains at two waves per SIMD: 5141 -> 2731 instructions
+// and 680 -> 256 B of adjoints an event, then the rows in LDS: n = 8 FP32 442 -> 332 -> 274 us per
+// 2^20 events, n = 6 FP64 46 -> 39 -> 34 per 2 10^5.
 template <int N, typename T>
-__global__ __launch_bounds__(256) void k_grad_back(GradArgs G) {
+__device__ __forceinline__ void grad_back_event(const GradArgs& G, int64_t i, double* row) {
   using R = GradRaw<N>;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= G.count) return;
   const T* __restrict__ o = static_cast<const T*>(G.pbuf) + i;
-  if (o[R::kFlag * G.count] == T(0)) return;
+  if (o[R::kFlag * G.count] == T(0)) {
+#pragma unroll
+    for (int c = 0; c < DrawRows<N>::W; ++c) row[c] = 0.0;
+    return;
+  }
   GradKin<N> K;
-  grad_front<N>(G, i, K);
+  grad_front<N>(G, i, row, K);
   double pb[N][4];
   double rsb = 0.0;
 #pragma unroll
@@ -681,7 +718,19 @@ __global__ __launch_bounds__(256) void k_grad_back(GradArgs G) {
       rsb += 0.5 * (pb[t][0] - pb[t][3]);  // leg 1: p = (rs/2)(1, 0, 0, -1)
     }
   }
-  grad_back<N>(G, i, K, pb, rsb);
+  grad_back<N>(G, i, K, pb, rsb, row);
+}
+
+// Launch: kLdsLanes lanes, DrawRows<N>::bytes(kLdsLanes) bytes of dynamic LDS.
+template <int N, typename T>
+__global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(N <= 8 ? 2 : 1, 8))) void k_grad_back(
+    GradArgs G) {
+  extern __shared__ __align__(16) unsigned char gdyn[];
+  double* rows = reinterpret_cast<double*>(gdyn);
+  const int64_t first = (int64_t)blockIdx.x * kLdsLanes, i = first + threadIdx.x;
+  DrawRows<N>::load(rows, G.u, first, G.count, kLdsLanes);
+  if (i < G.count) grad_back_event<N, T>(G, i, rows + threadIdx.x * DrawRows<N>::kStride);
+  DrawRows<N>::store(rows, G.grad_u, first, G.count, kLdsLanes);
 }
 
 }  // namespace bgk

@@ -132,14 +132,15 @@ hipError_t BG_NAME(launch_grad_n, BG_N, BG_PREC, BG_KIND)(const GradArgs& G, int
   constexpr int GL = grad_lanes(BG_N, BG_PREC);
   if constexpr (GL == 1) {
     const int64_t nb = (G.count + block - 1) / block;
-    hipLaunchKernelGGL((k_grad<BG_N, Real>), dim3((unsigned)nb), dim3(block), 0, s, G);
+    hipLaunchKernelGGL((k_grad<BG_N, Real>), dim3((unsigned)nb), dim3(block), DrawRows<BG_N>::bytes(block), s, G);
   } else {
     (void)block;
-    const int64_t nb = (GL * G.count + 255) / 256;
-    hipLaunchKernelGGL((k_grad_g<BG_N, Real, GL>), dim3((unsigned)nb), dim3(256),
-                       (SpanKGroupLds<BG_N - 1, GL, Real>::kBytes * 256), s, G);
+    const int64_t nb = (GL * G.count + kLdsLanes - 1) / kLdsLanes;
+    hipLaunchKernelGGL((k_grad_g<BG_N, Real, GL>), dim3((unsigned)nb), dim3(kLdsLanes),
+                       (grad_lds_bytes<BG_N, Real, GL>()), s, G);
   }
-  hipLaunchKernelGGL((k_grad_back<BG_N, Real>), dim3((unsigned)((G.count + 255) / 256)), dim3(256), 0, s, G);
+  hipLaunchKernelGGL((k_grad_back<BG_N, Real>), dim3((unsigned)((G.count + kLdsLanes - 1) / kLdsLanes)),
+                     dim3(kLdsLanes), DrawRows<BG_N>::bytes(kLdsLanes), s, G);
   return hipGetLastError();
 }
 #else

@@ -23,6 +23,8 @@ import torch
 from . import bg
 
 NS = list(range(4, 13))
+# with |A|^2 of every event: without it the recursion runs on the events that pass the cuts only
+OUTPUTS = ("weight", "amp2", "acc")
 
 
 def _time(fn, reps=3):
@@ -64,7 +66,7 @@ def tune_single(prec=32, scale=0, log=print):
     for n in NS:
         N = 1 << max(20 - scale, 26 - n - scale)
         cfg = bg.config(n, prec=prec, seed=0xB6000003 + n)
-        out = bg.generate(cfg, N, outputs=("weight", "acc"))
+        out = bg.generate(cfg, N, outputs=OUTPUTS)
         cands = [(lanes, 0, block) for lanes in lane_forms(n, prec) for block in (64, 128, 256)]
         if wtensor_forms(n, prec):
             cands.append((0, 1, 64))   # W-tensor: fixed 64-lane workgroups, lanes unused
@@ -74,7 +76,7 @@ def tune_single(prec=32, scale=0, log=print):
             if lanes:
                 bg.set_lanes(n, prec, lanes)
             bg.set_launch(n, prec, block, bg.get_launch(n, prec)[1] or 1)
-            t = _time(lambda: bg.generate(cfg, N, outputs=("weight", "acc"), out_tensors=[out]))
+            t = _time(lambda: bg.generate(cfg, N, outputs=OUTPUTS, out_tensors=[out]))
             log(f"n={n} prec={prec} form={form} lanes={lanes} block={block}: {t:.3f} ms for {N} events")
             if best is None or t < best[0]:
                 best = (t, block, lanes, form)
@@ -91,8 +93,8 @@ def tune(prec=32, scale=0, log=print):
     if prec != 32:   # the persistent multi-class kernel is FP32 only
         return [dict(n=n, prec=prec, block=b, tile_iters=i, lanes=l, form=f) for n, (b, i, l, f) in shapes.items()], None
     cfgs, counts = mixed_workload(prec, scale)
-    outs = bg.generate(cfgs, counts, outputs=("weight", "acc"))
-    run = lambda: bg.generate(cfgs, counts, outputs=("weight", "acc"), out_tensors=outs)
+    outs = bg.generate(cfgs, counts, outputs=OUTPUTS)
+    run = lambda: bg.generate(cfgs, counts, outputs=OUTPUTS, out_tensors=outs)
     base = _time(run)
     log(f"mixed launch, default tiles: {base:.3f} ms")
     for n in NS:

@@ -42,8 +42,9 @@ def flops_plain(n: int) -> int:
 
 
 def flops_executed(n: int) -> int:
-    """Per-event floating-point operations of the recursion and closure as the kernel
-    executes them (fma = 2; span momenta and propagators come precomputed): per split of a
+    """Per-event floating-point operations of the recursion and closure in the kernels' regrouped
+    form, every term counted (the one-lane FP32 kernels leave out those with a zero word of a
+    helicity source, 17% of their instructions at n = 8) (fma = 2; span momenta and propagators come precomputed): per split of a
     span, complex dot 30, two complex-real dots 28, two complex axpys 64, K_A - K_B 4 and
     its axpy 16, the span scalar 2 (144); per pair of splits, dot 30 + axpy 32; 2(l-2)
     span-scalar axpys of 32; V = 2X + Y 16; then the propagator 8, or the closure dot 30."""

@@ -145,15 +145,28 @@ struct PdfParams {
   const double* tab;  // [kPdfSegs][4] cubic coefficients (device memory)
 };
 
+// x^k and the primitive's polynomial: loops that run at least once, without a test before the first
+// pass.  (They stand in loops that lanes leave one by one; the compiler evaluates such a test there,
+// for the lanes still in the loop, and takes its mask for the code behind it as well: with b = 0
+// the lanes that had left earlier would run the loop 2^32 times.)
 __host__ __device__ inline double ipow(double x, int k) {
-  double r = 1.0;
-  for (int i = 0; i < k; ++i) r *= x;
+  double r = 1.0, f = 1.0;
+  int i = 0;
+#pragma clang loop unroll(disable)
+  do {
+    r *= f;
+    f = x;
+  } while (i++ < k);
   return r;
 }
 
 __host__ __device__ inline double pdf_poly(const PdfParams& P, double x) {
-  double poly = P.coef[P.b];
-  for (int k = P.b - 1; k >= 0; --k) poly = fma(poly, x, P.coef[k]);
+  double poly = 0.0;
+  int k = P.b;
+#pragma clang loop unroll(disable)
+  do {
+    poly = fma(poly, x, P.coef[k]);
+  } while (--k >= 0);
   return poly;
 }
 

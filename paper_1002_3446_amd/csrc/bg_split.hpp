@@ -183,11 +183,15 @@ __device__ __forceinline__ double rec_one(const GenClass& C, int64_t i, int64_t 
 }
 
 // The same with the event on the G lanes of a group (grouped_amp2; gdyn: the workgroup's dynamic
-// LDS); with live, lane g = 0 writes the outputs and returns w, the others return 0.
-template <int N, typename T, int G>
-__device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t i, int64_t j, const double* __restrict__ buf,
-                                            int g, bool live, unsigned char* gdyn) {
+// LDS); with live, lane g = 0 writes the outputs and returns w, the others return 0.  slot() gives
+// the event's staging slot, and is asked again after the recursion, which has no register to keep it
+// in (event 0 of the launch: first); left in j.
+template <int N, typename T, int G, typename F>
+__device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t first, const F& slot,
+                                            const double* __restrict__ buf, int g, bool live, unsigned char* gdyn,
+                                            int64_t& j) {
   using L = SplitLayout<N>;
+  j = slot();
   const double shat = buf[L::at(j, L::kShat)];
   double pc[N][4];
   const double hb = 0.5 * (C.use_pdf ? sqrt(shat) : C.sqrt_s);
@@ -204,13 +208,16 @@ __device__ __forceinline__ double rec_one_g(const GenClass& C, int64_t i, int64_
   word.legs(leg);
   const double a2 = grouped_amp2<N, T, G>(pc, leg, word.hel(), g, gdyn);
   if (g != 0 || !live) return 0.0;
-  return finish_staged<N>(C, i, j, buf, word.pass(), a2, shat);
+  j = slot();
+  return finish_staged<N>(C, first + j, j, buf, word.pass(), a2, shat);
 }
 
 // Launch: blockDim.x = kKinBlock, perm_lds_bytes(N, kKinBlock) bytes of dynamic LDS,
 // ceil(cnt / kKinBlock) workgroups; events first .. first + cnt - 1 into slots 0 .. cnt - 1.
+// Three waves per SIMD up to n = 8, two beyond (n = 12 wants 257 registers when left alone, and runs
+// at one wave then: 2^20 events 204 -> 290 us).
 template <int N>
-__global__ __launch_bounds__(kKinBlock) void k_kin(GenClass C, int64_t first, int64_t cnt, double* __restrict__ buf,
+__global__ __launch_bounds__(kKinBlock) __attribute__((amdgpu_waves_per_eu(N <= 8 ? 3 : 2, 8))) void k_kin(GenClass C, int64_t first, int64_t cnt, double* __restrict__ buf,
                                                    uint64_t* __restrict__ passed) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= cnt) return;
@@ -281,9 +288,14 @@ __global__ __launch_bounds__(256)
   const int64_t listed = list.count ? (int64_t)*list.count : cnt;
   if ((int64_t)blockIdx.x * (blockDim.x / G) >= listed) return;
   const bool live = jj < listed;
-  int64_t j = live ? jj : listed - 1;
-  if (listed < cnt) j = pass_slot<N>(buf, j);
-  const double w = rec_one_g<N, T, G>(C, first + j, j, buf, g, live, gdyn);
+  const auto slot = [&] {
+    const double* b = buf;
+    opaque(b);  // a read of its own each time
+    const int64_t l = live ? jj : listed - 1;
+    return listed < cnt ? pass_slot<N>(b, l) : l;
+  };
+  int64_t j;
+  const double w = rec_one_g<N, T, G>(C, first, slot, buf, g, live, gdyn, j);
   if (listed < cnt) {
     if (g == 0 && live) list.stage[SplitLayout<N>::at(j, SplitLayout<N>::kX2)] = w;
     return;

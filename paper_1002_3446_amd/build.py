@@ -66,9 +66,9 @@ def has_lane_pairs(n: int, p: int) -> bool:
     return n >= 9 if p == 32 else n >= 6
 
 
-def kernel_lanes(n: int, p: int, setting: int) -> int:
-    """Lanes per event of the kernel behind a lanes setting (FP64 n = 7, 8: one)."""
-    return 1 if p == 64 and n in (7, 8) else setting
+def one_or_pair(n: int, p: int) -> bool:
+    """FP64 n = 7, 8: one lane per event, two in short calls."""
+    return p == 64 and n in (7, 8)
 
 
 def has_lane_quads(n: int, p: int) -> bool:
@@ -117,8 +117,8 @@ def units_for(ns, precs=(32, 64), kinds=KINDS):
                 if k == 2:
                     forms = (1,)
                 else:
-                    one = has_one_lane(n, p) or kernel_lanes(n, p, 2) == 1
-                    forms = tuple(f for f, ok in ((1, one), (2, has_lane_pairs(n, p) and kernel_lanes(n, p, 2) == 2),
+                    one = has_one_lane(n, p) or one_or_pair(n, p)
+                    forms = tuple(f for f, ok in ((1, one), (2, has_lane_pairs(n, p)),
                                                   (3, k == 0 and has_real_pol(n, p)),
                                                   (4, has_wtensor(n, p)),
                                                   (5, k < 2 and has_lane_quads(n, p))) if ok)

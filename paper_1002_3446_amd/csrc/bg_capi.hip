@@ -57,26 +57,13 @@ using namespace bgk;
     launch_generate_w_n##N##_p64_k0, launch_amp2_w_n##N##_p64_k1, launch_generate4_n##N##_p64_k0,        \
     launch_amp2_4_n##N##_p64_k1}}
 
-// FP64 n = 7, 8: the one-lane kernels answer to the setting 2 (kernel_lanes)
-struct Table {
-  Launchers t[9][2] = {BG_ROW(4),  BG_ROW(5),  BG_ROW(6), BG_ROW(7), BG_ROW(8),
-                       BG_ROW(9), BG_ROW(10), BG_ROW(11), BG_ROW(12)};
-  Table() {
-    for (int n = 7; n <= 8; ++n) {
-      Launchers& l = t[n - 4][1];
-      l.generate2 = l.generate;
-      l.amp2_2 = l.amp2;
-      l.generate = nullptr;
-      l.amp2 = nullptr;
-    }
-  }
-};
+const Launchers kTable[9][2] = {BG_ROW(4), BG_ROW(5), BG_ROW(6), BG_ROW(7), BG_ROW(8),
+                                BG_ROW(9), BG_ROW(10), BG_ROW(11), BG_ROW(12)};
 
 const Launchers* table(int n, int prec) {
-  static const Table t;
   if (n < 4 || n > 12) return nullptr;
   if (prec != 32 && prec != 64) return nullptr;
-  return &t.t[n - 4][prec == 32 ? 0 : 1];
+  return &kTable[n - 4][prec == 32 ? 0 : 1];
 }
 
 // launch shapes per (n, prec): threads per workgroup, and events per lane in one tile of
@@ -562,11 +549,12 @@ int plan_class(const bg_config& c, const GenClass& G, ClassPlan& P) {
   const Launchers* L = table(c.n, c.prec);
   P.wform = !c.polarisation && form_of(c.n, c.prec) == 1;
   P.lanes = (c.polarisation || P.wform) ? 1 : lanes_of(c.n, c.prec);
+  P.lanes = kernel_lanes(c.n, c.prec, P.lanes, G.count);
+  if (c.polarisation || P.wform) P.lanes = 1;
   P.fn = c.polarisation ? L->generate_real
                         : (P.wform ? L->generate_w
                                    : (P.lanes == 4 ? L->generate4 : (P.lanes == 2 ? L->generate2 : L->generate)));
   if (!P.fn) return BG_ENOTSUP;
-  P.lanes = kernel_lanes(c.n, c.prec, P.lanes);
   // 64-lane workgroups: the W-tensor form and the one-lane kernels with an LDS table
   const bool table_class = P.lanes == 1 && lds_span_table(c.n, c.prec) && !(c.polarisation && c.prec == 64);
   // staged: the W-tensor form, the split table classes, and every grouped form (kinematics in
@@ -835,7 +823,7 @@ int bg_set_lanes(int n, int prec, int lanes) {
   const Launchers* L = table(n, prec);
   if (!L) return BG_ENOTSUP;
   if (lanes != 0 && lanes != 1 && lanes != 2 && lanes != 4) return BG_EINVAL;
-  if (lanes == 1 && !(L->generate && L->amp2)) return BG_ENOTSUP;
+  if (lanes == 1 && (one_or_pair(n, prec) || !(L->generate && L->amp2))) return BG_ENOTSUP;
   if (lanes == 2 && !(L->generate2 && L->amp2_2)) return BG_ENOTSUP;
   if (lanes == 4 && !(L->generate4 && L->amp2_4)) return BG_ENOTSUP;
   std::lock_guard<std::mutex> lk(g_shape_mu);
@@ -1055,12 +1043,12 @@ int bg_amp2(int n, int prec, int64_t N, const double* mom, const uint32_t* hel, 
   const Launchers* L = table(n, prec);
   if (!L) return BG_ENOTSUP;
   if (N < 0) return BG_EINVAL;
-  const int lanes = lanes_of(n, prec);
+  const int lanes = kernel_lanes(n, prec, lanes_of(n, prec), N);
   const Amp2Fn f = form_of(n, prec) == 1 ? L->amp2_w : (lanes == 4 ? L->amp2_4 : (lanes == 2 ? L->amp2_2 : L->amp2));
   if (!f) return BG_ENOTSUP;
   if (N == 0) return BG_OK;
   if (!mom || !hel || !order || !amp2_out) return BG_EINVAL;
-  const int block = prec == 64 && n >= 9 ? kLdsLanes : shape_of(n, prec).block;  // as plan_class
+  const int block = prec == 64 && n >= 7 ? kLdsLanes : shape_of(n, prec).block;  // as plan_class
   return from_hip(f(N, mom, hel, order, amp2_out, block, (hipStream_t)stream));
 }
 

@@ -830,6 +830,121 @@ struct Fp64Span {
   __device__ __forceinline__ double2 scalar() const { return sc[(S - L) * LANES]; }
 };
 
+// The products for n = 7, 8 (L >= 6) in the order of the two-lane form, (0, 1) and (3, 2) summed
+// apart, so that both forms give the same bits and short calls can take that one (pair_call).
+template <bool LX, bool LY>
+__device__ __forceinline__ void dot_pairs(const cv4<double>& x, const cv4<double>& y, double& r, double& i) {
+#pragma clang fp contract(off)
+  double r0, i0 = -x.re[1] * y.im[1], r1 = -x.re[3] * y.re[3], i1 = -x.re[2] * y.im[2];
+  if constexpr (LX || LY)
+    r0 = -x.re[1] * y.re[1];
+  else
+    r0 = fmac(-x.re[1], y.re[1], x.re[0] * y.re[0]);
+  r0 = fmac(x.im[1], y.im[1], r0);
+  i0 = fmac(-x.im[1], y.re[1], i0);
+  r1 = fmac(x.im[2], y.im[2], fmac(-x.re[2], y.re[2], r1));
+  i1 = fmac(-x.im[2], y.re[2], i1);
+  if constexpr (!LX && !LY) {
+    r0 = fmac(-x.im[0], y.im[0], r0);
+    i0 = fmac(x.im[0], y.re[0], fmac(x.re[0], y.im[0], i0));
+    r1 = fmac(x.im[3], y.im[3], r1);
+  }
+  if constexpr (!LY) i1 = fmac(-x.re[3], y.im[3], i1);
+  if constexpr (!LX) i1 = fmac(-x.im[3], y.re[3], i1);
+  r = r0 + r1;
+  i = i0 + i1;
+}
+
+template <bool LX>
+__device__ __forceinline__ void rdot_pairs(const cv4<double>& x, const double (&k)[4], double& r, double& i) {
+#pragma clang fp contract(off)
+  const double r1 = fmac(x.re[2], k[2], x.re[3] * k[3]);
+  if constexpr (LX) {
+    r = x.re[1] * k[1] + r1;
+    i = x.im[1] * k[1] + x.im[2] * k[2];
+  } else {
+    r = fmac(x.re[1], k[1], x.re[0] * k[0]) + r1;
+    i = fmac(x.im[1], k[1], x.im[0] * k[0]) + fmac(x.im[2], k[2], x.im[3] * k[3]);
+  }
+}
+
+template <bool LY>
+__device__ __forceinline__ void axpy_pairs(double cr, double ci, const cv4<double>& y, cv4<double>& acc) {
+#pragma unroll
+  for (int mu = 0; mu < 4; mu += 3) {
+    if (LY && mu == 0) continue;
+    acc.re[mu] = fmac(cr, y.re[mu], acc.re[mu]);
+    acc.im[mu] = fmac(ci, y.re[mu], acc.im[mu]);
+    if constexpr (!LY) {
+      acc.re[mu] = fmac(-ci, y.im[mu], acc.re[mu]);
+      acc.im[mu] = fmac(cr, y.im[mu], acc.im[mu]);
+    }
+  }
+#pragma unroll
+  for (int mu = 1; mu < 3; ++mu) {
+    acc.re[mu] = fmac(-ci, y.im[mu], fmac(cr, y.re[mu], acc.re[mu]));
+    acc.im[mu] = fmac(ci, y.re[mu], fmac(cr, y.im[mu], acc.im[mu]));
+  }
+}
+
+// span_vertex_d in that order
+template <int L, int A, int B, int LANES>
+__device__ __forceinline__ void span_vertex_pairs(const Fp64Span<L, LANES>& ks,
+                                                  const cv4<double> (&J)[Spans<L>::count], const double (&KP)[4],
+                                                  cv4<double>& X, double& sr, double& si) {
+#pragma clang fp contract(off)
+  using SP = Spans<L>;
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) X.re[mu] = X.im[mu] = 0.0;
+  sr = 0.0;
+  si = 0.0;
+  double ka[4];
+  static_for<A, B>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
+    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
+    double kb[4];
+    if constexpr (i == A)
+      ks.template first<A>(ka);
+    else
+      ks.template add<i>(ka);
+    ks.template sum<i + 1, B>(kb);
+    double dr, di, ar, ai, br, bi;
+    dot_pairs<LA, LB>(J[PA], J[PB], dr, di);
+    rdot_pairs<LA>(J[PA], kb, ar, ai);
+    rdot_pairs<LB>(J[PB], ka, br, bi);
+    axpy_pairs<LB>(ar, ai, J[PB], X);
+    axpy_pairs<LA>(-br, -bi, J[PA], X);
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+      const double dk = mu == 0 ? fmac(-0.5, KP[0], ka[0]) : fmac(0.5, KP[mu], -ka[mu]);
+      X.re[mu] = fmac(dr, dk, X.re[mu]);
+      X.im[mu] = fmac(di, dk, X.im[mu]);
+    }
+    sr = fmac(-0.5, dr, sr);
+    si = fmac(-0.5, di, si);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    static_for<i + 1, B>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      double er, ei;
+      dot_pairs<i == A, j + 1 == B>(J[SP::at(A, i)], J[SP::at(j + 1, B)], er, ei);
+      axpy_pairs<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
+    });
+  });
+  static_for<A + 1, B>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    const double2 c = ks.template scalar<SP::at(A, j)>();
+    axpy_pairs<j + 1 == B>(c.x, c.y, J[SP::at(j + 1, B)], X);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const double2 c = ks.template scalar<SP::at(i + 1, B)>();
+    axpy_pairs<i == A>(c.x, c.y, J[SP::at(A, i)], X);
+  });
+}
+
 // Half the bracket sum of span [A..B] (see above) and its -S/2; KP is the span's momentum.
 template <int L, int A, int B, int LANES>
 __device__ __forceinline__ void span_vertex_d(const Fp64Span<L, LANES>& ks, const cv4<double> (&J)[Spans<L>::count],
@@ -902,8 +1017,16 @@ __device__ __forceinline__ void bg_amplitude_d(const Fp64Span<L, LANES>& ks, con
       cv4<double> X;
       double sr, si, K[4];
       ks.template sum<a, b>(K);
-      span_vertex_d<L, a, b, LANES>(ks, J, K, X, sr, si);
-      const double prop = 2.0 / minkowski_sq(K);
+      double k2;
+      if constexpr (L >= 6) {
+#pragma clang fp contract(off)
+        span_vertex_pairs<L, a, b, LANES>(ks, J, K, X, sr, si);
+        k2 = (K[0] * K[0] - K[1] * K[1]) + (-(K[3] * K[3]) - K[2] * K[2]);
+      } else {
+        span_vertex_d<L, a, b, LANES>(ks, J, K, X, sr, si);
+        k2 = minkowski_sq(K);
+      }
+      const double prop = 2.0 / k2;
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) {
         J[s].re[mu] = X.re[mu] * prop;
@@ -916,8 +1039,13 @@ __device__ __forceinline__ void bg_amplitude_d(const Fp64Span<L, LANES>& ks, con
   cv4<double> X;
   double sr, si, K[4], mr, mi;
   ks.template sum<0, L - 1>(K);
-  span_vertex_d<L, 0, L - 1, LANES>(ks, J, K, X, sr, si);
-  cdot<true, false>(eps0, X, mr, mi);
+  if constexpr (L >= 6) {
+    span_vertex_pairs<L, 0, L - 1, LANES>(ks, J, K, X, sr, si);
+    dot_pairs<true, false>(eps0, X, mr, mi);
+  } else {
+    span_vertex_d<L, 0, L - 1, LANES>(ks, J, K, X, sr, si);
+    cdot<true, false>(eps0, X, mr, mi);
+  }
   m_re = 2.0 * mr;
   m_im = 2.0 * mi;
 }

@@ -455,6 +455,7 @@ struct PairSpan {
 // x . y over the pair; xs: x with the first slot times its metric sign (pair_signed)
 template <bool LX, bool LY>
 __device__ __forceinline__ void pdot(const cvp& xs, const cvp& y, double& r, double& i) {
+#pragma clang fp contract(off)
   r = xs.re[0] * y.re[0];
   r = fmac(-xs.re[1], y.re[1], r);
   r = fmac(xs.im[1], y.im[1], r);
@@ -470,6 +471,7 @@ __device__ __forceinline__ void pdot(const cvp& xs, const cvp& y, double& r, dou
 // x . K over the pair for a covariant real K
 template <bool LX>
 __device__ __forceinline__ void prdot(const cvp& x, const double (&k)[2], double& r, double& i) {
+#pragma clang fp contract(off)
   r = group_sum<2>(fmac(x.re[1], k[1], x.re[0] * k[0]));
   if constexpr (LX)
     i = group_sum<2>(x.im[1] * k[1]);
@@ -507,6 +509,7 @@ __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (
   for (int c = 0; c < 2; ++c) X.re[c] = X.im[c] = 0.0;
   sr = 0.0;
   si = 0.0;
+  constexpr bool kApart = L == 6 || L == 7;  // n = 7, 8: the order of span_vertex_pairs
   double ka[2];
   static_for<A, B>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
@@ -533,13 +536,25 @@ __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (
     sr = fmac(-0.5, dr, sr);
     si = fmac(-0.5, di, si);
     // the four-gluon pairs of this left current
-    static_for<i + 1, B>([&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      double er, ei;
-      pdot<LA, j + 1 == B>(xs, J[SP::at(j + 1, B)], er, ei);
-      paxpy<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
-    });
+    if constexpr (!kApart)
+      static_for<i + 1, B>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        double er, ei;
+        pdot<LA, j + 1 == B>(xs, J[SP::at(j + 1, B)], er, ei);
+        paxpy<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
+      });
   });
+  if constexpr (kApart)
+    static_for<A, B - 1>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      const cvp xs = pair_signed<i == A>(ks.sg, J[SP::at(A, i)]);
+      static_for<i + 1, B>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        double er, ei;
+        pdot<i == A, j + 1 == B>(xs, J[SP::at(j + 1, B)], er, ei);
+        paxpy<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
+      });
+    });
   static_for<A + 1, B>([&](auto jc) {
     constexpr int j = decltype(jc)::value;
     const double2 c = ks.template scalar<SP::at(A, j)>();

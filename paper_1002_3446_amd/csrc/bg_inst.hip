@@ -28,8 +28,8 @@ using Real = float;
 using Real = double;
 #endif
 
-static_assert(BG_KIND == 2 || (BG_FORM == 1 && (has_one_lane(BG_N, BG_PREC) || kernel_lanes(BG_N, BG_PREC, 2) == 1)) ||
-                  (BG_FORM == 2 && has_lane_pairs(BG_N, BG_PREC) && kernel_lanes(BG_N, BG_PREC, 2) == 2) || (BG_FORM == 3 && has_real_pol(BG_N, BG_PREC)) ||
+static_assert(BG_KIND == 2 || (BG_FORM == 1 && (has_one_lane(BG_N, BG_PREC) || one_or_pair(BG_N, BG_PREC))) ||
+                  (BG_FORM == 2 && has_lane_pairs(BG_N, BG_PREC)) || (BG_FORM == 3 && has_real_pol(BG_N, BG_PREC)) ||
                   (BG_FORM == 4 && has_wtensor(BG_N, BG_PREC)) || (BG_FORM == 5 && has_lane_quads(BG_N, BG_PREC)),
               "this lane form is not built for (n, prec)");
 

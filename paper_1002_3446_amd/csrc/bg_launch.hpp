@@ -41,7 +41,14 @@ constexpr bool has_one_lane(int n, int prec) { return prec == 32 ? n <= 9 : n <=
 constexpr bool has_lane_pairs(int n, int prec) { return prec == 32 ? n >= 9 : n >= 6; }
 constexpr bool has_lane_quads(int n, int prec) { return prec == 64 && n >= 10; }
 constexpr int default_lanes(int n, int prec) { return prec == 32 ? (n >= 10 ? 2 : 1) : (n >= 10 ? 4 : (n >= 7 ? 2 : 1)); }
-constexpr int kernel_lanes(int n, int prec, int setting) { return prec == 64 && (n == 7 || n == 8) ? 1 : setting; }
+// Up to 2^15 events, where the two-lane form's waves are at most one per SIMD, that form answers
+// sooner (bg_amp2, 2000 to 20000 events, one lane / two: n = 7 14.2 / TA7 us, n = 8 25.0 / TA8; both give
+// the same bits): kernel_lanes is 2 there.
+constexpr bool one_or_pair(int n, int prec) { return prec == 64 && (n == 7 || n == 8); }
+constexpr int64_t kPairEvents = int64_t(1) << 15;
+constexpr int kernel_lanes(int n, int prec, int setting, int64_t count) {
+  return one_or_pair(n, prec) ? (count <= kPairEvents ? 2 : 1) : setting;
+}
 
 // Classes built with real polarisations (real currents: half the registers of complex ones,
 // so one lane per event fits every FP32 class).
@@ -109,8 +116,8 @@ struct Launchers {
   GenerateFn generate;   // one lane per event (the split form for the table classes)
   Amp2Fn amp2;
   GradFn grad;
-  GenerateFn generate2;  // the setting 2 (where has_lane_pairs): two lanes per event, or kernel_lanes
-  Amp2Fn amp2_2;
+  GenerateFn generate2;  // the setting 2 (where has_lane_pairs): two lanes per event
+  Amp2Fn amp2_2;             // (one_or_pair: the setting 2 names generate2 and generate, by count)
   GenerateFn generate_real;  // real polarisations, one lane per event (where has_real_pol)
   GenerateFn generate_w;     // W-tensor form, 16 lanes per event (where has_wtensor)
   Amp2Fn amp2_w;

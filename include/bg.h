@@ -241,8 +241,9 @@ int bg_get_launch(int n, int prec, int *block, int *tile_iters);
  * values BG_EINVAL; 0 restores the default (4 for FP64 n >= 10, 2 for FP32 n >= 10 and
  * FP64 n = 7..9, else 1).  With G lanes each holds 4/G of the four
  * Lorentz components of every current: 1/G of the registers, at the price of cross-lane
- * sums in every Minkowski product.  At FP64 n = 7, 8 the setting 2 names the only form built,
- * whose kernels run one lane per event.  Affects speed only: |A|^2 agrees to the recursion
+ * sums in every Minkowski product.  At FP64 n = 7, 8 the setting 2 names
+ * two kernels with the same bits: two lanes per event in calls of up to 2^15 events, one lane
+ * in longer ones.  Affects speed only: |A|^2 agrees to the recursion
  * precision's rounding between the forms. */
 int bg_set_lanes(int n, int prec, int lanes);
 int bg_get_lanes(int n, int prec, int *lanes);

@@ -571,11 +571,18 @@ constexpr bool grad_dist_scalars() {
 // the forward pass's intermediates live across it.  Workgroups of kLdsLanes lanes, with
 // grad_lds_bytes of dynamic LDS: the draws' rows, then the span table.  Bound by VALU issue at one wave per SIMD (87% at
 // n = 8: 20892 instructions a wave).
+// Whether its span momenta and propagators come from the LDS table: where the sweep spills without
+// it too, what the table brings into registers spills more than the sums cost (us, sums / table:
+// FP64 n = 11, 6 10^4 events 1538 / 1579, n = 12, 8 10^4 3212 / 3408; FP32 n = 12, 10^5 1381 / 1406, but n = 11
+// 1011 / 913; FP64 n = 8, 10^5 566 / 497).
+template <int N, typename T>
+constexpr bool grad_span_table() { return sizeof(T) == 8 ? N <= 8 : N <= 11; }
+
 template <int N, typename T, int GL>
 constexpr int grad_lds_bytes() {
-  return SpanKGroupLds<N - 1, GL, T>::kBytes * kLdsLanes > DrawRows<N>::bytes(kLdsLanes / GL)
-             ? SpanKGroupLds<N - 1, GL, T>::kBytes * kLdsLanes
-             : DrawRows<N>::bytes(kLdsLanes / GL);
+  constexpr int table = grad_span_table<N, T>() ? SpanKGroupLds<N - 1, GL, T>::kBytes * kLdsLanes : 0;
+  constexpr int rows = DrawRows<N>::bytes(kLdsLanes / GL);
+  return table > rows ? table : rows;
 }
 
 template <int N, typename T, int GL>
@@ -615,7 +622,12 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, 1)
       e0.im[c] = ls.template pick<true>(e.im, c);
     }
   }
-  const SpanKGroupLds<L, GL, T> ks(k, lsd.sg, gdyn, (int)threadIdx.x, kLdsLanes);
+  const auto ks = [&] {
+    if constexpr (grad_span_table<N, T>())
+      return SpanKGroupLds<L, GL, T>(k, lsd.sg, gdyn, (int)threadIdx.x, kLdsLanes);
+    else
+      return SpanKGroup<L, GL, T>{k, lsd.sg};
+  }();
   cvl<T, C> J[SP::count];
   SS S(g);
   cvl<T, C> V;

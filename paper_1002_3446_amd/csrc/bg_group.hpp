@@ -206,6 +206,54 @@ __device__ __forceinline__ void caxpy_l(T cr, T ci, const cvl<T, C>& y, cvl<T, C
   }
 }
 
+// Covariant span momenta of this lane's components, summed left to right in FP64 over the
+// legs and cast to T; propagators 1/K^2 from the group sum of FP64 partials (the gradients of the
+// largest n, grad_span_table).
+template <int L, int G, typename T>
+struct SpanKGroup {
+  static constexpr int C = 4 / G;
+  const double (&k)[L][C];   // covariant FP64 leg components held by this lane
+  const double (&sg)[C];     // their metric signs
+  // Every use sums afresh: an optimisation barrier on the first term keeps the compiler from merging
+  // the sums of one span over the whole kernel and holding them in registers.
+  template <int A, int B>
+  __device__ __forceinline__ void sum(double d[C]) const {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      d[c] = k[A][c];
+      opaque(d[c]);
+    }
+    static_for<A + 1, B + 1>([&](auto t) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) d[c] += k[decltype(t)::value][c];
+    });
+  }
+  template <int A, int B>
+  __device__ __forceinline__ void K(T (&out)[C]) const {
+    double d[C];
+    sum<A, B>(d);
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[c] = T(d[c]);
+  }
+  template <int A, int B>
+  __device__ __forceinline__ T prop() const {
+    double d[C];
+    sum<A, B>(d);
+    double part;
+    {
+#pragma clang fp contract(off)
+      part = sg[0] * (d[0] * d[0]);
+#pragma unroll
+      for (int c = 1; c < C; ++c) part = part + sg[c] * (d[c] * d[c]);
+    }
+    const double k2 = group_sum<G>(part);
+    if constexpr (std::is_same<T, float>::value)
+      return __builtin_amdgcn_rcpf(float(k2));
+    else
+      return 1.0 / k2;
+  }
+};
+
 // Covariant span momenta and propagators, read from a per-workgroup LDS table filled once per
 // event: for every span of 2..L-1 legs this lane's components, summed left to right in FP64 over
 // its legs and cast to T, and 1/K^2 from the group sum of the FP64 partials.  Layout [span][lane]

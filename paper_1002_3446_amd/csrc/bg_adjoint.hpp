@@ -573,8 +573,8 @@ constexpr bool grad_dist_scalars() {
 // n = 8: 20892 instructions a wave).
 // Whether its span momenta and propagators come from the LDS table: where the sweep spills without
 // it too, what the table brings into registers spills more than the sums cost (us, sums / table:
-// FP64 n = 11, 6 10^4 events 1538 / 1579, n = 12, 8 10^4 3212 / 3408; FP32 n = 12, 10^5 1381 / 1406, but n = 11
-// 1011 / 913; FP64 n = 8, 10^5 566 / 497).
+// FP64 n = 11, 6 10^4 events 1465 / 1579, n = 12, 8 10^4 3024 / 3408; FP32 n = 12, 10^5 1322 / 1406; where it
+// fits, n = 8 FP32, 2^20, this kernel alone 1730 / 1517).
 template <int N, typename T>
 constexpr bool grad_span_table() { return sizeof(T) == 8 ? N <= 8 : N <= 11; }
 

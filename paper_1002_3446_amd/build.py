@@ -110,7 +110,10 @@ def units_for(ns, precs=(32, 64), kinds=KINDS):
              (os.path.join(CSRC, "bg_hist.hip"), os.path.join(OUT_DIR, "bg_hist.o"), [], 0),
              (os.path.join(CSRC, "bg_probe.hip"), os.path.join(OUT_DIR, "bg_probe.o"), [], 0)]
     if set(range(4, 13)) <= set(ns) and 32 in precs:
-        units.append((os.path.join(CSRC, "bg_multi.hip"), os.path.join(OUT_DIR, "bg_multi_p32.o"), [], 1000))
+        units.append((os.path.join(CSRC, "bg_multi.hip"), os.path.join(OUT_DIR, "bg_multi_p32.o"),
+                      # without the pre-RA scheduler, as unit_flags: its large-n paths spill less (n = 4..12 with
+                      # 2^26 / 2^n events each, one persistent launch: 1838 / 1587 us; 2^20 / 2^n: 569 / 548)
+                      ["-mllvm", "-enable-misched=0"], 1000))
     for n in ns:
         for p in precs:
             for k in kinds:

@@ -101,8 +101,9 @@ struct GenWork {
                      // only (PassList); NULL: on every event
 };
 
-// Words of a PassList over cap events (a multiple of 64): one mask per 64 events, then their count.
-constexpr int64_t pass_words(int64_t cap) { return cap / 64 + 1; }
+// Words of a PassList over cap events (a multiple of 64): one mask per 64 events, then their count; whole
+// lines of 256 B, as another class's staging may follow.
+constexpr int64_t pass_words(int64_t cap) { return (cap / 64 + 1 + 31) / 32 * 32; }
 // The list of a chunk of cnt events from its masks, into word `word` of the staging slots of `words`
 // words; the count behind the masks of W.stage_cap events.
 hipError_t launch_pass_list(const GenWork& W, int64_t cnt, int word, int words, hipStream_t s);

@@ -62,20 +62,28 @@ __host__ __device__ __forceinline__ double sqrt_fp64(double x) {
 #endif
 }
 
-// 1 / sqrt(x) of a normal positive x within about one ulp: two Newton steps on the hardware's
-// estimate (x = 0 gives no number).
+// 1 / sqrt(x) of a normal positive x, closer than the quotient of the rounded root (two Newton steps on
+// the hardware's estimate, the second with the residual 1 - x y^2 to twice the precision; x = 0 gives
+// no number).  The host starts from an FP32 estimate, which two steps bring as far.
 __host__ __device__ __forceinline__ double rsqrt_fp64(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const double g = x * y;
-    y = std::fma(0.5 * y, std::fma(-g, y, 1.0), y);
-  }
-  return y;
 #else
-  return 1.0 / std::sqrt(x);
+  int e = 0;
+  const double m = std::frexp(x, &e);  // x = m 2^e, the root of an even power of two is exact
+  double y = std::ldexp((double)(1.0f / std::sqrt((float)((e & 1) ? 2.0 * m : m))), -((e & 1) ? e - 1 : e) / 2);
 #endif
+  double g = x * y;
+  y = std::fma(0.5 * y, std::fma(-g, y, 1.0), y);
+  g = x * y;
+  const double low = std::fma(x, y, -g);
+  return std::fma(0.5 * y, std::fma(-low, y, std::fma(-g, y, 1.0)), y);
+}
+
+// sqrt(x) from y = rsqrt_fp64(x)
+__host__ __device__ __forceinline__ double sqrt_refined(double x, double y) {
+  const double g = x * y;
+  return std::fma(0.5 * y, std::fma(-g, g, x), g);
 }
 
 // ln 2 as a 42-bit head (so that e * head is exact for every binary exponent e of a double)

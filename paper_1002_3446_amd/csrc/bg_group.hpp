@@ -547,10 +547,11 @@ __device__ __forceinline__ cvp pair_signed(double sg, const cvp& x) {
   return s;
 }
 
-// Half the bracket sum of span [A..B] and its -S/2; KP is the span's momentum.
+// Half the bracket sum of span [A..B] and its -S/2 (in the order of span_vertex_d, but for the pairs beside
+// their left current's brackets from n = 9); KP: the span's momentum.
 template <int L, int A, int B>
 __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (&J)[Spans<L>::count],
-                                              const double (&KP)[2], cvp& X, double& sr, double& si) {
+                                              double (&KP)[2], cvp& X, double& sr, double& si) {
 #pragma clang fp contract(off)
   using SP = Spans<L>;
 #pragma unroll
@@ -558,40 +559,6 @@ __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (
   sr = 0.0;
   si = 0.0;
   constexpr bool kApart = L == 6 || L == 7;  // n = 7, 8: the order of span_vertex_pairs
-  double ka[2];
-  static_for<A, B>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
-    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
-    double kb[2];
-    if constexpr (i == A)
-      ks.template sum<A, A>(ka);
-    else
-      ks.template add<i>(ka);
-    ks.template sum<i + 1, B>(kb);
-    const cvp xs = pair_signed<LA>(ks.sg, J[PA]);
-    double dr, di, ar, ai, br, bi;
-    pdot<LA, LB>(xs, J[PB], dr, di);
-    prdot<LA>(J[PA], kb, ar, ai);
-    prdot<LB>(J[PB], ka, br, bi);
-    paxpy<LB>(ar, ai, J[PB], X);
-    paxpy<LA>(-br, -bi, J[PA], X);
-    const double d0 = ks.sg * fmac(-0.5, KP[0], ka[0]), d1 = fmac(0.5, KP[1], -ka[1]);
-    X.re[0] = fmac(dr, d0, X.re[0]);
-    X.im[0] = fmac(di, d0, X.im[0]);
-    X.re[1] = fmac(dr, d1, X.re[1]);
-    X.im[1] = fmac(di, d1, X.im[1]);
-    sr = fmac(-0.5, dr, sr);
-    si = fmac(-0.5, di, si);
-    // the four-gluon pairs of this left current
-    if constexpr (!kApart)
-      static_for<i + 1, B>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        double er, ei;
-        pdot<LA, j + 1 == B>(xs, J[SP::at(j + 1, B)], er, ei);
-        paxpy<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
-      });
-  });
   if constexpr (kApart)
     static_for<A, B - 1>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
@@ -613,6 +580,45 @@ __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (
     const double2 c = ks.template scalar<SP::at(i + 1, B)>();
     paxpy<i == A>(c.x, c.y, J[SP::at(A, i)], X);
   });
+  double ka[2];
+  static_for<A, B>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr int PA = SP::at(A, i), PB = SP::at(i + 1, B);
+    constexpr bool LA = i == A, LB = i + 1 == B;  // leaves
+    double kb[2];
+    if constexpr (i == A)
+      ks.template sum<A, A>(ka);
+    else
+      ks.template add<i>(ka);
+    ks.template sum<i + 1, B>(kb);
+    const cvp xs = pair_signed<LA>(ks.sg, J[PA]);
+    double dr, di, ar, ai, br, bi;
+    pdot<LA, LB>(xs, J[PB], dr, di);
+    dr *= 0.5;
+    di *= 0.5;
+    prdot<LA>(J[PA], kb, ar, ai);
+    prdot<LB>(J[PB], ka, br, bi);
+    paxpy<LB>(ar, ai, J[PB], X);
+    paxpy<LA>(-br, -bi, J[PA], X);
+    const double d0 = ks.sg * (ka[0] - kb[0]), d1 = kb[1] - ka[1];
+    X.re[0] = fmac(dr, d0, X.re[0]);
+    X.im[0] = fmac(di, d0, X.im[0]);
+    X.re[1] = fmac(dr, d1, X.re[1]);
+    X.im[1] = fmac(di, d1, X.im[1]);
+    sr -= dr;
+    si -= di;
+    // the four-gluon pairs of this left current
+    if constexpr (!kApart)
+      static_for<i + 1, B>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        double er, ei;
+        pdot<LA, j + 1 == B>(xs, J[SP::at(j + 1, B)], er, ei);
+        paxpy<i + 1 == j>(er, ei, J[SP::at(i + 1, j)], X);
+      });
+  });
+  ks.template add<B>(ka);
+  KP[0] = ka[0];
+  KP[1] = ka[1];
 }
 
 template <int L>
@@ -628,7 +634,6 @@ __device__ __forceinline__ void bg_amplitude_p(const PairSpan<L>& ks, const cvp 
       asm volatile("" ::: "memory");  // momenta and scalars are read afresh in every span
       cvp X;
       double sr, si, K[2];
-      ks.template sum<a, b>(K);
       span_vertex_p<L, a, b>(ks, J, K, X, sr, si);
       double part;
       {
@@ -647,7 +652,6 @@ __device__ __forceinline__ void bg_amplitude_p(const PairSpan<L>& ks, const cvp 
   asm volatile("" ::: "memory");
   cvp X;
   double sr, si, K[2], mr, mi;
-  ks.template sum<0, L - 1>(K);
   span_vertex_p<L, 0, L - 1>(ks, J, K, X, sr, si);
   pdot<true, false>(pair_signed<true>(ks.sg, eps0), X, mr, mi);
   m_re = 2.0 * mr;
@@ -718,13 +722,23 @@ __device__ __forceinline__ void qaxpy(double cr, double ci, const cvq& y, cvq& a
   acc.im = fmac(ci, y.re, fmac(cr, y.im, acc.im));
 }
 
-// Half the bracket sum of span [A..B] and its -S/2 (as span_vertex_p); KP is the span's momentum.
+// Half the bracket sum of span [A..B] and its -S/2 (as span_vertex_p); KP: the span's momentum.
 template <int L, int A, int B>
-__device__ __forceinline__ void span_vertex_q(const QuadSpan<L>& ks, const cvq (&J)[Spans<L>::count], double KP, cvq& X,
+__device__ __forceinline__ void span_vertex_q(const QuadSpan<L>& ks, const cvq (&J)[Spans<L>::count], double& KP, cvq& X,
                                               double& sr, double& si) {
 #pragma clang fp contract(off)
   using SP = Spans<L>;
   X.re = X.im = sr = si = 0.0;
+  static_for<A + 1, B>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    const double2 s = ks.template scalar<SP::at(A, j)>();
+    qaxpy(s.x, s.y, J[SP::at(j + 1, B)], X);
+  });
+  static_for<A, B - 1>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const double2 s = ks.template scalar<SP::at(i + 1, B)>();
+    qaxpy(s.x, s.y, J[SP::at(A, i)], X);
+  });
   double ka = 0.0;
   static_for<A, B>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
@@ -733,13 +747,15 @@ __device__ __forceinline__ void span_vertex_q(const QuadSpan<L>& ks, const cvq (
     const double kb = ks.template sum<i + 1, B>();
     double dr, di, ar, ai, br, bi;
     ks.dot(J[PA], J[PB], dr, di);
+    dr *= 0.5;
+    di *= 0.5;
     ks.rdot(J[PA], kb, ar, ai);
     ks.rdot(J[PB], ka, br, bi);
-    const double dk = ks.sg * fmac(-0.5, KP, ka);
+    const double dk = ks.sg * (ka - kb);
     X.re = fmac(dr, dk, X.re);
     X.im = fmac(di, dk, X.im);
-    sr = fmac(-0.5, dr, sr);
-    si = fmac(-0.5, di, si);
+    sr -= dr;
+    si -= di;
     // the four-gluon pairs of this left current; each sum is used one product after it was
     // issued, so that its latency is covered in the order written (the unit is built without the
     // pre-RA scheduler)
@@ -764,16 +780,7 @@ __device__ __forceinline__ void span_vertex_q(const QuadSpan<L>& ks, const cvq (
       qaxpy(-br, -bi, J[PA], X);
     }
   });
-  static_for<A + 1, B>([&](auto jc) {
-    constexpr int j = decltype(jc)::value;
-    const double2 s = ks.template scalar<SP::at(A, j)>();
-    qaxpy(s.x, s.y, J[SP::at(j + 1, B)], X);
-  });
-  static_for<A, B - 1>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    const double2 s = ks.template scalar<SP::at(i + 1, B)>();
-    qaxpy(s.x, s.y, J[SP::at(A, i)], X);
-  });
+  KP = ka + ks.template sum<B, B>();
 }
 
 template <int L>
@@ -789,7 +796,7 @@ __device__ __forceinline__ void bg_amplitude_q(const QuadSpan<L>& ks, const cvq 
       asm volatile("" ::: "memory");  // momenta and scalars are read afresh in every span
       cvq X;
       double sr, si;
-      const double K = ks.template sum<a, b>();
+      double K;
       span_vertex_q<L, a, b>(ks, J, K, X, sr, si);
       const double prop = 2.0 / quad_sum(ks.sg, K * K);
       J[s].re = X.re * prop;
@@ -799,8 +806,8 @@ __device__ __forceinline__ void bg_amplitude_q(const QuadSpan<L>& ks, const cvq 
   });
   asm volatile("" ::: "memory");
   cvq X;
-  double sr, si, mr, mi;
-  span_vertex_q<L, 0, L - 1>(ks, J, ks.template sum<0, L - 1>(), X, sr, si);
+  double sr, si, K, mr, mi;
+  span_vertex_q<L, 0, L - 1>(ks, J, K, X, sr, si);
   ks.dot(eps0, X, mr, mi);
   m_re = 2.0 * mr;
   m_im = 2.0 * mi;

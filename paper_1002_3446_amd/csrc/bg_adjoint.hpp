@@ -320,16 +320,21 @@ __device__ __forceinline__ void rambo_init_adj(const RamboMap& m, const double Q
   for (int j = 0; j < 3; ++j) Qb[j + 1] += -2.0 * Q[j + 1] * M2b;
 }
 
-// Adjoint of rambo_q: rho adjoints from q and its adjoints, without the angles (q holds them):
-// d q / d phi = (0, -q2, q1, 0), d q / d c = q0 (0, -c cos phi / st, -c sin phi / st, 1), q / q0 for
-// d q / d q0, and st^2 = 1 - c^2.
-__device__ __forceinline__ void rambo_q_adj(double r1, double r3, double r4, const double q[4], const double qb[4],
-                                            double rb[4]) {
+// Adjoint of rambo_q: rho adjoints from q adjoints, with no division by q0 (zero where r3 r4 = 1);
+// at r1 = 0 or 1 the derivative in r1 is infinite and the others are finite.
+__host__ __device__ __forceinline__ void rambo_q_adj(double r1, double r2, double r3, double r4, const double qb[4],
+                                                     double rb[4]) {
   const double c = 2.0 * r1 - 1.0;
-  const double across = q[1] * qb[1] + q[2] * qb[2];
-  const double q0b = qb[0] + (across + q[3] * qb[3]) / q[0];
-  rb[0] = 2.0 * (q[0] * qb[3] - across * c / (1.0 - c * c));
-  rb[1] = 2.0 * 3.14159265358979323846 * (q[1] * qb[2] - q[2] * qb[1]);
+  const double st = sqrt_fp64(1.0 - c * c);
+  double sp, cp;
+  sincospi_fp64(2.0 * r2, &sp, &cp);
+  const double q0 = -log_fp64(r3 * r4);
+  const double q0b = qb[0] + qb[1] * st * cp + qb[2] * st * sp + qb[3] * c;
+  const double stb = q0 * (qb[1] * cp + qb[2] * sp);
+  const double cpb = q0 * st * qb[1], spb = q0 * st * qb[2];
+  const double cb = q0 * qb[3] - stb * c / st;
+  rb[0] = 2.0 * cb;
+  rb[1] = 2.0 * 3.14159265358979323846 * (cp * spb - sp * cpb);
   rb[2] = -q0b / r3;
   rb[3] = -q0b / r4;
 }
@@ -468,7 +473,7 @@ __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const Gr
       double qbt[4], rb[4];
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) qbt[mu] = qb[t][mu] + Qb[mu];
-      rambo_q_adj(u[0], u[2], u[3], K.q[t], qbt, rb);
+      rambo_q_adj(u[0], u[1], u[2], u[3], qbt, rb);
 #pragma unroll
       for (int c = 0; c < 4; ++c) u[c] = gw * rb[c];
     }

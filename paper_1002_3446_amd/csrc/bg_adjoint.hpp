@@ -238,27 +238,29 @@ __device__ __forceinline__ void bg_reverse(const double (&k)[L][4], const cv4<T>
 }
 
 // Adjoint of polarisation(): accumulates dL/dp (spatial components) from the adjoints of the
-// source's words that are not identically zero (re[1..3], im[1], im[2]).  With the unit vectors
-// along and across the polar angle, t = (ct cf, ct sf, -st) and f = (-sf, cf, 0):
-//   d(ct) = -st (t.dp) / |p|,  d(st) = ct (t.dp) / |p|,  d(cf) = -sf (f.dp) / pT,  d(sf) = cf (f.dp) / pT.
-// (Written with two reciprocal roots; a division per term took 14 divisions a leg, a quarter of
-// the second gradient kernel.)
-__device__ __forceinline__ void polarisation_adj(const double p[4], bool plus, const double (&er)[4],
-                                                 const double (&ei)[4], double pb[4]) {
+// source's words that are not identically zero (re[1..3], im[1], im[2]).  Every coefficient is one
+// rounded quotient of products (the quotients by one number share its reciprocal): along and across the
+// polar angle with reciprocal roots, the result was 1.5 times further from its exact value.
+__host__ __device__ __forceinline__ void polarisation_adj(const double p[4], bool plus, const double (&er)[4],
+                                                          const double (&ei)[4], double pb[4]) {
   const double px = p[1], py = p[2], pz = p[3];
   const double pt2 = px * px + py * py;
   if (!(pt2 > 0.0)) return;  // a leg along the beam axis: its direction is fixed
-  const double ipa = rsqrt_fp64(pt2 + pz * pz), ipt = rsqrt_fp64(pt2);
-  const double ct = pz * ipa, st = (pt2 * ipt) * ipa, cf = px * ipt, sf = py * ipt;
-  const double r = 0.70710678118654752440, hr = plus ? r : -r;
-  const double ctb = -hr * (cf * er[1] + sf * er[2]);
-  const double stb = hr * er[3];
-  const double cfb = -hr * ct * er[1] - r * ei[2];
-  const double sfb = r * ei[1] - hr * ct * er[2];
-  const double tb = (stb * ct - ctb * st) * ipa, fb = (sfb * cf - cfb * sf) * ipt;
-  pb[1] += tb * (ct * cf) - fb * sf;
-  pb[2] += tb * (ct * sf) + fb * cf;
-  pb[3] -= tb * st;
+  const double pa = sqrt_fp64(pt2 + pz * pz), pt = sqrt_fp64(pt2), ipt = recip_refine(pt);
+  const double ct = div_fp64(pz, pa), cf = div_refined(px, pt, ipt), sf = div_refined(py, pt, ipt);
+  const double r = 0.70710678118654752440;
+  const double hs = plus ? 1.0 : -1.0;
+  const double ctb = -hs * r * (cf * er[1] + sf * er[2]);
+  const double stb = hs * r * er[3];
+  const double cfb = -hs * r * ct * er[1] - r * ei[2];
+  const double sfb = r * ei[1] - hs * r * ct * er[2];
+  const double a3 = pa * pa * pa, t3 = pt2 * pt, m3 = pt * a3;
+  const double ia3 = recip_refine(a3), it3 = recip_refine(t3), im3 = recip_refine(m3);
+  pb[1] += ctb * div_refined(-pz * px, a3, ia3) + stb * div_refined(px * pz * pz, m3, im3) +
+           cfb * div_refined(py * py, t3, it3) + sfb * div_refined(-px * py, t3, it3);
+  pb[2] += ctb * div_refined(-pz * py, a3, ia3) + stb * div_refined(py * pz * pz, m3, im3) +
+           cfb * div_refined(-px * py, t3, it3) + sfb * div_refined(px * px, t3, it3);
+  pb[3] += ctb * div_refined(pt2, a3, ia3) + stb * div_refined(-pt * pz, a3, ia3);
 }
 
 struct RamboMapAdj {
@@ -298,23 +300,23 @@ __device__ __forceinline__ void rambo_apply_adj(const RamboMap& m, const double 
   A.bzb += bb[2];
 }
 
-// Adjoint of RamboMap::init: accumulates dL/dQ and dL/dsqrt(s_hat).
-__device__ __forceinline__ void rambo_init_adj(const RamboMap& m, const double Q[4], const RamboMapAdj& A,
-                                               double Qb[4], double& sb) {
-  const double iM = m.iM;
-  sb += A.Xb * iM;
-  double Mb = -A.Xb * m.X * iM;
+// Adjoint of RamboMap::init: accumulates dL/dQ and dL/dsqrt(s_hat); every quotient by M rounded.
+__host__ __device__ __forceinline__ void rambo_init_adj(const RamboMap& m, const double Q[4], const RamboMapAdj& A,
+                                                        double Qb[4], double& sb) {
+  const double M = sqrt_fp64(Q[0] * Q[0] - Q[1] * Q[1] - Q[2] * Q[2] - Q[3] * Q[3]), iM = recip_refine(M);
+  sb += div_refined(A.Xb, M, iM);
+  double Mb = div_refined(-A.Xb * m.X, M, iM);
   const double gammab = A.gammab - A.ab * m.a * m.a;
-  Qb[0] += gammab * iM;
-  Mb += -gammab * m.gamma * iM;
+  Qb[0] += div_refined(gammab, M, iM);
+  Mb += div_refined(-gammab * m.gamma, M, iM);
   const double b[3] = {m.bx, m.by, m.bz};
   const double bb[3] = {A.bxb, A.byb, A.bzb};
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    Qb[j + 1] += -bb[j] * iM;
-    Mb += -bb[j] * b[j] * iM;
+    Qb[j + 1] += div_refined(-bb[j], M, iM);
+    Mb += div_refined(-bb[j] * b[j], M, iM);
   }
-  const double M2b = 0.5 * Mb * iM;
+  const double M2b = div_refined(0.5 * Mb, M, iM);
   Qb[0] += 2.0 * Q[0] * M2b;
 #pragma unroll
   for (int j = 0; j < 3; ++j) Qb[j + 1] += -2.0 * Q[j + 1] * M2b;

@@ -363,10 +363,10 @@ __device__ __forceinline__ void rambo_q(double r1, double r2, double r3, double 
 }
 
 struct RamboMap {
-  double bx, by, bz, gamma, a, X, iM;  // iM = 1 / M
-  __device__ __forceinline__ void init(const double Q[4], double sqrt_shat) {
+  double bx, by, bz, gamma, a, X;
+  __host__ __device__ __forceinline__ void init(const double Q[4], double sqrt_shat) {
     const double M = sqrt_fp64(Q[0] * Q[0] - Q[1] * Q[1] - Q[2] * Q[2] - Q[3] * Q[3]);
-    iM = div_fp64(1.0, M);
+    const double iM = div_fp64(1.0, M);
     bx = -Q[1] * iM;
     by = -Q[2] * iM;
     bz = -Q[3] * iM;

@@ -70,3 +70,56 @@ def test_rambo_q_adj_at_the_edges(adjoints):
     assert np.isfinite(got[:3, 1:]).all() and np.isfinite(got[2]).all(), got
     want = [-(qb[0] + c * qb[3]) / 0.3 for c in (-1.0, 1.0)]
     assert np.allclose(got[:2, 2], want, rtol=1e-15, atol=0)
+
+
+def source_adj(p, h, er, ei, t):
+    """d(Re e . er + Im e . ei) of the helicity source e(p) in px, py, pz: the derivatives of the polar
+    and azimuthal cosines and sines, each a quotient of products."""
+    px, py, pz = p.astype(t).T
+    e1, e2, e3 = er.astype(t).T
+    i1, i2 = ei.astype(t).T
+    r, h = np.sqrt(t(0.5)), h.astype(t)
+    pt2 = px * px + py * py
+    pa, pt = np.sqrt(pt2 + pz * pz), np.sqrt(pt2)
+    ct, cf, sf = pz / pa, px / pt, py / pt
+    ctb, stb = -h * r * (cf * e1 + sf * e2), h * r * e3
+    cfb, sfb = -h * r * ct * e1 - r * i2, r * i1 - h * r * ct * e2
+    pa3, pt3 = pa * pa * pa, pt2 * pt
+    return np.stack([ctb * (-pz * px / pa3) + stb * (px * pz * pz / (pt * pa3)) + cfb * (py * py / pt3) + sfb * (-px * py / pt3),
+                     ctb * (-pz * py / pa3) + stb * (py * pz * pz / (pt * pa3)) + cfb * (-px * py / pt3) + sfb * (px * px / pt3),
+                     ctb * (pt2 / pa3) + stb * (-pt * pz / pa3)], -1)
+
+
+def test_polarisation_adj(adjoints):
+    rng = np.random.default_rng(6)
+    p = rng.normal(size=(40000, 3)) * 100.0
+    h, er, ei = rng.choice([-1.0, 1.0], 40000), rng.normal(size=(40000, 3)), rng.normal(size=(40000, 2))
+    size = np.hypot(p[:, 0], p[:, 1])[:, None]   # the derivative falls as 1 / pT
+    exact = source_adj(p, h, er, ei, LD) * size
+    got = rms(adjoints("P", np.concatenate([p, h[:, None], er, ei], 1)) * size, exact)
+    plain = rms(source_adj(p, h, er, ei, np.float64) * size, exact)
+    assert (got <= 1.05 * plain).all(), (got, plain)
+
+
+def init_adj(Q, rs, A, t):
+    """Adjoint of b = -Q / M, gamma = Q0 / M, a = 1 / (1 + gamma), X = sqrt(s) / M in Q and sqrt(s)."""
+    Q, rs, A = Q.astype(t), rs.astype(t), A.astype(t)
+    bb, gb, ab, Xb = A[:, :3], A[:, 3], A[:, 4], A[:, 5]
+    M = np.sqrt(Q[:, 0] ** 2 - Q[:, 1] ** 2 - Q[:, 2] ** 2 - Q[:, 3] ** 2)
+    b, g, X = -Q[:, 1:] / M[:, None], Q[:, 0] / M, rs / M
+    gb = gb - ab / ((1 + g) * (1 + g))
+    Mb = -Xb * X / M - gb * g / M - (bb * b / M[:, None]).sum(1)
+    m2 = Mb / (2 * M)
+    return np.concatenate([(gb / M + 2 * Q[:, 0] * m2)[:, None], -bb / M[:, None] - 2 * Q[:, 1:] * m2[:, None],
+                           (Xb / M)[:, None]], 1)
+
+
+def test_rambo_init_adj(adjoints):
+    rng = np.random.default_rng(7)
+    q = rng.normal(size=(40000, 6, 3)) * rng.exponential(2.0, (40000, 6, 1))
+    Q = np.concatenate([np.sqrt((q * q).sum(-1)).sum(1)[:, None], q.sum(1)], 1)
+    rs, A = rng.uniform(200.0, 5000.0, 40000), rng.normal(size=(40000, 6))
+    exact = init_adj(Q, rs, A, LD)
+    got = rms(adjoints("I", np.concatenate([Q, rs[:, None], A], 1)), exact)
+    plain = rms(init_adj(Q, rs, A, np.float64), exact)
+    assert (got <= 1.05 * plain).all(), (got, plain)

@@ -145,13 +145,14 @@ int bg_generate(const bg_config *cfgs, int ncfg, const int64_t *counts,
  * serving loops, harnesses that forbid hipMalloc): bg_generate for ONE class (cfg, count,
  * in, out as bg_generate's entries; in may be NULL) with no allocation and no copy of its
  * own.  Every buffer the call needs lives in a library array that each GPU holds from the
- * first such call until the process ends (about 27 MiB): the inverse-CDF table of the
+ * first such call until the process ends (about 51 MiB): the inverse-CDF table of the
  * density last used (rebuilt by a small kernel when the density changes), the partials of
  * the compensated sums and the split form's staging (chunks of 2^16 events at n = 8, fewer
  * at larger n).  The kernels,
  * the partial layout and their reduction are bg_generate's, so every per-event output and
  * the totals equal bg_generate's bitwise.  count <= 2^24 and at most 2^18 + 1 workgroups
- * (count x lanes per event / workgroup size), else BG_EINVAL.  All calls on
+ * (count x lanes per event / workgroup size, as bg_set_lanes and bg_set_launch have them, also
+ * for the kernels that use 64 lanes whatever is set), else BG_EINVAL.  All calls on
  * one GPU share that array and it keeps the last call's contents: calls that overlap on one
  * GPU (other streams, other threads) race; order them.  Errors as bg_generate. */
 int bg_generate_noalloc(const bg_config *cfg, int64_t count, const bg_inputs *in, const bg_outputs *out,

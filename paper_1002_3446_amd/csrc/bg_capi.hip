@@ -677,7 +677,7 @@ __global__ void k_check_final(int64_t* first_bad) {
 // ----------------------------------------------------------------------------------------
 // Allocation-free generation (bg_generate_noalloc).  Every device buffer such a call needs
 // lives in one file-scope array, `scratch`, which each GPU holds once until the process
-// ends (about 27 MiB): the inverse-CDF table of the density last used, the compensated-sum
+// ends (about 51 MiB): the inverse-CDF table of the density last used, the compensated-sum
 // partials and their second level, and the staging of the split form (chunks of
 // kNoAllocStage events).  Host code never uses the array's name as an address: its device
 // address is looked up once per device (noalloc_scratch) and passed to the kernels.
@@ -685,7 +685,12 @@ __global__ void k_check_final(int64_t* first_bad) {
 constexpr int64_t kNoAllocMaxEvents = int64_t(1) << 24;
 constexpr int64_t kNoAllocStage = int64_t(1) << 16;
 constexpr size_t round256(size_t doubles) { return (doubles + 31) / 32 * 32; }
-constexpr size_t kNoAllocParts = (size_t)(kNoAllocMaxEvents / 64 + 1);  // workgroups of >= 64 events
+// the documented limit on count x lanes / workgroup size, as set (bg_set_lanes, bg_set_launch)
+constexpr size_t kNoAllocGroups = (size_t)(kNoAllocMaxEvents / 64 + 1);
+// partials of the largest call: FP64 groups run in 64-lane workgroups whatever size is set, up to four
+// lanes per event
+constexpr size_t kNoAllocParts = (size_t)(kNoAllocMaxEvents * 4 / kLdsLanes);
+static_assert(kNoAllocParts >= kNoAllocGroups, "every class within the limit has room for its partials");
 constexpr size_t kOffPdf = 0;
 constexpr size_t kOffParts = kOffPdf + round256((size_t)kPdfSegs * 4);
 constexpr size_t kOffLevel2 = kOffParts + round256(kNoAllocParts * 4);
@@ -736,15 +741,12 @@ int bg_generate_noalloc(const bg_config* cfg, int64_t count, const bg_inputs* in
   if (st == BG_OK) st = plan_class(*cfg, G, P);
   if (st != BG_OK) return st;
   if (count == 0) return BG_OK;
-  // the documented limit goes by the settings of lanes and workgroup size
+  // the limit goes by the settings of lanes and workgroup size, whatever the kernels use
   const Shape sh = shape_of(cfg->n, cfg->prec);
   const int setting = P.wform || cfg->polarisation ? 1 : lanes_of(cfg->n, cfg->prec);
   const int sblock = P.wform || (setting == 1 && cfg->prec == 32 && cfg->n <= 8) ? kLdsLanes : sh.block;
-  if ((size_t)((setting * count + sblock - 1) / sblock) > kNoAllocParts) return BG_EINVAL;
-  if ((size_t)P.nblocks > kNoAllocParts) {  // only FP64 groups: the kernels take any workgroup size
-    P.block = sh.block;
-    P.nblocks = (P.lanes * G.count + P.block - 1) / P.block;
-  }
+  if ((size_t)((setting * count + sblock - 1) / sblock) > kNoAllocGroups) return BG_EINVAL;
+  if ((size_t)P.nblocks > kNoAllocParts) return BG_EINVAL;  // (none: see kNoAllocParts)
   NoAllocDevice* D = nullptr;
   if ((st = noalloc_device(&D)) != BG_OK) return st;
   hipStream_t s = (hipStream_t)stream;

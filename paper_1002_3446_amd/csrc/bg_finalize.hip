@@ -63,47 +63,46 @@ __global__ __launch_bounds__(256) void k_finalize(const double* __restrict__ lev
 }
 
 // Both levels in one workgroup of four 256-lane quarters, for at most kOneLaunchRuns runs of 256
-// partials: quarter q reduces runs q, q + 4, ... in the order of level 1, then the first wave takes
-// the run results as level 2 does, so the sums are bitwise those of the two launches.  A launch
-// costs 2.7 us of host time and leaves a gap of as much on the device; beyond 16 runs (2^18
-// events in one-wave workgroups) one compute unit's loads cost more than that.
-constexpr int kOneLaunchRuns = 16;
+// partials: quarter q reduces run q in the order of level 1, then the first wave takes the run
+// results as level 2 does, so the sums are bitwise those of the two launches.  A launch costs 2.7 us of
+// host time and leaves a gap of as much on the device; a second run for each quarter costs more
+// than that (n = 4 FP32 calls with 512, 1024, 2048, 4096 partials, us: up to 16 runs in one launch
+// 15.9, 16.4, 20.8, 32.1; from 5 runs in two 15.8, 16.4, 18.5, 22.9).
+constexpr int kOneLaunchRuns = 4;
 
 __global__ __launch_bounds__(1024) void k_finalize_small(const double* __restrict__ partials, int64_t nparts, double* acc) {
   __shared__ double red[16][4], run[kOneLaunchRuns][4];
   const int t = threadIdx.x & 255, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = threadIdx.x >> 8;
   const int nruns = (int)((nparts + 255) / 256);
-  for (int r0 = 0; r0 < nruns; r0 += 4) {
-    const int64_t p = (int64_t)(r0 + quarter) * 256 + t;
-    CSum a{0.0, 0.0}, b{0.0, 0.0};
-    if (p < nparts) {
-      a = cs_add(a, CSum{partials[4 * p], partials[4 * p + 1]});
-      b = cs_add(b, CSum{partials[4 * p + 2], partials[4 * p + 3]});
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      a = cs_add(a, CSum{__shfl_down(a.s, off), __shfl_down(a.c, off)});
-      b = cs_add(b, CSum{__shfl_down(b.s, off), __shfl_down(b.c, off)});
-    }
-    if (lane == 0) {
-      red[wave][0] = a.s; red[wave][1] = a.c; red[wave][2] = b.s; red[wave][3] = b.c;
-    }
-    __syncthreads();
-    if (t == 0 && r0 + quarter < nruns) {
-      const int w0 = 4 * quarter;
-      a = CSum{red[w0][0], red[w0][1]};
-      b = CSum{red[w0][2], red[w0][3]};
-      for (int v = 1; v < 4; ++v) {
-        a = cs_add(a, CSum{red[w0 + v][0], red[w0 + v][1]});
-        b = cs_add(b, CSum{red[w0 + v][2], red[w0 + v][3]});
-      }
-      double* d = run[r0 + quarter];
-      d[0] = a.s; d[1] = a.c; d[2] = b.s; d[3] = b.c;
-    }
-    __syncthreads();
-  }
-  if (wave != 0) return;
+  const int64_t p = (int64_t)quarter * 256 + t;
   CSum a{0.0, 0.0}, b{0.0, 0.0};
+  if (p < nparts) {
+    a = cs_add(a, CSum{partials[4 * p], partials[4 * p + 1]});
+    b = cs_add(b, CSum{partials[4 * p + 2], partials[4 * p + 3]});
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    a = cs_add(a, CSum{__shfl_down(a.s, off), __shfl_down(a.c, off)});
+    b = cs_add(b, CSum{__shfl_down(b.s, off), __shfl_down(b.c, off)});
+  }
+  if (lane == 0) {
+    red[wave][0] = a.s; red[wave][1] = a.c; red[wave][2] = b.s; red[wave][3] = b.c;
+  }
+  __syncthreads();
+  if (t == 0 && quarter < nruns) {
+    const int w0 = 4 * quarter;
+    a = CSum{red[w0][0], red[w0][1]};
+    b = CSum{red[w0][2], red[w0][3]};
+    for (int v = 1; v < 4; ++v) {
+      a = cs_add(a, CSum{red[w0 + v][0], red[w0 + v][1]});
+      b = cs_add(b, CSum{red[w0 + v][2], red[w0 + v][3]});
+    }
+    double* d = run[quarter];
+    d[0] = a.s; d[1] = a.c; d[2] = b.s; d[3] = b.c;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  a = b = CSum{0.0, 0.0};
   if (lane < nruns) {
     a = cs_add(a, CSum{run[lane][0], run[lane][1]});
     b = cs_add(b, CSum{run[lane][2], run[lane][3]});

@@ -227,7 +227,7 @@ int bg_check_events(int n, int64_t N, const uint32_t *hel, const uint8_t *order,
                     void *stream);
 
 /* Launch shape for one (n, prec) class: threads per workgroup (64, 128, 192 or 256; the kernels of
- * n <= 8 and of FP64 with helicity states use 64) and
+ * n <= 8 and of FP64 with helicity states use 64, or 256 in some short calls) and
  * events per lane in one tile of the persistent multi-class launch (1..64; a tile holds
  * block * tile_iters events).  The autotuner writes these; (0, 0) restores the built-in
  * default.  Affects speed only: per-event outputs are identical for every shape, totals

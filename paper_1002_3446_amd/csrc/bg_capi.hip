@@ -545,6 +545,18 @@ struct ClassPlan {
   GenerateFn fn;
 };
 
+// Lanes per workgroup of generation with FP64 groups.  One wave: their LDS leaves whole workgroups of one
+// wave the best fit (n = 12 with four lanes, 2^18 events: 868 us in workgroups of 64, 913 in 128; n = 9
+// with two 272 against 279).  But where four lanes per event give every compute unit three or four waves,
+// the workgroups have four: two waves of that form fit a SIMD, and workgroups of one wave, which start while
+// the kinematics drain, are put two on a SIMD while others stand idle.  us, one wave / four, n = 10, 12: 8192
+// events (two waves per unit) 54 / 55, 95 / 98; 10000 73 / 55, 115 / 98; 16384 75 / 56, 135 / 108.
+int group_block(int lanes, int64_t count) {
+  if (lanes != 4) return kLdsLanes;
+  const int64_t unit = (int64_t)cu_count() * kLdsLanes;  // lanes of one wave per compute unit
+  return lanes * count > 2 * unit && lanes * count <= 4 * unit ? 4 * kLdsLanes : kLdsLanes;
+}
+
 int plan_class(const bg_config& c, const GenClass& G, ClassPlan& P) {
   const Launchers* L = table(c.n, c.prec);
   P.wform = !c.polarisation && form_of(c.n, c.prec) == 1;
@@ -560,9 +572,9 @@ int plan_class(const bg_config& c, const GenClass& G, ClassPlan& P) {
   // staged: the W-tensor form, the split table classes, and every grouped form (kinematics in
   // their own kernel, one lane per event, instead of on every lane of a group)
   P.staged = P.wform || (table_class && split_form(c.n, c.prec)) || P.lanes > 1;
-  // FP64 groups too: their LDS leaves whole workgroups of one wave the best fit (n = 12 with four
-  // lanes, 2^18 events: 868 us in workgroups of 64, 913 in 128; n = 9 with two 272 against 279)
-  P.block = P.wform || table_class || (P.lanes > 1 && c.prec == 64) ? kLdsLanes : shape_of(c.n, c.prec).block;
+  P.block = P.wform || table_class ? kLdsLanes
+                                   : (P.lanes > 1 && c.prec == 64 ? group_block(P.lanes, G.count)
+                                                                  : shape_of(c.n, c.prec).block);
   P.nblocks = (P.lanes * G.count + P.block - 1) / P.block;
   return BG_OK;
 }
@@ -1050,7 +1062,7 @@ int bg_amp2(int n, int prec, int64_t N, const double* mom, const uint32_t* hel, 
   if (!f) return BG_ENOTSUP;
   if (N == 0) return BG_OK;
   if (!mom || !hel || !order || !amp2_out) return BG_EINVAL;
-  const int block = prec == 64 && n >= 7 ? kLdsLanes : shape_of(n, prec).block;  // as plan_class
+  const int block = prec == 64 && n >= 7 ? kLdsLanes : shape_of(n, prec).block;
   return from_hip(f(N, mom, hel, order, amp2_out, block, (hipStream_t)stream));
 }
 

@@ -203,6 +203,18 @@ __device__ __forceinline__ float azimuth_f32(float y, float x) {
   return copysignf(r, y);
 }
 
+// Whether FP32 decides the cut |eta| < eta_max of a jet with the pseudorapidity e: 1 it fails, -1 it
+// passes, 0 within the error (left to FP64).  No cut at all (infinity, or anything beyond 1e30, which
+// no pseudorapidity reaches) counts as 1e30: the difference to infinity would never decide, and
+// every jet went through FP64 (1.8 us of 65 and 79 at n = 7, 8 FP32, 131072 events).
+__host__ __device__ __forceinline__ int eta_side(float e, float eta_max) {
+#pragma clang fp contract(off)
+  eta_max = eta_max > 1e30f ? 1e30f : eta_max;
+  const float d = fabsf(e) - eta_max;
+  if (d >= 2.0f * kAngleErr + 1e-6f * eta_max) return 1;
+  return d < -2.0f * kAngleErr - 1e-6f * eta_max ? -1 : 0;
+}
+
 // Delta R^2 of two jets; no fused multiply-adds: every form of the cuts rounds exactly as written
 __device__ __forceinline__ double delta_r2(double eta_a, double phi_a, double eta_b, double phi_b) {
 #pragma clang fp contract(off)
@@ -270,9 +282,9 @@ __device__ __forceinline__ bool cuts(const GenClass& C, const EventKin<N>& ev, P
       eta[p] = copysignf(e, (float)m[3]);
       phi[p] = azimuth_f32((float)m[2], (float)m[1]);
       ok = ok && (pt > C.pt_min);
-      const float d = fabsf(e) - eta_max;
-      ok = ok && !(fine && d >= 2.0f * kAngleErr + 1e-6f * eta_max);
-      near |= ((fine && d < -2.0f * kAngleErr - 1e-6f * eta_max) || !ok) ? 0u : 1u << p;
+      const int side = fine ? eta_side(e, eta_max) : 0;
+      ok = ok && side <= 0;
+      near |= (side < 0 || !ok) ? 0u : 1u << p;
       resolved = resolved && fine && fabsf(e) <= 20.0f && fabsf(phi[p]) < 4.0f;
     }
     float d2[NP];

@@ -122,11 +122,12 @@ int side_streams(hipStream_t** out) {
   return BG_OK;
 }
 
-// rough relative cost of one event (FP32; FP64 about three times), for balancing classes
-// over the side streams
+// rough cost of one event in ns (generation with |A|^2 of 10^6 events, 4 10^5 beyond n = 8): for balancing
+// classes over the side streams and for pass_listed
 double event_cost(int n, int prec) {
-  static const double ns[13] = {0, 0, 0, 0, 0.31, 0.38, 0.47, 0.60, 0.75, 1.4, 2.7, 5.0, 8.7};
-  return ns[n] * (prec == 64 ? 3.0 : 1.0);
+  static const double ns[2][13] = {{0, 0, 0, 0, 0.055, 0.085, 0.15, 0.23, 0.36, 0.75, 1.05, 1.46, 2.0},
+                                   {0, 0, 0, 0, 0.065, 0.11, 0.17, 0.31, 0.52, 1.06, 1.57, 2.27, 3.25}};
+  return ns[prec == 64 ? 1 : 0][n];
 }
 
 // compute units of the current device (cached per device)
@@ -581,15 +582,21 @@ int plan_class(const bg_config& c, const GenClass& G, ClassPlan& P) {
 
 // Whether a staged class runs its recursion on the events that pass the cuts only (PassList): no
 // output of |A|^2 or log w, cuts that can reject, and a recursion long enough.  The list's two
-// launches and its writes take 10 to 18 us, lost where every event passes, and nothing is gained
-// within the first round or two of waves (2^17 lanes).  us per call of weights, observables and
-// totals, every event / list, at 14 TeV (0.4% pass at n = 8), and with cuts that all pass:
-//   n = 7 FP32 2^17 63 / 55 (60 / 69 all), 2^20 253 / 134 (230 / 249);  n = 8 FP32 2^17 77 / 66 (74 / 85),
-//   2^18 131 / 87, 2^20 383 / 159 (370 / 386), FP64 2^20 548 / 164 (531 / 550);
-//   n = 12 FP32 2^15 90 / 92, 2^16 155 / 102, 2^17 279 / 117 (278 / 288), 2^20 2000 / 293 (1989 / 2016).
+// launches and its writes take 8 to 16 us, lost where every event passes: a call of 60 us by event_cost
+// loses a ninth at most.  Nothing is gained within the first round or two of waves (2^17 lanes).  us per
+// call of weights, observables and totals, every event / list, at 14 TeV (0.4% pass at n = 8), at 1 TeV
+// (71% pass at n = 7, 10% at n = 12) and with cuts that all pass, either side of the line:
+//   n = 7 FP32 131072 63 / 54, 59 / 63, 60 / 68; 262144 93 / 70, 88 / 91, 88 / 97
+//   n = 8 FP32 131072 76 / 64, 73 / 82, 73 / 82; 196608 99 / 70, 95 / 90, 95 / 104
+//   n = 12 FP32 32768 90 / 92, 87 / 94, 87 / 96; 65536 156 / 104, 153 / 107, 154 / 162
+//   n = 7 FP64 131072 69 / 58, 65 / 74, 65 / 74; 262144 112 / 75, 107 / 105, 108 / 117
+//   n = 8 FP64 98304 90 / 66, 87 / 73, 88 / 95; 131072 97 / 74, 93 / 102, 94 / 103
+//   n = 10 FP64 32768 81 / 64, 78 / 69, 78 / 86; 49152 111 / 72, 109 / 96, 109 / 117
+// A cut in |eta| alone counts as none: |eta| < 2.5 keeps 57 to 72% of the events at 14 TeV (n = 12 to 4), 87
+// to 99% at a fixed energy.
 bool pass_listed(const bg_config& c, const ClassPlan& P, const GenClass& G) {
   return P.staged && !P.wform && !G.out.amp2 && !G.out.logw && (c.pt_min > 0 || c.dr_min > 0) &&
-         P.lanes * G.count >= (int64_t(1) << 17) && G.count * event_cost(c.n, c.prec) >= 3e5;
+         P.lanes * G.count >= (int64_t(1) << 17) && G.count * event_cost(c.n, c.prec) >= 6e4;
 }
 
 // Persistent multi-class launch over the FP32 classes ks (see bg_multi.hip).  Returns

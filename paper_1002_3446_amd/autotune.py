@@ -1,12 +1,12 @@
 """Launch-shape autotuner for libbg (needs a GPU).
 
 For every multiplicity n and recursion precision it times single-class bg_generate with
-64, 128 and 256 threads per workgroup and, where the library holds both, one or two lanes
-per event, and keeps the fastest; then, on the FP32 mixed workload
-(n = 4..12 with 2^(26-n) events each, one persistent launch), it tunes each class's tile
-length (events per lane per tile) by coordinate search, and finally records which of the
-three strategies for several classes (one after another, one persistent launch, classes on
-concurrent streams) is fastest for that workload.  The result is written to
+64, 128 and 256 threads per workgroup (FP32; the FP64 kernels do not go by the setting, which
+stays) and, where the library holds both, one or two lanes per event, and keeps the fastest;
+then, on the FP32 mixed workload (n = 4..12 with 2^(26-n) events each, one persistent launch),
+it tunes each class's tile length (events per lane per tile) by coordinate search, and
+finally records which of the three strategies for several classes (one after another, one
+persistent launch, classes on concurrent streams) is fastest for that workload.  The result is written to
 autotune.json next to this file, which the binding applies on import.
 
 Usage: python -m paper_1002_3446_amd.autotune [--prec 32|64|both] [--out PATH] [--scale S]
@@ -60,6 +60,12 @@ def wtensor_forms(n, prec):
     return (prec == 32 and n in (8, 10, 11, 12)) or (prec == 64 and n in (6, 10))
 
 
+def block_sizes(n, prec):
+    """Workgroup sizes to try: FP64 generation runs in workgroups of its own choice, so trying sizes there
+    would record noise, and the size set (bg_generate_noalloc's limit goes by it) is kept."""
+    return (64, 128, 256) if prec == 32 else (bg.get_launch(n, prec)[0],)
+
+
 def tune_single(prec=32, scale=0, log=print):
     """Workgroup size, lanes per event and recursion form of every single-class kernel."""
     shapes = {}
@@ -67,9 +73,10 @@ def tune_single(prec=32, scale=0, log=print):
         N = 1 << max(20 - scale, 26 - n - scale)
         cfg = bg.config(n, prec=prec, seed=0xB6000003 + n)
         out = bg.generate(cfg, N, outputs=OUTPUTS)
-        cands = [(lanes, 0, block) for lanes in lane_forms(n, prec) for block in (64, 128, 256)]
+        cands = [(lanes, 0, block) for lanes in lane_forms(n, prec) for block in block_sizes(n, prec)]
         if wtensor_forms(n, prec):
-            cands.append((0, 1, 64))   # W-tensor: fixed 64-lane workgroups, lanes unused
+            # W-tensor: fixed 64-lane workgroups, lanes unused
+            cands.append((0, 1, 64 if prec == 32 else cands[0][2]))
         best = None
         for lanes, form, block in cands:
             bg.set_form(n, prec, form)
@@ -127,7 +134,8 @@ def main():
     t0 = time.time()
     for prec in precs:
         for n in NS:
-            bg.set_launch(n, prec, 0, 0)   # start from the built-in defaults
+            if prec == 32:
+                bg.set_launch(n, prec, 0, 0)   # start from the built-in defaults
             bg.set_lanes(n, prec, 0)
             bg.set_form(n, prec, 0)
     bg.set_mixed_launch(bg.MIXED_PERSISTENT)

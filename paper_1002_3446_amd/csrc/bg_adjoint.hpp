@@ -323,14 +323,14 @@ __host__ __device__ __forceinline__ void rambo_init_adj(const RamboMap& m, const
 }
 
 // Adjoint of rambo_q: rho adjoints from q adjoints, with no division by q0 (zero where r3 r4 = 1);
-// at r1 = 0 or 1 the derivative in r1 is infinite and the others are finite.
-__host__ __device__ __forceinline__ void rambo_q_adj(double r1, double r2, double r3, double r4, const double qb[4],
-                                                     double rb[4]) {
+// at r1 = 0 or 1 the derivative in r1 is infinite and the others are finite.  q0: the energy,
+// -log_fp64(r3 r4), from rambo_q.
+__host__ __device__ __forceinline__ void rambo_q_adj(double r1, double r2, double r3, double r4, double q0,
+                                                     const double qb[4], double rb[4]) {
   const double c = 2.0 * r1 - 1.0;
   const double st = sqrt_fp64(1.0 - c * c);
   double sp, cp;
   sincospi_fp64(2.0 * r2, &sp, &cp);
-  const double q0 = -log_fp64(r3 * r4);
   const double q0b = qb[0] + qb[1] * st * cp + qb[2] * st * sp + qb[3] * c;
   const double stb = q0 * (qb[1] * cp + qb[2] * sp);
   const double cpb = q0 * st * qb[1], spb = q0 * st * qb[2];
@@ -475,7 +475,7 @@ __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const Gr
       double qbt[4], rb[4];
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) qbt[mu] = qb[t][mu] + Qb[mu];
-      rambo_q_adj(u[0], u[1], u[2], u[3], qbt, rb);
+      rambo_q_adj(u[0], u[1], u[2], u[3], K.q[t][0], qbt, rb);
 #pragma unroll
       for (int c = 0; c < 4; ++c) u[c] = gw * rb[c];
     }

@@ -21,7 +21,7 @@ int main() {
       double r[4], qb[4], rb[4];
       for (double& x : r) x = word();
       for (double& x : qb) x = word();
-      bgk::rambo_q_adj(r[0], r[1], r[2], r[3], qb, rb);
+      bgk::rambo_q_adj(r[0], r[1], r[2], r[3], -bgk::log_fp64(r[2] * r[3]), qb, rb);
       std::printf("%a %a %a %a\n", rb[0], rb[1], rb[2], rb[3]);
     } else if (tag[0] == 'P') {
       double p[4] = {0.0}, er[4] = {0.0}, ei[4] = {0.0}, pb[4] = {0.0};

@@ -3,7 +3,7 @@
 //
 // Lane g of a group holds the Lorentz components mu = g C .. g C + C - 1 (C = 4 / G) of
 // every current and span scalar's share, so a lane needs about 1/G of the registers of
-// the one-lane form; at n >= 10 in FP32 and n >= 7 in FP64 the one-lane form exceeds the
+// the one-lane form; at n >= 10 in FP32 and n >= 9 in FP64 the one-lane form exceeds the
 // 512 registers a lane can address and spills to scratch memory.  Minkowski products are
 // formed per lane over its components with their metric signs sigma_mu = (+,-,-,-) and
 // completed across the group by DPP lane permutations; every lane of the group ends with
@@ -448,7 +448,7 @@ __device__ __forceinline__ void bg_amplitude_g(const LaneShare<G, T>& ls, const 
 }
 
 // ----------------------------------------------------------------------------------------
-// FP64 with an event on a pair of lanes (n = 6, n >= 9).  What limits these classes is where a lane
+// FP64 with an event on a pair of lanes (n >= 6; n = 7, 8 in short calls).  What limits these classes is where a lane
 // keeps its currents (n = 12: 498 registers of 512), so, as in the one-lane FP64 form
 // (bg_amplitude_d), the covariant leg momenta and the span scalars -S/2 live in LDS and brackets
 // accumulate V / 2 in one vector.  Lane 0 holds the components (0, 1), lane 1 (3, 2): the first
@@ -580,6 +580,7 @@ __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (
     const double2 c = ks.template scalar<SP::at(i + 1, B)>();
     paxpy<i == A>(c.x, c.y, J[SP::at(A, i)], X);
   });
+  const double hsg = 0.5 * ks.sg;
   double ka[2];
   static_for<A, B>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
@@ -594,19 +595,17 @@ __device__ __forceinline__ void span_vertex_p(const PairSpan<L>& ks, const cvp (
     const cvp xs = pair_signed<LA>(ks.sg, J[PA]);
     double dr, di, ar, ai, br, bi;
     pdot<LA, LB>(xs, J[PB], dr, di);
-    dr *= 0.5;
-    di *= 0.5;
     prdot<LA>(J[PA], kb, ar, ai);
     prdot<LB>(J[PB], ka, br, bi);
     paxpy<LB>(ar, ai, J[PB], X);
     paxpy<LA>(-br, -bi, J[PA], X);
-    const double d0 = ks.sg * (ka[0] - kb[0]), d1 = kb[1] - ka[1];
+    const double d0 = hsg * (ka[0] - kb[0]), d1 = 0.5 * (kb[1] - ka[1]);
     X.re[0] = fmac(dr, d0, X.re[0]);
     X.im[0] = fmac(di, d0, X.im[0]);
     X.re[1] = fmac(dr, d1, X.re[1]);
     X.im[1] = fmac(di, d1, X.im[1]);
-    sr -= dr;
-    si -= di;
+    sr = fmac(-0.5, dr, sr);
+    si = fmac(-0.5, di, si);
     // the four-gluon pairs of this left current
     if constexpr (!kApart)
       static_for<i + 1, B>([&](auto jc) {
@@ -667,9 +666,9 @@ __device__ __forceinline__ void bg_amplitude_p(const PairSpan<L>& ks, const cvp 
 // issue slots (measured: 16.5 cycles, 32 to its result, no overlap with FP64 vector work) in place
 // of six.  Its columns are the lanes l, l + 16, l + 32, l + 48: lane 16 c + e holds component c of
 // event e of the wave.  Generation, 2^18 events, with the sums by DPP, scalars and momenta in
-// registers and one wave per SIMD: n = 11 819 -> 598 us, n = 12 1172 -> 868 us.  The instruction ignores the execution mask, so every lane of a wave runs
-// the recursion (callers clamp the event index).  No element of A is zero: a column's infinities
-// and NaN stay its own.
+// registers and one wave per SIMD: n = 11 819 -> 598 us, n = 12 1172 -> 868 us.  The instruction
+// ignores the execution mask, so every lane of a wave runs the recursion (callers clamp the event
+// index).  No element of A is zero: a column's infinities and NaN stay its own.
 // ----------------------------------------------------------------------------------------
 struct cvq {
   double re, im;
@@ -707,9 +706,10 @@ struct QuadSpan {
   __device__ __forceinline__ void put_scalar(double r, double i) const { put[(S - L) * 32] = (c & 1) ? i : r; }
   template <int S>
   __device__ __forceinline__ double2 scalar() const { return get[(S - L) * 16]; }
-  __device__ __forceinline__ void dot(const cvq& x, const cvq& y, double& r, double& i) const {
-    r = quad_sum(sg, fmac(-x.im, y.im, x.re * y.re));
-    i = quad_sum(sg, fmac(x.im, y.re, x.re * y.im));
+  // x . y times scale
+  __device__ __forceinline__ void dot(const cvq& x, const cvq& y, double& r, double& i, double scale = 1.0) const {
+    r = quad_sum(scale * sg, fmac(-x.im, y.im, x.re * y.re));
+    i = quad_sum(scale * sg, fmac(x.im, y.re, x.re * y.im));
   }
   __device__ __forceinline__ void rdot(const cvq& x, double k, double& r, double& i) const {
     r = quad_sum(1.0, x.re * k);
@@ -746,9 +746,7 @@ __device__ __forceinline__ void span_vertex_q(const QuadSpan<L>& ks, const cvq (
     ka = i == A ? ks.template sum<A, A>() : ka + ks.template sum<i, i>();
     const double kb = ks.template sum<i + 1, B>();
     double dr, di, ar, ai, br, bi;
-    ks.dot(J[PA], J[PB], dr, di);
-    dr *= 0.5;
-    di *= 0.5;
+    ks.dot(J[PA], J[PB], dr, di, 0.5);
     ks.rdot(J[PA], kb, ar, ai);
     ks.rdot(J[PB], ka, br, bi);
     const double dk = ks.sg * (ka - kb);

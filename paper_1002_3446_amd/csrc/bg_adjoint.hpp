@@ -359,8 +359,8 @@ struct GradKin {
 // rows start in all banks), and their adjoints on the way back.  A lane's words lie together in
 // memory and it takes them in the order of its colour ordering: read from there they cost a chain of
 // two loads and a line per lane and word, while the workgroup's rows are one contiguous block,
-// whose loads depend on nothing (second kernel, n = 8 FP32, 2^20 events:
-// 332 -> 274 us; n = 6 FP64, 2 10^5: 39 -> 34).  Called by every lane of the workgroup.
+// whose loads depend on nothing (second kernel, when the step was made: n = 8 FP32, 2^20 events
+// 332 -> 274 us; n = 6 FP64, 2 10^5 39 -> 34).  Called by every lane of the workgroup.
 template <int N>
 struct DrawRows {
   static constexpr int W = 4 * (N - 2), kStride = W + 1;
@@ -700,11 +700,11 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, 1)
 
 // Second gradient kernel (one lane per event): from the recursion's adjoints that k_grad or
 // k_grad_g left in pbuf, the helicity sources' and momenta's adjoints (CM frame), RAMBO's
-// conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were
-// completed by the first, but for the draws' zeros.  Bound by
-// its 700 B an event (2.7 TB/s) and the FP64 chains at two waves per SIMD: 5141 -> 2731 instructions
-// and 680 -> 256 B of adjoints an event, then the rows in LDS: n = 8 FP32 442 -> 332 -> 274 us per
-// 2^20 events, n = 6 FP64 46 -> 39 -> 34 per 2 10^5.
+// conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were completed by the first, but for the
+// draws' zeros.  Bound by its 700 B an event (2.5 TB/s) and the FP64 chains: 5141 -> 4149 instructions a
+// wave and 680 -> 256 B of adjoints an event, and the rows in LDS: n = 8 FP32 442 -> 293 us per 2^20
+// events, n = 6 FP64 46 -> 37 per 2 10^5.  (With products of reciprocals for the rounded quotients 3239
+// instructions, 273 and 34 us, and results further from their exact values.)
 template <int N, typename T>
 __device__ __forceinline__ void grad_back_event(const GradArgs& G, int64_t i, double* row) {
   using R = GradRaw<N>;

@@ -836,7 +836,7 @@ struct Fp64Span {
 };
 
 // The products for n = 7, 8 (L >= 6) in the order of the two-lane form, (0, 1) and (3, 2) summed
-// apart, so that both forms give the same bits and short calls can take that one (pair_call).
+// apart, so that both forms give the same bits and short calls can take that one (kernel_lanes).
 template <bool LX, bool LY>
 __device__ __forceinline__ void dot_pairs(const cv4<double>& x, const cv4<double>& y, double& r, double& i) {
 #pragma clang fp contract(off)

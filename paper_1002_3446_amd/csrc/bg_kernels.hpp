@@ -949,7 +949,7 @@ constexpr int grouped_lds_bytes(int block) {
 }
 
 // Waves per SIMD of the grouped kernels.  Four-lane FP64 runs two, which cover the latency of
-// the matrix sums and the LDS: at n = 12 that means 588 B of scratch per lane, but one wave
+// the matrix sums and the LDS: at n = 12 that means 480 B of scratch per lane (bg_amp2 520), but one wave
 // without scratch is slower (2^18 events: n = 11 731 -> 598 us, n = 12 1000 -> 868 us; n = 10 fits).
 // Elsewhere the currents take more than half the registers.
 template <typename T, int G>

@@ -32,16 +32,16 @@ constexpr int split_words(int n) { return 4 * (n - 1) + 5; }
 // Lane forms of a class as a launch setting (bg_set_lanes), defaulting to default_lanes: one
 // event per lane (FP32 n <= 9, FP64 n <= 6); two lanes per event from FP32 n = 9 and FP64 n = 6 on
 // (the one-lane form would spill kilobytes per lane at large n); four lanes for FP64 n >= 10, where
-// two still spill (FP64 n = 12: 2.9 KB per lane with two, 448 B with four).  FP64 n = 7, 8 have no
+// two still spill (FP64 n = 12: 2.0 KB per lane with two, 480 B with four).  FP64 n = 7, 8 have no
 // setting 1: behind the setting 2 stands the recursion with one event per lane, whose LDS leg
 // momenta and span scalars leave its registers to the currents, and in short calls the two-lane
 // form (kernel_lanes).  us, two lanes / one: bg_amp2, n = 7, 5 10^5 events 162 / 104; generation, n = 8,
-// 1.5 10^6 events 965 / 782.
+// 1.5 10^6 events 965 / 754.
 constexpr bool has_one_lane(int n, int prec) { return prec == 32 ? n <= 9 : n <= 6; }
 constexpr bool has_lane_pairs(int n, int prec) { return prec == 32 ? n >= 9 : n >= 6; }
 constexpr bool has_lane_quads(int n, int prec) { return prec == 64 && n >= 10; }
 constexpr int default_lanes(int n, int prec) { return prec == 32 ? (n >= 10 ? 2 : 1) : (n >= 10 ? 4 : (n >= 7 ? 2 : 1)); }
-// Up to 2^15 events, where the two-lane form's waves are at most one per SIMD, that form answers
+// Up to 2^15 events, where the two-lane form's waves are at most one per SIMD (of 1024), that form answers
 // sooner (bg_amp2, 2000 to 20000 events, one lane / two: n = 7 14 / 10 us, n = 8 25 / 17; both give
 // the same bits): kernel_lanes is 2 there.
 constexpr bool one_or_pair(int n, int prec) { return prec == 64 && (n == 7 || n == 8); }

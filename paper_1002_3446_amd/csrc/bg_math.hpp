@@ -20,8 +20,9 @@ __host__ __device__ __forceinline__ double coef(double c) {
 }
 
 // a / b for finite a and a normal b with a quotient in the normal range: the correctly rounded
-// quotient by the same refinement the general division uses, without its range scaling and
-// special cases (a third of its instructions).
+// quotient by Markstein's method (P. Markstein, IBM J. Res. Dev. 34, 1990: Newton steps on the
+// hardware's estimate of 1 / b, then one correction of the quotient by its exact remainder), without
+// the range scaling and special cases of the general division (a third of its instructions).
 __host__ __device__ __forceinline__ double recip_refine(double b) {
 #if defined(__HIP_DEVICE_COMPILE__)
   double r = __builtin_amdgcn_rcp(b);
@@ -45,8 +46,10 @@ __host__ __device__ __forceinline__ double div_refined(double a, double b, doubl
 
 __host__ __device__ __forceinline__ double div_fp64(double a, double b) { return div_refined(a, b, recip_refine(b)); }
 
-// sqrt(x) for x = 0 or x in [2^-767, inf): the correctly rounded root by the same refinement
-// the general square root uses, without its range scaling; negative x and NaN give NaN.
+// sqrt(x) for x = 0 or x in [2^-767, inf): the correctly rounded root by Goldschmidt's iteration from
+// the hardware's estimate of 1 / sqrt(x) (g -> sqrt(x) and h -> 1 / (2 sqrt(x)) together) and
+// Markstein's corrections of g by its exact remainder, without the range scaling of the general
+// square root; negative x and NaN give NaN.
 __host__ __device__ __forceinline__ double sqrt_fp64(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const double y = __builtin_amdgcn_rsq(x);

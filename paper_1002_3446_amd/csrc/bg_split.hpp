@@ -20,7 +20,7 @@ namespace bgk {
 // another, word w of event j at buf[((j / 64) * kWords + w) * 64 + j % 64], so that a wave
 // reads one contiguous block.  Words: the centre-of-mass momenta of recursion positions
 // 1..N-1 (position t, component mu at 4 (t - 1) + mu; position 0 is always the beam leg 0,
-// which follows from s_hat), s_hat, the packed word (event_word); then, written and read only
+// which follows from s_hat), s_hat, the packed word (EventWord); then, written and read only
 // when they are used, x1, x2 (with the log w output) and the weight factor of the dynamic scale
 // (scale_ratio).
 template <int N>

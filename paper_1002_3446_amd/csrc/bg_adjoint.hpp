@@ -468,10 +468,29 @@ __device__ __forceinline__ void grad_back(const GradArgs& G, int64_t i, const Gr
   }
   double Qb[4] = {0.0, 0.0, 0.0, 0.0};
   rambo_init_adj(K.map, K.Q, A, Qb, rsb);
+  // an ordering is not checked: of a leg that it names twice the last position's adjoint is kept, a leg
+  // that it leaves out has none
+  uint32_t leg[N], named = 1u;
 #pragma unroll
   for (int t = 1; t < N; ++t) {
-    if (K.leg[t] >= 2u) {
-      double* u = row + 4 * (K.leg[t] - 2u);
+    leg[t] = K.leg[t];
+    named |= 1u << leg[t];
+  }
+  if (named != (1u << N) - 1u) {
+    uint32_t later = 0;
+#pragma unroll
+    for (int t = N - 1; t >= 1; --t) {
+      const uint32_t bit = 1u << leg[t];
+      leg[t] = (later & bit) ? 0u : leg[t];
+      later |= bit;
+    }
+    for (int c = 0; c < DrawRows<N>::W; ++c)
+      if (!((named >> (c / 4 + 2)) & 1u)) row[c] = 0.0;
+  }
+#pragma unroll
+  for (int t = 1; t < N; ++t) {
+    if (leg[t] >= 2u) {
+      double* u = row + 4 * (leg[t] - 2u);
       double qbt[4], rb[4];
 #pragma unroll
       for (int mu = 0; mu < 4; ++mu) qbt[mu] = qb[t][mu] + Qb[mu];
@@ -701,9 +720,9 @@ __global__ __launch_bounds__(kLdsLanes) __attribute__((amdgpu_waves_per_eu(1, 1)
 // Second gradient kernel (one lane per event): from the recursion's adjoints that k_grad or
 // k_grad_g left in pbuf, the helicity sources' and momenta's adjoints (CM frame), RAMBO's
 // conformal map, q(rho) and x1, x2.  Events with |A|^2 = 0 were completed by the first, but for the
-// draws' zeros.  Bound by its 700 B an event (2.5 TB/s) and the FP64 chains: 5141 -> 4149 instructions a
-// wave and 680 -> 256 B of adjoints an event, and the rows in LDS: n = 8 FP32 442 -> 293 us per 2^20
-// events, n = 6 FP64 46 -> 37 per 2 10^5.  (With products of reciprocals for the rounded quotients 3239
+// draws' zeros.  Bound by its 700 B an event (2.5 TB/s) and the FP64 chains: 5141 -> 4292 instructions a
+// wave and 680 -> 256 B of adjoints an event, and the rows in LDS: n = 8 FP32 442 -> 298 us per 2^20
+// events, n = 6 FP64 46 -> 38 per 2 10^5.  (With products of reciprocals for the rounded quotients 3239
 // instructions, 273 and 34 us, and results further from their exact values.)
 template <int N, typename T>
 __device__ __forceinline__ void grad_back_event(const GradArgs& G, int64_t i, double* row) {
